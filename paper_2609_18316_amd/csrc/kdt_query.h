@@ -2,6 +2,8 @@
 // query, grouping and batched kernels.
 #pragma once
 
+#include <type_traits>
+
 #include "kdt_internal.h"
 
 namespace kdt {
@@ -54,9 +56,9 @@ struct FillOut {
 // algorithmic bytes of the roofline.  Slots: kVisitNodes / kVisitPoints /
 // kVisitInsert for one traversal per lane (nodes visited, i.e. node boxes
 // tested -- the root and both children of every expanded node --, leaf
-// records scanned, records read again to insert a candidate), kVisitReload
-// for a box read again when its node leaves the stack (the stack keeps node
-// ids only), kVisitWaveNodes / kVisitWavePoints for the wave-shared
+// records scanned, candidates among them), kVisitReload
+// for a box read again when its node leaves the stack (sliding-midpoint
+// trees, whose stack keeps node ids only), kVisitWaveNodes / kVisitWavePoints for the wave-shared
 // traversals (one box read and one leaf staged into LDS count once per
 // wave).  Each slot has kVisitShards
 // counters (workgroup b adds to shard b % kVisitShards).  In the product
@@ -87,7 +89,6 @@ __device__ __forceinline__ void count_visit(const TreeView& t, int slot, uint32_
 // (Sec. 2.1, data-dependent depth) stores per node (left child or -1 for a
 // leaf, first point, end point, level); its right child follows the left.
 struct MedianShape {
-  static constexpr bool kUniformLeaves = true;
   int64_t n;
   int levels;
   uint32_t first_leaf;
@@ -104,7 +105,6 @@ struct MedianShape {
 };
 
 struct StoredShape {
-  static constexpr bool kUniformLeaves = false;
   const int4* node;
   __device__ __forceinline__ explicit StoredShape(const TreeView& t) : node(t.nodes) {}
   __device__ __forceinline__ bool is_leaf(uint32_t v) const { return node[v].x < 0; }
@@ -241,9 +241,12 @@ constexpr uint64_t kEmptyKey = 0x7F800000FFFFFFFFull;
 // (keys below 2^52 are subnormal doubles, which the float64 min/max keep
 // exact because float64 subnormals are not flushed).  That turns each
 // compare-and-carry step into one v_min_f64 and one v_max_f64.
+constexpr int kListBatch = 16;  // keys that a merge takes
+
 template <int KC>
 struct TopK {
   double a[KC];
+  using Key = double;
   __device__ __forceinline__ void init(int k) {
 #pragma unroll
     for (int i = 0; i < KC; ++i) a[i] = (i < KC - k) ? 0.0 : __longlong_as_double((long long)kEmptyKey);
@@ -277,7 +280,63 @@ struct TopK {
     }
   }
   __device__ __forceinline__ void offer(float d2, int32_t id);
+  // The KC smallest keys of the list and of a batch of keys (in any order;
+  // kEmptyKey where there is none): the batch is sorted, its smallest keys
+  // are laid in reverse against the list's largest -- the smaller of each
+  // pair stays -- and the bitonic list that leaves is sorted.
+  __device__ __forceinline__ void merge(double (&c)[kListBatch]);
 };
+
+// a <- the smaller, b <- the larger of two keys (see TopK::insert), both in
+// the registers they came in: with two fresh results per step the register
+// allocator keeps a second copy of the list (k = 32: 165 instead of 130
+// VGPRs), which costs a wave per SIMD and more time than the move.
+__device__ __forceinline__ void order_in_place(double& a, double& b) {
+  double lo;
+  asm("v_min_f64 %0, %1, %2\n\tv_max_f64 %2, %1, %2\n\tv_mov_b64 %1, %0"
+      : "=&v"(lo), "+v"(a), "+v"(b));
+}
+__device__ __forceinline__ void order_in_place(uint32_t& a, uint32_t& b) {
+  uint32_t lo;
+  asm("v_min_u32 %0, %1, %2\n\tv_max_u32 %2, %1, %2\n\tv_mov_b32 %1, %0"
+      : "=&v"(lo), "+v"(a), "+v"(b));
+}
+
+// Batcher's odd-even merge sort (K. E. Batcher, "Sorting networks and their
+// applications", AFIPS SJCC 1968).
+template <class T, int N>
+__device__ __forceinline__ void sort_network(T (&c)[N]) {
+#pragma unroll
+  for (int p = 1; p < N; p *= 2)
+#pragma unroll
+    for (int k = p; k >= 1; k /= 2)
+#pragma unroll
+      for (int j = k % p; j + k < N; j += 2 * k)
+#pragma unroll
+        for (int i = 0; i < k; ++i)
+          if (i + j + k < N && (i + j) / (2 * p) == (i + j + k) / (2 * p))
+            order_in_place(c[i + j], c[i + j + k]);
+}
+
+// Sorts a bitonic sequence (Batcher's half-cleaners).
+template <class T, int N>
+__device__ __forceinline__ void sort_bitonic(T (&a)[N]) {
+#pragma unroll
+  for (int k = N / 2; k >= 1; k /= 2)
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+      if ((i & k) == 0) order_in_place(a[i], a[i + k]);
+}
+
+template <int KC>
+__device__ __forceinline__ void TopK<KC>::merge(double (&c)[kListBatch]) {
+  sort_network(c);
+  constexpr int M = KC < kListBatch ? KC : kListBatch;
+#pragma unroll
+  for (int i = 0; i < M; ++i)
+    asm("v_min_f64 %0, %0, %1" : "+v"(a[KC - M + i]) : "v"(c[M - 1 - i]));
+  sort_bitonic(a);
+}
 
 __device__ __forceinline__ uint64_t make_key(float d2, int32_t idx) {
   return ((uint64_t)__float_as_uint(d2) << 32) | (uint32_t)idx;
@@ -298,6 +357,7 @@ __device__ __forceinline__ void TopK<KC>::offer(float d2, int32_t id) {
 template <int KC>
 struct TopD {
   uint32_t a[KC];
+  using Key = uint32_t;
   __device__ __forceinline__ void init(int k) {
 #pragma unroll
     for (int i = 0; i < KC; ++i) a[i] = (i < KC - k) ? 0u : 0x7F800000u;
@@ -306,16 +366,34 @@ struct TopD {
   __device__ __forceinline__ void offer(float d2, int32_t) {
     const uint32_t x = __float_as_uint(d2);
     if (x < a[KC - 1]) {
-      uint32_t carry = x;
+      // every slot becomes the middle one of (slot below, x, itself), from
+      // the top down so that the slot below is still the old one: one
+      // instruction per slot where compare-and-carry takes two
 #pragma unroll
-      for (int i = 0; i < KC; ++i) {
-        const uint32_t up = max(a[i], carry);
-        a[i] = min(a[i], carry);
-        carry = up;
-      }
+      for (int i = KC - 1; i > 0; --i)
+        asm("v_med3_u32 %0, %1, %2, %0" : "+v"(a[i]) : "v"(a[i - 1]), "v"(x));
+      a[0] = min(a[0], x);
     }
   }
+  // As TopK::merge.
+  __device__ __forceinline__ void merge(uint32_t (&c)[kListBatch]) {
+    sort_network(c);
+    constexpr int M = KC < kListBatch ? KC : kListBatch;
+#pragma unroll
+    for (int i = 0; i < M; ++i) a[KC - M + i] = min(a[KC - M + i], c[M - 1 - i]);
+    sort_bitonic(a);
+  }
 };
+
+// The entry of a leaf point in a merge's batch (empty: no such point).
+template <int KC>
+__device__ __forceinline__ double batch_key(const TopK<KC>&, bool there, float d2, int32_t id) {
+  return __longlong_as_double((long long)(there ? make_key(d2, id) : kEmptyKey));
+}
+template <int KC>
+__device__ __forceinline__ uint32_t batch_key(const TopD<KC>&, bool there, float d2, int32_t) {
+  return there ? __float_as_uint(d2) : 0x7F800000u;
+}
 
 // Open-space metric of the traversals: the point distance (Eq. 1, p = 2) and
 // the lower and upper bounds over a node box.  Other metrics (the D-torus of
@@ -335,17 +413,212 @@ struct OpenMetric {
   }
 };
 
+#ifndef KNN_SM
+#define KNN_SM i
+#endif
+// Which lists take a leaf's points in sorted batches (ListMerge<...>::kOn): those of
+// 17 to 32 entries below five dimensions.  Inserting one key costs 64
+// (TopK) or 32 (TopD) instructions at k = 32 and runs for the wave when any
+// lane inserts -- about ten times per leaf of 16 points --, a merge of 16 keys
+// 430, whatever the number of candidates; a merge also needs no second pass
+// over the points.  Measured against insertion alone: 5.10 and 5.88 ms for 2^22
+// external queries on 2^24 clustered points (k = 32), 2.66 and 3.12 ms for the
+// smoothing lengths of 2^22 points.  At 16 entries the merge loses its 16
+// registers' worth of waves for nothing (1.86 against 1.78 ms, 2^21 points), at
+// 64 it does not fit the registers, and in 8 dimensions the batch's
+// coordinates do not (8.9 against 7.7 ms, 200003 points, k = 16).
+// kMin: the wave merges when some lane has more candidates than this, else
+// each lane inserts its own (equal within 1 % from 1 to 5).
+template <class List, int D>
+struct ListMerge;
+template <int KC, int D>
+struct ListMerge<TopK<KC>, D> {
+  static constexpr bool kOn = KC == 32 && D <= 4;
+  static constexpr int kMin = 3;
+};
+template <int KC, int D>
+struct ListMerge<TopD<KC>, D> {
+  static constexpr bool kOn = KC == 32 && D <= 4;
+  static constexpr int kMin = 5;
+};
+// Waves per SIMD that a per-lane kNN kernel is compiled for: its list with a
+// batch takes 128 VGPRs, which the compiler reaches only when asked to.
+template <int D, int KC, bool KTH, class Shape = MedianShape>
+constexpr int lane_waves() {
+  return !KTH && std::is_same_v<Shape, MedianShape> && ListMerge<TopK<KC>, D>::kOn ? 4 : 1;
+}
+// The list length of k for kNN over n points with one traversal per lane: k
+// rounded up, except that a merge reads kListBatch consecutive points, so
+// smaller trees take a list that inserts.
+inline int lane_list(int k, int64_t n) {
+  return k <= 8 ? 8 : k <= 16 ? 16 : k <= 32 && n >= kListBatch ? 32 : 64;
+}
+
+// Offers the cnt points from b on, a lane's leaf, to its list; most: no leaf
+// of the tree is larger (wave-uniform).  Without kMerge, in two passes per 32
+// points: the first computes every distance and marks the points that can
+// enter the list (float test against the current k-th distance, ties kept);
+// the second inserts the marked points, recomputing their distances.  The
+// wave pays for an insertion when any lane inserts, so marking first makes it
+// pay for the largest number of insertions of one lane, not for every
+// position at which some lane inserts.  With kMerge, 16 points at a time: their
+// keys stay in registers and are merged into the list at once (ListMerge), except for a
+// short rest of a leaf (at most kFewPoints: smoothing lengths on leaves of 20 points
+// 3.00 against 3.52 ms, 5000011 points) and where no lane has many candidates.
+template <int D, bool kMerge, class List, class Metric>
+__device__ __forceinline__ void leaf_offer(const TreeView& t, int32_t b, int cnt, int most,
+                                           const float p[D], List& best, const Metric& metric) {
+  constexpr int B = kMerge ? kListBatch : 32;
+  constexpr int kFewPoints = 8;
+  for (int o = 0; o < cnt; o += B) {
+    const float w = best.worst_d2();
+    const int m = min(cnt - o, B);
+    const int32_t c = b + o;
+    int32_t base = c;
+    uint32_t mask = 0;
+    bool batch = false;
+    if constexpr (kMerge) batch = most - o > kFewPoints;
+    if (batch) {
+      if constexpr (kMerge) {
+        // the B points from base on, which end inside the array
+        base = max(min(c, (int32_t)t.n - B), 0);
+        const float* r = t.rec + (int64_t)base * rec_stride(D);
+        const uint32_t valid = ((1u << m) - 1u) << (c - base);
+        typename List::Key key[B];
+#pragma unroll
+        for (int i = 0; i < B; ++i) {
+          float x[D];
+          int32_t id = 0;
+          load_rec<D>(r, i, x, id);
+          const float d2 = metric.dist(x, p);
+          mask |= (uint32_t)(d2 <= w) << i;
+          key[i] = batch_key(best, (valid >> i) & 1u, d2, id);
+          // built here, not later from the loaded record: registers
+          asm volatile("" : "+v"(key[i]));
+          if (i % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+        }
+        mask &= valid;
+        KDT_LANE_VISIT(t, kVisitInsert, __popc(mask));
+        // runs once at most; as a loop the list keeps its registers, as a
+        // branch the compiler copies it (153 instead of 128 VGPRs)
+        uint32_t go = __any(__popc(mask) > ListMerge<List, D>::kMin);
+        while (go) {
+          best.merge(key);
+          mask = 0;
+          asm volatile("v_mov_b32 %0, 0" : "=v"(go));
+        }
+      }
+    } else {
+#pragma unroll 1
+      for (int i = 0; i < m; ++i) {
+        float x[D];
+        int32_t id = 0;
+        load_rec<D>(t.rec, c + i, x, id);
+        mask |= (uint32_t)(metric.dist(x, p) <= w) << i;
+      }
+    }
+    if (!batch) KDT_LANE_VISIT(t, kVisitInsert, __popc(mask));
+    while (mask) {
+      const int i = __builtin_ctz(mask);
+      mask &= mask - 1;
+      float x[D];
+      int32_t id = 0;
+      load_rec<D>(t.rec, base + i, x, id);
+      best.offer(metric.dist(x, p), id);
+    }
+  }
+}
+
+// knn_one over a median tree.  A node's box distance is stored when its sibling is
+// descended into, one entry per level of the lane's path; which node it was
+// follows from the path.
+//
+// What bounds it: instructions, and the waves' divergence multiplies them -- a
+// lane visits 15 leaves and 56 inner nodes (2^22 uniform queries, 2^24
+// clustered points, k = 32), but when every lane walks to its next leaf before
+// any leaf is scanned the wave pays for 31 and 251, because the others wait
+// for the lane whose walk is the longest.  So the wave votes each round: its
+// lanes take one step down (or back), until kWait times as many wait at a leaf as still
+// walk; then the leaves are scanned.  That leaves 25 and 142, with
+// 5.08 instead of 5.99 ms (kWait 1 / 2 / 4 / never all waiting: 5.53 / 5.14 / 5.08 /
+// 5.64 ms).  Lists that insert do best at 6 (2^21 points, k = 8, clustered:
+// 1.33, at 3 1.35, at 1 1.55 ms); in 8 dimensions, where a step costs
+// as much as a third of a leaf, at 2 (200003 points, k = 16, normal:
+// 10.2, at 3 10.4, at 6 10.8 ms).
+// Whole call, before and after the vote and the merge: 6.64 and 5.10 ms; smoothing
+// lengths of 5000011 points 5.26 and 3.00 ms.
+template <int D, bool kMerge, class List, class Metric>
+__device__ __forceinline__ void knn_median(const TreeView& t, const float p[D], List& best,
+                                           uint32_t* stk, int ld, const Metric& metric) {
+  constexpr int kWait = D > 4 ? 2 : kMerge ? 4 : 6;
+  const uint32_t first = 1u << t.levels;
+  const int lmax = (int)((t.n + (int64_t(1) << t.levels) - 1) >> t.levels);
+  uint32_t h = 1;     // 1-based heap id of the lane's node (children 2h, 2h + 1)
+  uint32_t pend = 0;  // bit l: the sibling of the path's level-l node waits
+  bool more = true;
+  KDT_LANE_VISIT(t, kVisitNodes, 1);
+  while (more) {
+    const bool leaf = h >= first;
+    const int nat = __popcll(__ballot(leaf)), nrun = __popcll(__ballot(!leaf));
+    // (no lane walks: scan.)  The vote is the same in every lane; kept in a
+    // vector register, it is a branch like the others to the compiler, which
+    // copies the list around branches that it knows to be uniform.
+    uint32_t scan = nat >= nrun * kWait;
+    asm volatile("" : "+v"(scan));
+    bool pop = false;
+    if (scan) {
+      if (leaf) {
+        const int64_t j = h - first;
+        const int32_t b = (int32_t)((j * t.n) >> t.levels);
+        const int32_t e = (int32_t)(((j + 1) * t.n) >> t.levels);
+        KDT_LANE_VISIT(t, kVisitPoints, e - b);
+        leaf_offer<D, kMerge>(t, b, e - b, lmax, p, best, metric);
+        pop = true;
+      }
+    } else if (!leaf) {
+      const uint32_t c0 = 2 * h;
+      float lo[D], hi[D];
+      KDT_LANE_VISIT(t, kVisitNodes, 2);
+      load_box<D>(t.box, c0 - 1, lo, hi);
+      const float d0 = metric.mindist(lo, hi, p);
+      load_box<D>(t.box, c0, lo, hi);
+      const float d1 = metric.mindist(lo, hi, p);
+      const float dn = fminf(d0, d1), df = fmaxf(d0, d1);
+      const float w = best.worst_d2();
+      const int lev = 32 - __clz(h);  // of the children
+      if (df <= w) {
+        pend |= 1u << lev;
+        stk[lev * ld] = __float_as_uint(df);
+      }
+      h = c0 + (d0 <= d1 ? 0u : 1u);
+      pop = !(dn <= w);
+    }
+    const float w = best.worst_d2();
+    while (pop) {
+      if (pend != 0) {
+        const int l = 31 - __clz(pend);
+        pend ^= 1u << l;
+        h = (h >> (31 - __clz(h) - l)) ^ 1u;
+        pop = !(__uint_as_float(stk[l * ld]) <= w);
+      } else {
+        more = pop = false;
+      }
+    }
+  }
+}
+
 // kNN of one query p over tree t (Algorithm 2 semantics): depth-first, nearer
 // child first, a node is skipped when its box is farther than the current
 // k-th candidate.  `stk` is this lane's column of an LDS stack with stride
-// `ld` entries.
-template <int D, class List, class Metric = OpenMetric<D>, class Shape = MedianShape>
+// `ld` entries (levels + 1 of them).  kMerge: the tree has at least kListBatch points.
+template <int D, bool kMerge = true, class Shape = MedianShape, class List, class Metric = OpenMetric<D>>
 __device__ __forceinline__ void knn_one(const TreeView& t, const float p[D], List& best,
                                         uint32_t* stk, int ld, const Metric& metric = Metric()) {
+  if constexpr (std::is_same_v<Shape, MedianShape>) {
+    knn_median<D, kMerge && ListMerge<List, D>::kOn>(t, p, best, stk, ld, metric);
+    return;
+  }
   const Shape sh(t);
-  // median trees: every leaf holds floor(n / 2^L) or one more points
-  const int lmin = (int)(t.n >> t.levels);
-  const int lmax = (int)((t.n + (int64_t(1) << t.levels) - 1) >> t.levels);
   float lo[D], hi[D];
   load_box<D>(t.box, 0, lo, hi);
   KDT_LANE_VISIT(t, kVisitNodes, 1);
@@ -358,55 +631,7 @@ __device__ __forceinline__ void knn_one(const TreeView& t, const float p[D], Lis
         int64_t b, e;
         sh.range(node, b, e);
         KDT_LANE_VISIT(t, kVisitPoints, e - b);
-        // Two passes per block of up to 64 leaf points.  The first computes
-        // every distance and marks the points that can enter the list (float
-        // test against the current k-th distance, ties kept); the second
-        // inserts the marked points, recomputing their distances.  The
-        // insertion is the expensive step and runs for the whole wave when
-        // any lane inserts, so marking first makes the wave pay for the
-        // largest number of insertions of one lane in this leaf, not for
-        // every position at which some lane inserts.
-        for (int64_t c = b; c < e; c += 64) {
-          const float w = best.worst_d2();
-          uint64_t mask = 0;
-          if (Shape::kUniformLeaves && lmax <= 32) {
-            // Every leaf holds lmin or lmin + 1 points: the first lmin are
-            // scanned with a wave-uniform trip count, the possible last one
-            // on its own (one block: e - b <= 32).
-            uint32_t m32 = 0;
-#pragma unroll 1  // unrolling costs occupancy (measured slower at k = 32)
-            for (int i = 0; i < lmin; ++i) {
-              float x[D];
-              int32_t id = 0;
-              load_rec<D>(t.rec, b + i, x, id);
-              m32 |= (uint32_t)(metric.dist(x, p) <= w) << i;
-            }
-            if (e - b > lmin) {
-              float x[D];
-              int32_t id = 0;
-              load_rec<D>(t.rec, b + lmin, x, id);
-              m32 |= (uint32_t)(metric.dist(x, p) <= w) << lmin;
-            }
-            mask = m32;
-          } else {
-            const int m = (int)((e - c) < 64 ? (e - c) : 64);
-            for (int i = 0; i < m; ++i) {
-              float x[D];
-              int32_t id = 0;
-              load_rec<D>(t.rec, c + i, x, id);
-              if (metric.dist(x, p) <= w) mask |= 1ull << i;
-            }
-          }
-          KDT_LANE_VISIT(t, kVisitInsert, __popcll(mask));
-          while (mask) {
-            const int i = __builtin_ctzll(mask);
-            mask &= mask - 1;
-            float x[D];
-            int32_t id = 0;
-            load_rec<D>(t.rec, c + i, x, id);
-            best.offer(metric.dist(x, p), id);
-          }
-        }
+        leaf_offer<D, false>(t, (int32_t)b, (int)(e - b), 0, p, best, metric);
       } else {
         const uint32_t c0 = sh.left(node), c1 = c0 + 1;
         KDT_LANE_VISIT(t, kVisitNodes, 2);

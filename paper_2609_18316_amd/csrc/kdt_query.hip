@@ -27,7 +27,8 @@ constexpr int kQBlock = 128;
 // depth bounds it: one pending sibling per level), sized at launch.  KTH:
 // only the k-th distance is written (modes 1 and 2), kept in a TopD list.
 template <int D, int KC, bool KTH, class Shape = MedianShape>
-__global__ __launch_bounds__(kQBlock) void k_knn_lane(TreeView t, const float* __restrict__ q,
+__global__ __launch_bounds__(kQBlock)
+__attribute__((amdgpu_waves_per_eu(lane_waves<D, KC, KTH, Shape>()))) void k_knn_lane(TreeView t, const float* __restrict__ q,
                                                       int64_t nq, int k,
                                                       const int32_t* __restrict__ order, int mode,
                                                       int32_t* __restrict__ oidx,
@@ -50,12 +51,12 @@ __global__ __launch_bounds__(kQBlock) void k_knn_lane(TreeView t, const float* _
   if constexpr (KTH) {
     TopD<KC> best;
     best.init(k);
-    knn_one<D, TopD<KC>, OpenMetric<D>, Shape>(t, p, best, stk_dyn + threadIdx.x, kQBlock);
+    knn_one<D, true, Shape>(t, p, best, stk_dyn + threadIdx.x, kQBlock);
     knn_write_kth<KC>(best, mode, row, od2);
   } else {
     TopK<KC> best;
     best.init(k);
-    knn_one<D, TopK<KC>, OpenMetric<D>, Shape>(t, p, best, stk_dyn + threadIdx.x, kQBlock);
+    knn_one<D, true, Shape>(t, p, best, stk_dyn + threadIdx.x, kQBlock);
     knn_write<KC>(best, k, mode, row, oidx, od2);
   }
 }
@@ -344,14 +345,11 @@ static kdt_status knn_dispatch(const kdt_tree* t, const float* d_q, int64_t nq, 
   } else {                      \
     KDT_LANE_S(KC, MedianShape) \
   }
-  if (k <= 8) {
-    KDT_LANE(8)
-  } else if (k <= 16) {
-    KDT_LANE(16)
-  } else if (k <= 32) {
-    KDT_LANE(32)
-  } else {
-    KDT_LANE(64)
+  switch (lane_list(k, t->n)) {
+    case 8: KDT_LANE(8) break;
+    case 16: KDT_LANE(16) break;
+    case 32: KDT_LANE(32) break;
+    default: KDT_LANE(64)
   }
 #undef KDT_LANE
 #undef KDT_LANE_S

@@ -41,7 +41,8 @@ __device__ __forceinline__ int64_t torus_query(const TreeView& t, const float* _
 }
 
 template <int D, int KC, bool KTH>
-__global__ __launch_bounds__(kTBlock) void k_torus_knn(TreeView t, const float* __restrict__ q,
+__global__ __launch_bounds__(kTBlock)
+__attribute__((amdgpu_waves_per_eu(lane_waves<D, KC, KTH>()))) void k_torus_knn(TreeView t, const float* __restrict__ q,
                                                        int64_t nq, int k,
                                                        const int32_t* __restrict__ order,
                                                        Torus<D> T, int mode,
@@ -211,14 +212,11 @@ static kdt_status torus_knn_impl(const kdt_tree* tr, const float* d_q, int64_t n
   else                                                                                         \
     k_torus_knn<D, KC, true><<<grid, kTBlock, smem, stream>>>(v, d_q, nq, k, order, T, mode,  \
                                                               d_idx, d_d2);
-  if (k <= 8) {
-    KDT_TORUS(8)
-  } else if (k <= 16) {
-    KDT_TORUS(16)
-  } else if (k <= 32) {
-    KDT_TORUS(32)
-  } else {
-    KDT_TORUS(64)
+  switch (lane_list(k, tr->n)) {
+    case 8: KDT_TORUS(8) break;
+    case 16: KDT_TORUS(16) break;
+    case 32: KDT_TORUS(32) break;
+    default: KDT_TORUS(64)
   }
 #undef KDT_TORUS
   if (hipGetLastError() != hipSuccess) {
