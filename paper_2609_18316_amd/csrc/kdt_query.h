@@ -491,13 +491,13 @@ __device__ __forceinline__ void leaf_offer(const TreeView& t, int32_t b, int cnt
           int32_t id = 0;
           load_rec<D>(r, i, x, id);
           const float d2 = metric.dist(x, p);
-          mask |= (uint32_t)(d2 <= w) << i;
-          key[i] = batch_key(best, (valid >> i) & 1u, d2, id);
+          const bool ok = ((valid >> i) & 1u) && d2 <= w;  // (false for NaN)
+          mask |= (uint32_t)ok << i;
+          key[i] = batch_key(best, ok, d2, id);
           // built here, not later from the loaded record: registers
           asm volatile("" : "+v"(key[i]));
           if (i % 4 == 3) __builtin_amdgcn_sched_barrier(0);
         }
-        mask &= valid;
         KDT_LANE_VISIT(t, kVisitInsert, __popc(mask));
         // runs once at most; as a loop the list keeps its registers, as a
         // branch the compiler copies it (153 instead of 128 VGPRs)

@@ -51,3 +51,23 @@ def test_lane_knn_torus_matches_oracle(n, leaf):
         np.testing.assert_array_equal(to_host(d2), od)
         kth = to_host(t.knn(to_dev(q), k, period=1.0, kth_only=1))
         np.testing.assert_array_equal(kth, od[:, k - 1])
+
+
+def test_lane_knn_nan_queries_find_nothing():
+    """A NaN coordinate (of either sign) is at no distance from any point."""
+    dev()
+    x = cases.points("uniform", 1000, 3, seed=5)
+    q = cases.points("uniform", 70, 3, seed=6)
+    q[3] = np.nan
+    q[64, 1] = -np.nan
+    good = ~np.isnan(q).any(axis=1)
+    t, ot = kdt.build(to_dev(x), leaf_size=16), oracle.Tree(x, 16)
+    for k in (8, 32, 64):
+        oi, od = ot.knn(q[good], k)
+        idx, d2 = (to_host(a) for a in t.knn(to_dev(q), k, traversal=1))
+        np.testing.assert_array_equal(idx[good], oi)
+        np.testing.assert_array_equal(d2[good], od)
+        assert (idx[~good] == -1).all() and np.isinf(d2[~good]).all()
+        kth = to_host(t.knn(to_dev(q), k, traversal=1, kth_only=1))
+        np.testing.assert_array_equal(kth[good], od[:, k - 1])
+        assert np.isinf(kth[~good]).all()
