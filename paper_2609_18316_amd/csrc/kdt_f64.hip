@@ -11,10 +11,10 @@
 // leaves from their points and inner nodes from their children, so pruning
 // is exact for the float64 points.
 //
-// Queries (kNN with k <= 64, closed-ball counts and CSR lists) take one
-// traversal per lane, depth first, nearer child first, with the node stack in
-// LDS.  Squared distances are float64 sums over the axes in order, each
-// operation rounded on its own; a node is pruned when its box distance is
+// kNN (k <= 64) takes one traversal per lane, depth first, nearer child first, with the
+// node stack in LDS; closed-ball counts and CSR lists share a traversal by the
+// wave (kdt_packet.h) on median trees.  Squared distances are float64 sums over the
+// axes in order, each operation rounded on its own; a node is pruned when its box distance is
 // above the current k-th key's distance (kNN) or above fl64(r * r) (balls),
 // and taken whole when its farthest corner is within the ball (Algorithm 3).
 // Rounding is monotone, so a box bound computed this way never exceeds the
@@ -38,15 +38,6 @@ namespace kdt {
 namespace {
 
 constexpr int kF64Block = 64;  // one wave per workgroup: the LDS stack is 4 B x depth per lane
-
-struct View64 {
-  const double* rec;   // [n][D] tree-ordered coordinates
-  const double* box;   // [n_nodes][2][D] lo then hi
-  const int32_t* perm; // [n] input index of each tree position
-  int64_t n;
-  int32_t levels;
-  const int4* nodes;   // stored nodes (sliding-midpoint trees) or NULL
-};
 
 __device__ __forceinline__ TreeView shape_view(const View64& v) {
   TreeView t{};
@@ -545,9 +536,25 @@ extern "C" kdt_status kdt_range_f64(const kdt_tree* tree, const double* d_q, int
   const int depth = stack_depth(tree);
   const size_t smem = sizeof(uint32_t) * (size_t)depth * kF64Block;
   const unsigned g = (unsigned)((nq + kF64Block - 1) / kF64Block);
+  // Median trees take the wave-shared counts (and their list fill): one
+  // traversal per lane waits for the few lanes whose balls sit in a dense halo.
+  // The call for 500009 balls of about 28 points on 2000003 clustered points took
+  // 11.1 ms with a traversal per lane and takes 1.6 ms shared by a wave, its lists
+  // 68 and 7.9 ms.  A leaf has to fit the wave's mask (64 points), and the
+  // leaves and packed queries of a workgroup the 64 KiB of LDS a launch gets
+  // (16 dimensions: leaves of up to 56 points).
+  int cap = 0;
+  const View64 vc = count_view(v, tree->leaf, &cap);
+  const bool shared = !tree->nodes && cap <= 64 && range64_packet_lds(tree->d, cap) <= 65536;
+  int32_t* cur = nullptr;
   auto launch = [&](bool fill, int32_t* out) {
     return by_dim(tree->d, [&](auto dd) -> kdt_status {
       constexpr int D = decltype(dd)::value;
+      if (shared) {
+        const FillOut fo{out, d_offsets, cur};
+        return range64_packet_launch<D>(vc, cap, d_q, nq, r2, order, d_count, stream,
+                                        fill ? &fo : nullptr);
+      }
       if (tree->nodes) {
         if (fill)
           k_range64<D, true, StoredShape><<<g, kF64Block, smem, stream>>>(
@@ -568,7 +575,7 @@ extern "C" kdt_status kdt_range_f64(const kdt_tree* tree, const double* d_q, int
   };
   kdt_status st = launch(false, nullptr);
   if (st != KDT_OK) {
-    kdt_set_error("kdt_range_f64: kernel launch failed");
+    if (st == KDT_EDEVICE) kdt_set_error("kdt_range_f64: kernel launch failed");
     return st;
   }
   if (!d_offsets) return KDT_OK;
@@ -598,13 +605,13 @@ extern "C" kdt_status kdt_range_f64(const kdt_tree* tree, const double* d_q, int
   }
   if (total == 0) return KDT_OK;
   int32_t* unsorted = nullptr;
-  if (!buf.get(&unsorted, (size_t)total)) {
+  if (!buf.get(&unsorted, (size_t)total) || (shared && !buf.get(&cur, (size_t)nq))) {
     kdt_set_error("kdt_range_f64: device allocation failed for the lists");
     return KDT_ENOMEM;
   }
   st = launch(true, unsorted);
   if (st != KDT_OK) {
-    kdt_set_error("kdt_range_f64: kernel launch failed");
+    if (st == KDT_EDEVICE) kdt_set_error("kdt_range_f64: kernel launch failed");
     return st;
   }
   // every row ascending by input index

@@ -18,29 +18,40 @@ namespace kdt {
 // scalar loads straight from the records was measured slower at every d:
 // each batch waits on the scalar cache, which the waves' leaves overflow --
 // ball counts 22.5 against 17.1 ms on the clustered workload.)
-template <int D>
+template <int D, class View = TreeView>
 struct LeafReader {
-  static constexpr int S = rec_stride(D);
-  const float* rec;
-  float* lds;
+  static constexpr int S = point_stride<D, View>();
+  using Real = typename View::Real;
+  const View& t;
+  Real* lds;
   int64_t b = 0;  // first record of the open leaf
-  __device__ __forceinline__ LeafReader(const float* r, float* l) : rec(r), lds(l) {}
+  __device__ __forceinline__ LeafReader(const View& v, Real* l) : t(v), lds(l) {}
   // Called by the whole wave with a wave-uniform leaf.
   __device__ __forceinline__ void open(int64_t first, int cnt) {
     b = first;
     wave_sync();  // every lane is done with the previous leaf
-    const float4* src = reinterpret_cast<const float4*>(rec + first * S);
-    float4* dst = reinterpret_cast<float4*>(lds);
-    for (int i = lane_id(); i < cnt * (S / 4); i += 64) dst[i] = src[i];
+    if constexpr (std::is_same_v<Real, float>) {
+      const float4* src = reinterpret_cast<const float4*>(t.rec + first * S);
+      float4* dst = reinterpret_cast<float4*>(lds);
+      for (int i = lane_id(); i < cnt * (S / 4); i += 64) dst[i] = src[i];
+    } else {
+      const Real* src = t.rec + first * S;
+      for (int i = lane_id(); i < cnt * S; i += 64) lds[i] = src[i];
+    }
     wave_sync();
   }
   // Point i of the open leaf (i wave-uniform: a broadcast).
-  __device__ __forceinline__ void point(int i, float x[D]) const {
+  __device__ __forceinline__ void point(int i, Real x[D]) const {
 #pragma unroll
     for (int a = 0; a < D; ++a) x[a] = lds[i * S + a];
   }
   // The input index of point i of the open leaf.
-  __device__ __forceinline__ int32_t index(int i) const { return __float_as_int(lds[i * S + D]); }
+  __device__ __forceinline__ int32_t index(int i) const {
+    if constexpr (std::is_same_v<Real, float>)
+      return __float_as_int(lds[i * S + D]);
+    else
+      return input_index<D>(t, b + i);
+  }
   // Point i of the open leaf and its index, i per lane.
   __device__ __forceinline__ void lane_point(int i, float x[D], int32_t& id) const {
 #pragma unroll
@@ -272,7 +283,7 @@ __device__ __forceinline__ void packet_knn(const TreeView& t, const float p[D], 
   uint32_t stackv = 0;  // lane i holds stack entry i
   int sp = 1;
   uint64_t mask = 0;    // this lane's pending candidates in the open leaf
-  LeafReader<D> leaf(t.rec, lds);
+  LeafReader<D> leaf(t, lds);
   DotFilter<D> filt;
   if constexpr (DotFilter<D>::kOn) filt.init(p, active, lds, leaf_cap);
   // One flat loop (the candidate list is then live across a single loop
@@ -477,23 +488,23 @@ kdt_status box_packet_launch(const TreeView& v, int leaf, const float* d_lo, con
 //
 // A closed ball (Algorithm 3): centre p, squared radius r2 (the same for all
 // queries of a launch).
-template <int D>
+template <int D, class Real = float>
 struct BallShape {
-  static constexpr int kFloats = D;
-  float p[D];
-  float r2;
-  __device__ __forceinline__ bool cuts(const float lo[D], const float hi[D]) const {
+  static constexpr int kFloats = D;  // packed values
+  Real p[D];
+  Real r2;
+  __device__ __forceinline__ bool cuts(const Real lo[D], const Real hi[D]) const {
     return box_mindist<D>(lo, hi, p) <= r2;
   }
-  __device__ __forceinline__ bool holds_box(const float lo[D], const float hi[D]) const {
+  __device__ __forceinline__ bool holds_box(const Real lo[D], const Real hi[D]) const {
     return box_maxdist<D>(lo, hi, p) <= r2;
   }
-  __device__ __forceinline__ bool holds(const float x[D]) const { return sq_dist<D>(x, p) <= r2; }
-  __device__ __forceinline__ void pack(float* dst) const {
+  __device__ __forceinline__ bool holds(const Real x[D]) const { return sq_dist<D>(x, p) <= r2; }
+  __device__ __forceinline__ void pack(Real* dst) const {
 #pragma unroll
     for (int a = 0; a < D; ++a) dst[a] = p[a];
   }
-  __device__ __forceinline__ BallShape unpack(const float* src) const {
+  __device__ __forceinline__ BallShape unpack(const Real* src) const {
     BallShape b;
 #pragma unroll
     for (int a = 0; a < D; ++a) b.p[a] = src[a];
@@ -582,12 +593,14 @@ struct BoxShape {
   }
 };
 
-// LDS floats of one wave of a count: the open leaf, then the packed queries
-// [64][K] (K floats per query shape), their counts [64] and, for the fill,
-// their hit masks [64] (uint64).
-template <int D, int K = D>
-__host__ __device__ constexpr size_t range_wave_floats(int leaf) {
-  return (size_t)leaf * rec_stride(D) + 64 * (K + 1) + 128;
+// LDS bytes of one wave of a count: the open leaf, then the packed queries
+// [64][K] (K values of View::Real per query shape), their counts [64] and,
+// for the fill, their hit masks [64] (uint64).
+template <int D, class View, int K>
+__host__ __device__ constexpr size_t range_wave_bytes(int leaf) {
+  const size_t b = sizeof(typename View::Real) * ((size_t)leaf * point_stride<D, View>() + 64 * K) +
+                   64 * (sizeof(int32_t) + sizeof(uint64_t));
+  return (b + 15) / 16 * 16;
 }
 
 // Fill mode: a lane appends n indices to its row; returns the first slot.
@@ -634,19 +647,20 @@ __device__ __forceinline__ void fill_hits(const FillOut& fo, int64_t row, uint64
 // rows instead of only counting: a whole node is written for each lane that
 // holds it by the whole wave (64 entries per step, its rows' slots reserved
 // by that lane), a leaf's hits by each lane from its hit mask.
-template <int D, class Shape, bool FILL = false>
-__device__ __forceinline__ int64_t packet_range_count(const TreeView& t, const Shape& sh,
-                                                      bool active, float* lds,
+template <int D, class Shape, bool FILL = false, class View>
+__device__ __forceinline__ int64_t packet_range_count(const View& t, const Shape& sh,
+                                                      bool active, typename View::Real* lds,
                                                       int leaf_cap, uint32_t start,
                                                       uint64_t start_mask, uint32_t group,
                                                       const PacketSpill& spill,
                                                       int64_t row = 0,
                                                       const FillOut& fo = FillOut{}) {
-  constexpr int S = rec_stride(D);
+  using Real = typename View::Real;
+  constexpr int S = point_stride<D, View>();
   constexpr int K = Shape::kFloats;
   const int lane = lane_id();
-  LeafReader<D> leaf(t.rec, lds);
-  float* cq = lds + (size_t)leaf_cap * S;                  // packed queries [64][K]
+  LeafReader<D, View> leaf(t, lds);
+  Real* cq = lds + (size_t)leaf_cap * S;                   // packed queries [64][K]
   int32_t* cc = reinterpret_cast<int32_t*>(cq + 64 * K);  // their counts [64]
   uint64_t* cm = reinterpret_cast<uint64_t*>(cc + 64);    // their hit masks [64] (fill)
   const uint32_t first_leaf = (1u << t.levels) - 1u;
@@ -665,8 +679,8 @@ __device__ __forceinline__ int64_t packet_range_count(const TreeView& t, const S
     const uint64_t live = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)stk_hi, sp) << 32) |
                           (uint32_t)__builtin_amdgcn_readlane((int)stk_lo, sp);
     const bool mine = active && ((live >> lane) & 1ull);
-    float lo[D], hi[D];
-    load_box_uniform<D>(t.box, node, lo, hi);
+    Real lo[D], hi[D];
+    load_node_uniform<D>(t, node, lo, hi);
     KDT_WAVE_VISIT(t, kVisitWaveNodes, 1);
     const bool touch = mine && sh.cuts(lo, hi);
     if (!__any(touch)) continue;
@@ -678,7 +692,6 @@ __device__ __forceinline__ int64_t packet_range_count(const TreeView& t, const S
     if (FILL) {
       uint64_t fm = __ballot(full);
       if (fm) {
-        constexpr int S2 = rec_stride(D);
         const int64_t at = full ? fill_reserve(fo, row, (int)(e - b)) : 0;
         while (fm) {
           const int l = __ffsll((unsigned long long)fm) - 1;
@@ -686,7 +699,7 @@ __device__ __forceinline__ int64_t packet_range_count(const TreeView& t, const S
           const int64_t dst = ((int64_t)__builtin_amdgcn_readlane((int)(at >> 32), l) << 32) |
                               (uint32_t)__builtin_amdgcn_readlane((int)at, l);
           for (int64_t i = b + lane; i < e; i += 64)
-            fo.out[dst + (i - b)] = __float_as_int(t.rec[i * S2 + D]);
+            fo.out[dst + (i - b)] = input_index<D>(t, i);
         }
       }
     }
@@ -707,7 +720,7 @@ __device__ __forceinline__ int64_t packet_range_count(const TreeView& t, const S
         wave_sync();
         const int slot = lane / W, i = lane % W;
         const uint64_t wmask = ~0ull >> (64 - W);
-        float x[D];
+        Real x[D];
         leaf.point(min(i, cnt - 1), x);
         for (int s = 0; s < steps; ++s) {
           const int a = s * G + slot;
@@ -728,7 +741,7 @@ __device__ __forceinline__ int64_t packet_range_count(const TreeView& t, const S
         uint64_t hits = 0;
 #pragma unroll uniform_batch<D>()
         for (int i = 0; i < cnt; ++i) {
-          float x[D];
+          Real x[D];
           leaf.point(i, x);
           const bool h = sh.holds(x);
           c += h;
@@ -774,7 +787,7 @@ __device__ __forceinline__ void packet_fof(const TreeView& t, const float p[D], 
   const uint32_t first_leaf = (1u << t.levels) - 1u;
   const int32_t gme = base + me;
   int32_t myroot = gme;  // an ancestor of this lane's point (see uf_union_from)
-  LeafReader<D> leaf(t.rec, lds);
+  LeafReader<D> leaf(t, lds);
   uint32_t stackv = 0;
   uint32_t stk_lo = 0xFFFFFFFFu, stk_hi = 0xFFFFFFFFu;
   int sp = 1;

@@ -54,6 +54,17 @@ __device__ __forceinline__ bool load_query(const TreeView& t, const float* __res
   return true;
 }
 
+template <int D>
+__device__ __forceinline__ bool load_query(const View64& t, const double* __restrict__ q,
+                                           int64_t nq, const int32_t* __restrict__ order,
+                                           int64_t s, double p[D], int64_t& row) {
+  const bool active = s < nq;
+  row = !active ? 0 : order && q ? order[s] : order || q ? s : t.perm[s];
+#pragma unroll
+  for (int a = 0; a < D; ++a) p[a] = !active ? 0.0 : q ? q[row * D + a] : t.rec[s * D + a];
+  return active;
+}
+
 // MODE 0 writes k (index, d2) pairs per row, 1 the k-th d2, 2 the k-th
 // distance (a compile-time choice, so each output form is its own kernel).
 template <int D, int KC, int MODE>
@@ -78,12 +89,14 @@ __global__ __launch_bounds__(64 * kPWaves) void k_knn_packet(TreeView t, const f
 
 // Where the queries of a count come from: balls (centres, or the tree's own
 // points, and one squared radius) or boxes (corners).
-template <int D>
+template <int D, class V = TreeView>
 struct BallQueries {
-  using Shape = BallShape<D>;
-  const float* q;  // [nq][D], or nullptr: the tree's own points
-  float r2;
-  __device__ __forceinline__ bool load(const TreeView& t, int64_t nq, const int32_t* order,
+  using View = V;
+  using Real = typename View::Real;
+  using Shape = BallShape<D, Real>;
+  const Real* q;  // [nq][D], or nullptr: the tree's own points
+  Real r2;
+  __device__ __forceinline__ bool load(const View& t, int64_t nq, const int32_t* order,
                                        int64_t s, Shape& sh, int64_t& row) const {
     sh.r2 = r2;
     return load_query<D>(t, q, nq, order, s, sh.p, row);
@@ -92,6 +105,7 @@ struct BallQueries {
 
 template <int D>
 struct TorusBallQueries {
+  using View = TreeView;
   using Shape = TorusBallShape<D>;
   const float* q;  // [nq][D], or nullptr: the tree's own points
   float r2;
@@ -106,6 +120,7 @@ struct TorusBallQueries {
 
 template <int D, class Metric>
 struct VarBallQueries {
+  using View = TreeView;
   using Shape = VarBallShape<D, Metric>;
   const float* q;   // [rows][D]
   const float* r2;  // [rows]
@@ -121,6 +136,7 @@ struct VarBallQueries {
 
 template <int D>
 struct BoxQueries {
+  using View = TreeView;
   using Shape = BoxShape<D>;
   const float* lo;  // [nq][D]
   const float* hi;
@@ -145,20 +161,24 @@ struct BoxQueries {
 };
 
 template <int D, class Q>
-__host__ __device__ constexpr size_t count_wave_floats(int leaf) {
-  return range_wave_floats<D, Q::Shape::kFloats>(leaf);
+__host__ __device__ constexpr size_t count_wave_bytes(int leaf) {
+  return range_wave_bytes<D, typename Q::View, Q::Shape::kFloats>(leaf);
+}
+template <int D, class Q>
+__device__ __forceinline__ typename Q::View::Real* count_slice(char* lds, int wave, int leaf) {
+  return reinterpret_cast<typename Q::View::Real*>(lds + wave * count_wave_bytes<D, Q>(leaf));
 }
 
 // First pass of the counts: one 64-query group per wave from the root; writes
 // each count (partial if the wave handed subtrees on), or with FILL the
 // lists.
 template <int D, class Q, bool FILL>
-__global__ __launch_bounds__(64 * kPWaves) void k_count_packet(TreeView t, Q src, int64_t nq,
+__global__ __launch_bounds__(64 * kPWaves) void k_count_packet(typename Q::View t, Q src, int64_t nq,
                                                                const int32_t* __restrict__ order,
                                                                int32_t* __restrict__ count,
                                                                int leaf_cap, PacketSpill spill,
                                                                FillOut fo) {
-  extern __shared__ __align__(16) float lds[];
+  extern __shared__ __align__(16) char count_lds[];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int64_t s0 = (xcd_block<kXcdRunPacket>() * kPWaves + wave) * 64;
   if (s0 >= nq) return;
@@ -166,7 +186,7 @@ __global__ __launch_bounds__(64 * kPWaves) void k_count_packet(TreeView t, Q src
   int64_t row = 0;
   const bool active = src.load(t, nq, order, s0 + lane, sh, row);
   const int64_t c = packet_range_count<D, typename Q::Shape, FILL>(
-      t, sh, active, lds + (size_t)wave * count_wave_floats<D, Q>(leaf_cap), leaf_cap, 0u, ~0ull,
+      t, sh, active, count_slice<D, Q>(count_lds, wave, leaf_cap), leaf_cap, 0u, ~0ull,
       (uint32_t)(s0 / 64), spill, row, fo);
   if (!FILL && active) count[row] = (int32_t)c;
   wave_done(spill);
@@ -176,13 +196,13 @@ __global__ __launch_bounds__(64 * kPWaves) void k_count_packet(TreeView t, Q src
 // count, read at start, so every wave's loop ends) and adds its counts.
 template <int D, class Q, bool FILL>
 __global__ __launch_bounds__(64 * kPWaves) void k_count_tasks(
-    TreeView t, Q src, int64_t nq, const int32_t* __restrict__ order,
+    typename Q::View t, Q src, int64_t nq, const int32_t* __restrict__ order,
     int32_t* __restrict__ count, int leaf_cap, const PacketTask* __restrict__ in,
     const uint32_t* __restrict__ in_count, uint32_t in_cap, PacketSpill spill, FillOut fo) {
-  extern __shared__ __align__(16) float lds[];
+  extern __shared__ __align__(16) char count_lds[];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const uint32_t n = min(*in_count, in_cap);
-  float* slice = lds + (size_t)wave * count_wave_floats<D, Q>(leaf_cap);
+  auto* slice = count_slice<D, Q>(count_lds, wave, leaf_cap);
   for (uint32_t k = blockIdx.x * kPWaves + wave; k < n; k += gridDim.x * kPWaves) {
     const PacketTask task = in[k];
     if (task.node == kNoNode) continue;
@@ -315,12 +335,12 @@ kdt_status knn_packet_launch(const TreeView& v, int leaf, const float* d_q, int6
 // With `fill` the same launches write the CSR lists instead (fill->cur zeroed
 // here first); d_count is then not written.
 template <int D, class Q>
-static kdt_status count_packet_launch(const TreeView& v, int leaf, Q src, int64_t nq,
+static kdt_status count_packet_launch(const typename Q::View& v, int leaf, Q src, int64_t nq,
                                       const int32_t* order, int32_t* d_count,
                                       uint32_t split_budget, hipStream_t stream,
                                       const char* who, const FillOut* fill = nullptr) {
   const unsigned grid = (unsigned)((nq + 64 * kPWaves - 1) / (64 * kPWaves));
-  const size_t smem = sizeof(float) * count_wave_floats<D, Q>(leaf) * kPWaves;
+  const size_t smem = count_wave_bytes<D, Q>(leaf) * kPWaves;
   PoolBuffers buf(stream);
   PacketTask* tasks = nullptr;
   uint32_t* counts = nullptr;
@@ -377,6 +397,14 @@ kdt_status range_packet_launch(const TreeView& v, int leaf, const float* d_q, in
 }
 
 template <int D>
+kdt_status range64_packet_launch(const View64& v, int leaf, const double* d_q, int64_t nq,
+                                 double r2, const int32_t* order, int32_t* d_count,
+                                 hipStream_t stream, const FillOut* fill) {
+  return count_packet_launch<D>(v, leaf, BallQueries<D, View64>{d_q, r2}, nq, order, d_count, 0u,
+                                stream, "kdt_range_f64", fill);
+}
+
+template <int D>
 kdt_status box_packet_launch(const TreeView& v, int leaf, const float* d_lo, const float* d_hi,
                              int64_t nq, const int32_t* order, int32_t* d_count,
                              uint32_t split_budget, hipStream_t stream, const FillOut* fill) {
@@ -401,12 +429,23 @@ kdt_status var_ball_count_launch(const TreeView& v, int leaf, const float* d_q, 
                                 d_count, 0u, stream, "kdt_knn");
 }
 
+size_t range64_packet_lds(int d, int leaf) {
+  return kPWaves * (d == 2   ? range_wave_bytes<2, View64, 2>(leaf)
+                    : d == 3 ? range_wave_bytes<3, View64, 3>(leaf)
+                    : d == 4 ? range_wave_bytes<4, View64, 4>(leaf)
+                    : d == 8 ? range_wave_bytes<8, View64, 8>(leaf)
+                             : range_wave_bytes<16, View64, 16>(leaf));
+}
+
 #define KDT_INST(D)                                                                                \
   template kdt_status knn_packet_launch<D>(const TreeView&, int, const float*, int64_t, int,       \
                                            int32_t*, float*, int, const int32_t*, hipStream_t);    \
   template kdt_status range_packet_launch<D>(const TreeView&, int, const float*, int64_t, float,   \
                                              const int32_t*, int32_t*, uint32_t, hipStream_t,    \
                                              const FillOut*);                                    \
+  template kdt_status range64_packet_launch<D>(const View64&, int, const double*, int64_t, double, \
+                                               const int32_t*, int32_t*, hipStream_t,            \
+                                               const FillOut*);                                  \
   template kdt_status box_packet_launch<D>(const TreeView&, int, const float*, const float*,       \
                                            int64_t, const int32_t*, int32_t*, uint32_t,          \
                                            hipStream_t, const FillOut*);                         \

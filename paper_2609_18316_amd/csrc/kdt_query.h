@@ -11,12 +11,25 @@ namespace kdt {
 constexpr int kMaxDepth = 32;  // levels <= 30 for n < 2^31 and leaf_size >= 2
 
 struct TreeView {
+  using Real = float;
   const float* rec;  // [n][rec_stride(D)] tree-ordered records
   const float* box;  // [n_nodes][2 * pad4(D)]
   int64_t n;
   int32_t levels;    // depth of the deepest leaf
   const int4* nodes = nullptr;  // stored node records (sliding-midpoint trees), else NULL
   unsigned long long* visits = nullptr;  // work counters of the instrumented build, else NULL
+};
+
+// A tree over float64 coordinates (kdt_build_f64).
+struct View64 {
+  using Real = double;
+  const double* rec;    // [n][D] tree-ordered coordinates
+  const double* box;    // [n_nodes][2][D] lo then hi
+  const int32_t* perm;  // [n] input index of each tree position
+  int64_t n;
+  int32_t levels;
+  const int4* nodes;    // stored nodes (sliding-midpoint trees) or NULL
+  unsigned long long* visits = nullptr;
 };
 
 // The wave-shared counts (and their list fill) over a median tree treat the
@@ -28,7 +41,8 @@ struct TreeView {
 // view and, in *cap, its largest node (the LDS slices' leaf capacity).
 constexpr int kCountLeaf = 32;
 // The view at the coarsest level whose nodes hold at most `most` points.
-inline TreeView coarse_view(TreeView v, int leaf, int most, int* cap) {
+template <class View>
+inline View coarse_view(View v, int leaf, int most, int* cap) {
   int l = v.levels;
   while (l > 0 && ((v.n + (int64_t(1) << (l - 1)) - 1) >> (l - 1)) <= most) --l;
   const int64_t big = (v.n + (int64_t(1) << l) - 1) >> l;
@@ -36,7 +50,8 @@ inline TreeView coarse_view(TreeView v, int leaf, int most, int* cap) {
   v.levels = l;
   return v;
 }
-inline TreeView count_view(TreeView v, int leaf, int* cap) {
+template <class View>
+inline View count_view(View v, int leaf, int* cap) {
   return coarse_view(v, leaf, kCountLeaf, cap);
 }
 
@@ -67,7 +82,8 @@ enum : int { kVisitNodes = 0, kVisitPoints = 1, kVisitInsert = 2, kVisitWaveNode
              kVisitWavePoints = 4, kVisitReload = 5, kVisitSlots = 8 };
 constexpr int kVisitShards = 64;
 #ifdef KDT_COUNT_VISITS
-__device__ __forceinline__ void count_visit(const TreeView& t, int slot, uint32_t n) {
+template <class View>
+__device__ __forceinline__ void count_visit(const View& t, int slot, uint32_t n) {
   if (t.visits)
     atomicAdd(t.visits + slot * kVisitShards + (blockIdx.x % kVisitShards),
               (unsigned long long)n);
@@ -152,6 +168,18 @@ __device__ __forceinline__ float box_mindist(const float lo[D], const float hi[D
   }
   return s;
 }
+// The same in float64 (float64 trees), NaN treated alike (a gap of 0).
+template <int D>
+__device__ __forceinline__ double box_mindist(const double lo[D], const double hi[D],
+                                              const double p[D]) {
+  double s = 0.0;
+#pragma unroll
+  for (int a = 0; a < D; ++a) {
+    const double t = fmax(fmax(lo[a] - p[a], p[a] - hi[a]), 0.0);
+    s += t * t;
+  }
+  return s;
+}
 
 // Largest squared distance from p to the box (never below any point's).
 template <int D>
@@ -168,9 +196,32 @@ __device__ __forceinline__ float box_maxdist(const float lo[D], const float hi[D
   return s;
 }
 
-// Squared Euclidean distance (Eq. 1, p = 2): float32, axes left to right,
-// every operation rounded on its own (the library is built without FMA
-// contraction).
+template <int D>
+__device__ __forceinline__ double box_maxdist(const double lo[D], const double hi[D],
+                                              const double p[D]) {
+  double s = 0.0;
+#pragma unroll
+  for (int a = 0; a < D; ++a) {
+    const double t1 = fabs(p[a] - lo[a]), t2 = fabs(p[a] - hi[a]);
+    const double t = t1 > t2 ? t1 : t2;
+    s += t * t;
+  }
+  return s;
+}
+
+// Squared Euclidean distance (Eq. 1, p = 2): float32 (float64 over float64
+// trees), axes left to right, every operation rounded on its own (the library
+// is built without FMA contraction).
+template <int D>
+__device__ __forceinline__ double sq_dist(const double* __restrict__ x, const double p[D]) {
+  double s = 0.0;
+#pragma unroll
+  for (int a = 0; a < D; ++a) {
+    const double t = x[a] - p[a];
+    s += t * t;
+  }
+  return s;
+}
 template <int D>
 __device__ __forceinline__ float sq_dist(const float* __restrict__ x, const float p[D]) {
   float s = 0.0f;
@@ -220,6 +271,37 @@ __device__ __forceinline__ void load_box_uniform(const float* box, uint32_t node
     lo[a] = b[a];
     hi[a] = b[P + a];
   }
+}
+
+typedef const __attribute__((address_space(4))) double cdouble;
+template <int D>
+__device__ __forceinline__ void load_node_uniform(const TreeView& t, uint32_t node, float lo[D],
+                                                  float hi[D]) {
+  load_box_uniform<D>(t.box, node, lo, hi);
+}
+template <int D>
+__device__ __forceinline__ void load_node_uniform(const View64& t, uint32_t node, double lo[D],
+                                                  double hi[D]) {
+  const cdouble* b = (const cdouble*)t.box + (size_t)node * 2 * D;
+#pragma unroll
+  for (int a = 0; a < D; ++a) {
+    lo[a] = b[a];
+    hi[a] = b[D + a];
+  }
+}
+// The input index of the point at tree position i.
+template <int D>
+__device__ __forceinline__ int32_t input_index(const TreeView& t, int64_t i) {
+  return __float_as_int(t.rec[i * rec_stride(D) + D]);
+}
+template <int D>
+__device__ __forceinline__ int32_t input_index(const View64& t, int64_t i) {
+  return t.perm[i];
+}
+// Elements of View::Real per point record.
+template <int D, class View>
+__host__ __device__ constexpr int point_stride() {
+  return std::is_same_v<View, View64> ? D : rec_stride(D);
 }
 
 // Leaf points a wave-uniform scan keeps in flight (a loop unroll factor).
@@ -928,6 +1010,13 @@ template <int D>
 kdt_status range_packet_launch(const TreeView& v, int leaf, const float* d_q, int64_t nq, float r2,
                                const int32_t* order, int32_t* d_count, uint32_t split_budget,
                                hipStream_t stream, const FillOut* fill = nullptr);
+// The same over a float64 tree (leaves of at most 64 points).
+template <int D>
+kdt_status range64_packet_launch(const View64& v, int leaf, const double* d_q, int64_t nq,
+                                 double r2, const int32_t* order, int32_t* d_count,
+                                 hipStream_t stream, const FillOut* fill = nullptr);
+// The LDS bytes of a workgroup of that launch.
+size_t range64_packet_lds(int d, int leaf);
 template <int D>
 kdt_status fof_packet_launch(const TreeView& v, int leaf, float l2, int32_t* parent, uint32_t* conn,
                              hipStream_t stream);
