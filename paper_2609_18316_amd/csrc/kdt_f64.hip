@@ -178,24 +178,95 @@ __device__ __forceinline__ int64_t load_query64(const View64& v, const double* _
   return order ? i : v.perm[i];  // self queries: tree order when order is set
 }
 
+// (127 VGPRs; three waves per SIMD 2.15, four 2.03 ms)
+template <int D, int KC>
+constexpr int lane64_waves() {
+  return ListMerge<TopK<KC>, D>::kOn ? 4 : 1;
+}
+// kNN over a median tree by keys of the float32 rounding of each float64
+// distance and the tree position: they take the float32 path's lists and
+// traversal (knn_median), where a (float64, index) list is 96 registers and
+// 12 instructions per slot and insertion at k = 32 (216 VGPRs, two waves per SIMD;
+// the call for 500009 queries on 2000003 clustered points 9.0 ms; now 2.03).  Rounding
+// keeps the order of all but equal keys, so the list holds the k nearest points unless
+// the k-th rounded distance is also that of a point that was turned away.
+// Such a query is left to k_knn64 (todo); every other row gets its exact
+// float64 distances, computed again from the list's positions, and runs of
+// equal rounded distances are put into (d2, index) order in place.
+template <int D, int KC>
+__global__ __launch_bounds__(kF64Block)
+__attribute__((amdgpu_waves_per_eu(lane64_waves<D, KC>()))) void k_knn64_median(
+    View64 v, const double* __restrict__ q, int64_t nq, int k, const int32_t* __restrict__ order,
+    int32_t* __restrict__ out_idx, double* __restrict__ out_d2, int32_t* __restrict__ todo,
+    int32_t* __restrict__ n_todo) {
+  extern __shared__ uint32_t stk[];  // [levels + 1][kF64Block]
+  const int64_t i = xcd_block<kXcdRunLane>() * kF64Block + threadIdx.x;
+  if (i >= nq) return;
+  double qq[D];
+  const int64_t row = load_query64<D>(v, q, order, i, qq);
+  TopKTie<KC> best;
+  best.init(k);
+  knn_median<D, ListMerge<TopK<KC>, D>::kOn>(Space64<D>{v}, qq, best, stk + threadIdx.x,
+                                             kF64Block);
+  double* d2 = out_d2 + row * k;
+  int32_t* idx = out_idx ? out_idx + row * k : nullptr;
+  bool runs = false;
+#pragma unroll
+  for (int j = 0; j < KC; ++j) {
+    if (j < KC - k) continue;
+    const uint64_t key = best.key(j);
+    const bool empty = key == kEmptyKey;
+    const int64_t pos = empty ? 0 : (int64_t)(uint32_t)key;
+    if (j > KC - k) runs |= !empty && (key >> 32) == (best.key(j - 1) >> 32);
+    d2[j - (KC - k)] = empty ? INFINITY : sq_dist<D>(v.rec + pos * D, qq);
+    if (idx) idx[j - (KC - k)] = empty ? -1 : v.perm[pos];
+  }
+  if (v.n > k && !(best.lost > best.worst_d2())) {
+    todo[atomicAdd(n_todo, 1)] = (int32_t)i;
+  } else if (runs) {
+    const int m = (int)(v.n < k ? v.n : k);
+    for (int a = 1; a < m; ++a) {
+      const double d = d2[a];
+      const int32_t id = idx ? idx[a] : 0;
+      int b = a;
+      for (; b > 0 && (d < d2[b - 1] || (idx && d == d2[b - 1] && id < idx[b - 1])); --b) {
+        d2[b] = d2[b - 1];
+        if (idx) idx[b] = idx[b - 1];
+      }
+      d2[b] = d;
+      if (idx) idx[b] = id;
+    }
+  }
+}
+
+// kNN by exact (d2, index) lists: sliding-midpoint trees (some == NULL), and
+// the *n_some queries some[] that k_knn64_median has left (order positions).
 template <int D, int KC, typename Shape>
 __global__ __launch_bounds__(kF64Block) void k_knn64(View64 v, const double* __restrict__ q,
                                                      int64_t nq, int k,
                                                      const int32_t* __restrict__ order,
                                                      int32_t* __restrict__ out_idx,
-                                                     double* __restrict__ out_d2, int depth) {
+                                                     double* __restrict__ out_d2, int depth,
+                                                     const int32_t* __restrict__ some,
+                                                     const int32_t* __restrict__ n_some) {
   extern __shared__ uint32_t stk[];  // [depth][kF64Block]
-  const int64_t i = (int64_t)blockIdx.x * kF64Block + threadIdx.x;
-  if (i >= nq) return;
+  int64_t i = (int64_t)blockIdx.x * kF64Block + threadIdx.x;
+  if (i >= (some ? (int64_t)*n_some : nq)) return;
+  if (some) i = some[i];
   double qq[D];
   const int64_t row = load_query64<D>(v, q, order, i, qq);
   const Shape shape(shape_view(v));
   double kd[KC];
   int32_t ki[KC];
-#pragma unroll
-  for (int j = 0; j < KC; ++j) kd[j] = INFINITY, ki[j] = INT_MAX;
   double wd = INFINITY;  // the k-th key
   int32_t wi = INT_MAX;
+  if (some) {
+    // the row holds k points already: none farther than they are can matter
+    wd = 0.0;
+    for (int j = 0; j < k; ++j) wd = fmax(wd, out_d2[row * k + j]);
+  }
+#pragma unroll
+  for (int j = 0; j < KC; ++j) kd[j] = wd, ki[j] = INT_MAX;
   int sp = 0;
   uint32_t node = 0;
   bool have = true;
@@ -468,26 +539,34 @@ extern "C" kdt_status kdt_knn_f64(const kdt_tree* tree, const double* d_q, int64
   const View64 v = view64(tree);
   const int depth = stack_depth(tree);
   const size_t smem = sizeof(uint32_t) * (size_t)depth * kF64Block;
+  const size_t smem1 = sizeof(uint32_t) * (size_t)(tree->levels + 1) * kF64Block;
   const unsigned g = (unsigned)((nq + kF64Block - 1) / kF64Block);
+  int32_t *todo = nullptr, *n_todo = nullptr;
+  if (!tree->nodes && (!buf.get(&todo, (size_t)nq) || !buf.get(&n_todo, 1))) {
+    kdt_set_error("kdt_knn_f64: device allocation failed");
+    return KDT_ENOMEM;
+  }
   const kdt_status st = by_dim(tree->d, [&](auto dd) -> kdt_status {
     constexpr int D = decltype(dd)::value;
     auto go = [&](auto kc) {
       constexpr int KC = decltype(kc)::value;
-      if (tree->nodes)
+      if (tree->nodes) {
         k_knn64<D, KC, StoredShape><<<g, kF64Block, smem, stream>>>(
-            v, d_q, nq, k, order, d_idx, d_d2, depth);
-      else
+            v, d_q, nq, k, order, d_idx, d_d2, depth, nullptr, nullptr);
+      } else {
+        k_zero64<<<1, 1, 0, stream>>>(n_todo, nullptr);
+        k_knn64_median<D, KC><<<g, kF64Block, smem1, stream>>>(v, d_q, nq, k, order, d_idx, d_d2,
+                                                               todo, n_todo);
         k_knn64<D, KC, MedianShape><<<g, kF64Block, smem, stream>>>(
-            v, d_q, nq, k, order, d_idx, d_d2, depth);
+            v, d_q, nq, k, order, d_idx, d_d2, depth, todo, n_todo);
+      }
     };
-    if (k <= 8)
-      go(std::integral_constant<int, 8>());
-    else if (k <= 16)
-      go(std::integral_constant<int, 16>());
-    else if (k <= 32)
-      go(std::integral_constant<int, 32>());
-    else
-      go(std::integral_constant<int, 64>());
+    switch (lane_list(k, tree->n)) {
+      case 8: go(std::integral_constant<int, 8>()); break;
+      case 16: go(std::integral_constant<int, 16>()); break;
+      case 32: go(std::integral_constant<int, 32>()); break;
+      default: go(std::integral_constant<int, 64>());
+    }
     return hipGetLastError() == hipSuccess ? KDT_OK : KDT_EDEVICE;
   });
   if (st != KDT_OK) kdt_set_error("kdt_knn_f64: kernel launch failed");

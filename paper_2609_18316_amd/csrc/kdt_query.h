@@ -350,7 +350,8 @@ struct TopK {
   // the hardware min/max order keys exactly.  They are issued directly: the
   // library fmin/fmax would first canonicalise both operands of every slot
   // (IEEE mode), half as many instructions again.
-  __device__ __forceinline__ void insert(uint64_t x) {
+  // Returns the key that fell off.
+  __device__ __forceinline__ uint64_t insert(uint64_t x) {
     double carry = __longlong_as_double((long long)x);
 #pragma unroll
     for (int i = 0; i < KC; ++i) {
@@ -360,6 +361,7 @@ struct TopK {
           : "v"(carry));
       carry = up;
     }
+    return (uint64_t)__double_as_longlong(carry);
   }
   __device__ __forceinline__ void offer(float d2, int32_t id);
   // The KC smallest keys of the list and of a batch of keys (in any order;
@@ -430,6 +432,33 @@ __device__ __forceinline__ void TopK<KC>::offer(float d2, int32_t id) {
   if (key < worst()) insert(key);
 }
 
+// TopK that also knows the smallest squared distance it has turned away: if
+// that is the k-th distance, which of the equals belongs into the list is open
+// to the caller (float64 trees, whose keys are rounded).
+template <int KC>
+struct TopKTie : TopK<KC> {
+  float lost = INFINITY;
+  __device__ __forceinline__ void turn_away(uint64_t key) {
+    lost = fminf(lost, __uint_as_float((uint32_t)(key >> 32)));
+  }
+  __device__ __forceinline__ void offer(float d2, int32_t id) {
+    uint64_t key = make_key(d2, id);
+    if (key < this->worst()) key = this->insert(key);
+    turn_away(key);
+  }
+  __device__ __forceinline__ void merge(double (&c)[kListBatch]) {
+    static_assert(KC >= kListBatch, "the whole batch fits the list");
+    sort_network(c);
+#pragma unroll
+    for (int i = 0; i < kListBatch; ++i) {
+      double& mine = this->a[KC - 1 - i];
+      order_in_place(mine, c[i]);
+      turn_away((uint64_t)__double_as_longlong(c[i]));
+    }
+    sort_bitonic(this->a);
+  }
+};
+
 // The k smallest squared distances alone, for queries that want only the
 // k-th distance: its value does not depend on how equal distances are
 // ordered, so no index is kept and the list takes half the registers of
@@ -498,6 +527,60 @@ struct OpenMetric {
 #ifndef KNN_SM
 #define KNN_SM i
 #endif
+// What a per-lane kNN traversal measures: the float32 points of a tree
+// under a metric.
+template <int D, class Metric>
+struct Space32 {
+  using Coord = float;
+  const TreeView& t;
+  const Metric& m;
+  // Box distances of the nodes c and c + 1.
+  __device__ __forceinline__ void pair(uint32_t c, const float p[D], float& d0, float& d1) const {
+    float lo[D], hi[D];
+    load_box<D>(t.box, c, lo, hi);
+    d0 = m.mindist(lo, hi, p);
+    load_box<D>(t.box, c + 1, lo, hi);
+    d1 = m.mindist(lo, hi, p);
+  }
+  // The records from tree position `base` on, and the squared distance and
+  // identity (input index) of the i-th.
+  __device__ __forceinline__ const float* run(int32_t base) const {
+    return t.rec + (int64_t)base * rec_stride(D);
+  }
+  __device__ __forceinline__ float dist(const float* r, int32_t, int i, const float p[D],
+                                        int32_t& id) const {
+    float x[D];
+    load_rec<D>(r, i, x, id);
+    return m.dist(x, p);
+  }
+};
+
+// The points of a float64 tree, by the float32 rounding of their float64
+// distances and by tree position.  Rounding is monotone, so a box distance
+// rounded this way never exceeds the rounded distance of a point inside.
+template <int D>
+struct Space64 {
+  using Coord = double;
+  const View64& t;
+  __device__ __forceinline__ void pair(uint32_t c, const double p[D], float& d0,
+                                       float& d1) const {
+    const double* b = t.box + (size_t)c * 2 * D;
+    double x[4 * D];
+#pragma unroll
+    for (int a = 0; a < 4 * D; ++a) x[a] = b[a];
+    d0 = (float)box_mindist<D>(x, x + D, p);
+    d1 = (float)box_mindist<D>(x + 2 * D, x + 3 * D, p);
+  }
+  __device__ __forceinline__ const double* run(int32_t base) const {
+    return t.rec + (int64_t)base * D;
+  }
+  __device__ __forceinline__ float dist(const double* r, int32_t base, int i, const double p[D],
+                                        int32_t& id) const {
+    id = base + i;
+    return (float)sq_dist<D>(r + i * D, p);
+  }
+};
+
 // Which lists take a leaf's points in sorted batches (ListMerge<...>::kOn): those of
 // 17 to 32 entries below five dimensions.  Inserting one key costs 64
 // (TopK) or 32 (TopD) instructions at k = 32 and runs for the wave when any
@@ -518,6 +601,8 @@ struct ListMerge<TopK<KC>, D> {
   static constexpr bool kOn = KC == 32 && D <= 4;
   static constexpr int kMin = 3;
 };
+template <int KC, int D>
+struct ListMerge<TopKTie<KC>, D> : ListMerge<TopK<KC>, D> {};
 template <int KC, int D>
 struct ListMerge<TopD<KC>, D> {
   static constexpr bool kOn = KC == 32 && D <= 4;
@@ -547,9 +632,9 @@ inline int lane_list(int k, int64_t n) {
 // keys stay in registers and are merged into the list at once (ListMerge), except for a
 // short rest of a leaf (at most kFewPoints: smoothing lengths on leaves of 20 points
 // 3.00 against 3.52 ms, 5000011 points) and where no lane has many candidates.
-template <int D, bool kMerge, class List, class Metric>
-__device__ __forceinline__ void leaf_offer(const TreeView& t, int32_t b, int cnt, int most,
-                                           const float p[D], List& best, const Metric& metric) {
+template <int D, bool kMerge, class Space, class List>
+__device__ __forceinline__ void leaf_offer(const Space& sp, int32_t b, int cnt, int most,
+                                           const typename Space::Coord p[D], List& best) {
   constexpr int B = kMerge ? kListBatch : 32;
   constexpr int kFewPoints = 8;
   for (int o = 0; o < cnt; o += B) {
@@ -563,16 +648,14 @@ __device__ __forceinline__ void leaf_offer(const TreeView& t, int32_t b, int cnt
     if (batch) {
       if constexpr (kMerge) {
         // the B points from base on, which end inside the array
-        base = max(min(c, (int32_t)t.n - B), 0);
-        const float* r = t.rec + (int64_t)base * rec_stride(D);
+        base = max(min(c, (int32_t)sp.t.n - B), 0);
+        const auto* r = sp.run(base);
         const uint32_t valid = ((1u << m) - 1u) << (c - base);
         typename List::Key key[B];
 #pragma unroll
         for (int i = 0; i < B; ++i) {
-          float x[D];
           int32_t id = 0;
-          load_rec<D>(r, i, x, id);
-          const float d2 = metric.dist(x, p);
+          const float d2 = sp.dist(r, base, i, p, id);
           const bool ok = ((valid >> i) & 1u) && d2 <= w;  // (false for NaN)
           mask |= (uint32_t)ok << i;
           key[i] = batch_key(best, ok, d2, id);
@@ -580,7 +663,7 @@ __device__ __forceinline__ void leaf_offer(const TreeView& t, int32_t b, int cnt
           asm volatile("" : "+v"(key[i]));
           if (i % 4 == 3) __builtin_amdgcn_sched_barrier(0);
         }
-        KDT_LANE_VISIT(t, kVisitInsert, __popc(mask));
+        KDT_LANE_VISIT(sp.t, kVisitInsert, __popc(mask));
         // runs once at most; as a loop the list keeps its registers, as a
         // branch the compiler copies it (153 instead of 128 VGPRs)
         uint32_t go = __any(__popc(mask) > ListMerge<List, D>::kMin);
@@ -591,22 +674,21 @@ __device__ __forceinline__ void leaf_offer(const TreeView& t, int32_t b, int cnt
         }
       }
     } else {
+      const auto* r = sp.run(c);
 #pragma unroll 1
       for (int i = 0; i < m; ++i) {
-        float x[D];
         int32_t id = 0;
-        load_rec<D>(t.rec, c + i, x, id);
-        mask |= (uint32_t)(metric.dist(x, p) <= w) << i;
+        mask |= (uint32_t)(sp.dist(r, c, i, p, id) <= w) << i;
       }
     }
-    if (!batch) KDT_LANE_VISIT(t, kVisitInsert, __popc(mask));
+    if (!batch) KDT_LANE_VISIT(sp.t, kVisitInsert, __popc(mask));
+    const auto* r = sp.run(base);
     while (mask) {
       const int i = __builtin_ctz(mask);
       mask &= mask - 1;
-      float x[D];
       int32_t id = 0;
-      load_rec<D>(t.rec, base + i, x, id);
-      best.offer(metric.dist(x, p), id);
+      const float d2 = sp.dist(r, base, i, p, id);
+      best.offer(d2, id);
     }
   }
 }
@@ -629,9 +711,10 @@ __device__ __forceinline__ void leaf_offer(const TreeView& t, int32_t b, int cnt
 // 10.2, at 3 10.4, at 6 10.8 ms).
 // Whole call, before and after the vote and the merge: 6.64 and 5.10 ms; smoothing
 // lengths of 5000011 points 5.26 and 3.00 ms.
-template <int D, bool kMerge, class List, class Metric>
-__device__ __forceinline__ void knn_median(const TreeView& t, const float p[D], List& best,
-                                           uint32_t* stk, int ld, const Metric& metric) {
+template <int D, bool kMerge, class Space, class List>
+__device__ __forceinline__ void knn_median(const Space& sp, const typename Space::Coord p[D],
+                                           List& best, uint32_t* stk, int ld) {
+  const auto& t = sp.t;
   constexpr int kWait = D > 4 ? 2 : kMerge ? 4 : 6;
   const uint32_t first = 1u << t.levels;
   const int lmax = (int)((t.n + (int64_t(1) << t.levels) - 1) >> t.levels);
@@ -654,17 +737,14 @@ __device__ __forceinline__ void knn_median(const TreeView& t, const float p[D], 
         const int32_t b = (int32_t)((j * t.n) >> t.levels);
         const int32_t e = (int32_t)(((j + 1) * t.n) >> t.levels);
         KDT_LANE_VISIT(t, kVisitPoints, e - b);
-        leaf_offer<D, kMerge>(t, b, e - b, lmax, p, best, metric);
+        leaf_offer<D, kMerge>(sp, b, e - b, lmax, p, best);
         pop = true;
       }
     } else if (!leaf) {
       const uint32_t c0 = 2 * h;
-      float lo[D], hi[D];
+      float d0, d1;
       KDT_LANE_VISIT(t, kVisitNodes, 2);
-      load_box<D>(t.box, c0 - 1, lo, hi);
-      const float d0 = metric.mindist(lo, hi, p);
-      load_box<D>(t.box, c0, lo, hi);
-      const float d1 = metric.mindist(lo, hi, p);
+      sp.pair(c0 - 1, p, d0, d1);
       const float dn = fminf(d0, d1), df = fmaxf(d0, d1);
       const float w = best.worst_d2();
       const int lev = 32 - __clz(h);  // of the children
@@ -696,8 +776,9 @@ __device__ __forceinline__ void knn_median(const TreeView& t, const float p[D], 
 template <int D, bool kMerge = true, class Shape = MedianShape, class List, class Metric = OpenMetric<D>>
 __device__ __forceinline__ void knn_one(const TreeView& t, const float p[D], List& best,
                                         uint32_t* stk, int ld, const Metric& metric = Metric()) {
+  const Space32<D, Metric> space{t, metric};
   if constexpr (std::is_same_v<Shape, MedianShape>) {
-    knn_median<D, kMerge && ListMerge<List, D>::kOn>(t, p, best, stk, ld, metric);
+    knn_median<D, kMerge && ListMerge<List, D>::kOn>(space, p, best, stk, ld);
     return;
   }
   const Shape sh(t);
@@ -713,7 +794,7 @@ __device__ __forceinline__ void knn_one(const TreeView& t, const float p[D], Lis
         int64_t b, e;
         sh.range(node, b, e);
         KDT_LANE_VISIT(t, kVisitPoints, e - b);
-        leaf_offer<D, false>(t, (int32_t)b, (int)(e - b), 0, p, best, metric);
+        leaf_offer<D, false>(space, (int32_t)b, (int)(e - b), 0, p, best);
       } else {
         const uint32_t c0 = sh.left(node), c1 = c0 + 1;
         KDT_LANE_VISIT(t, kVisitNodes, 2);
