@@ -210,12 +210,15 @@ kdt_status kdt_build(const float *d_pts, int64_t n, int32_t d, const kdt_build_o
 kdt_status kdt_free(kdt_tree *tree);
 
 /*
- * Releases the device scratch the library keeps for `stream` between calls
- * (the particle-to-mesh deposits keep theirs, sized by the largest call so
- * far, so that repeated calls allocate nothing).  The memory is returned in
+ * Releases the device memory the library keeps for `stream` between calls: the
+ * scratch of the particle-to-mesh deposits (sized by the largest call so
+ * far) and idle blocks of earlier trees and calls (blocks of up to 128 MiB, at
+ * most 512 MiB per stream and 2 GiB in all; they are also given back when an
+ * allocation of the library fails), so that repeated calls allocate
+ * nothing.  The memory is returned in
  * stream order (work already queued on `stream` finishes first).  Call it
- * before destroying a stream that ran deposits, or to give the memory back;
- * the next deposit on the stream allocates again.  Errors: KDT_EDEVICE.
+ * before destroying a stream that ran the library's calls, or to give the memory back;
+ * the next call on the stream allocates again.  Errors: KDT_EDEVICE.
  */
 kdt_status kdt_stream_release(hipStream_t stream);
 

@@ -984,8 +984,7 @@ static void set_smem_attr(int cap) {
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes(D, cap));
 }
 
-hipError_t dev_alloc(void** ptr, size_t bytes, hipStream_t stream) {
-  if (alloc_should_fail()) return hipErrorOutOfMemory;
+hipError_t pool_alloc(void** ptr, size_t bytes, hipStream_t stream) {
   static std::once_flag once;
   std::call_once(once, [] {
     int dev = 0;
@@ -1026,7 +1025,12 @@ kdt_status build_scratch_alloc(const Plan& p, const PlanDev& pd, BuildScratch& w
 void build_scratch_free(BuildScratch& w, hipStream_t stream) {
   void* ptrs[] = {w.x[0], w.x[1], w.p[0], w.p[1], w.pbox, w.cbox, w.st, w.chist, w.cnt, w.bad};
   for (void* q : ptrs)
-    if (q) (void)(stream == kPlainAlloc ? hipFree(q) : hipFreeAsync(q, stream));
+    if (q) {
+      if (stream == kPlainAlloc)
+        (void)hipFree(q);
+      else
+        dev_free(q, stream);
+    }
   w = BuildScratch();
 }
 

@@ -148,11 +148,11 @@ extern "C" kdt_status kdt_fof(const kdt_tree* tree, float l, int32_t* d_labels, 
     case 8: st = fof_launch<8>(v, tree->leaf, tree->n_nodes, l2, d_labels, conn, stream); break;
     case 16: st = fof_launch<16>(v, tree->leaf, tree->n_nodes, l2, d_labels, conn, stream); break;
     default:
-      (void)hipFreeAsync(conn, stream);
+      dev_free(conn, stream);
       kdt_set_error("kdt_fof: unsupported dimension %d", tree->d);
       return KDT_EUNSUPPORTED;
   }
-  (void)hipFreeAsync(conn, stream);
+  dev_free(conn, stream);
   if (st != KDT_OK) return st;
   k_fof_final<<<g, 256, 0, stream>>>(d_labels, n);
   if (hipGetLastError() != hipSuccess) {

@@ -252,10 +252,16 @@ void build_scratch_free(BuildScratch& w, hipStream_t stream);
 // phase 0: ingest and root boxes; phase 1: everything after.
 kdt_status build_launch(const Plan& p, const PlanDev& pd, const float* d_pts,
                         const BuildScratch& w, const BuildOut& o, int phase, hipStream_t stream);
-// Stream-ordered device allocation from the default pool (kept cached).
-// Fails on purpose when the allocation-failure hook (kdt_debug_fail_alloc)
+// Stream-ordered device memory: what dev_alloc returns may be used by work
+// queued on `stream` from here on, and dev_free (the same stream) gives it back once the work
+// queued so far has run.  Small blocks are kept by the library for later calls
+// on the same stream, the rest goes through the default pool (kdt_api.hip says which).
+// dev_alloc fails on purpose when the allocation-failure hook (kdt_debug_fail_alloc)
 // says so.
 hipError_t dev_alloc(void** ptr, size_t bytes, hipStream_t stream);
+void dev_free(void* ptr, hipStream_t stream);
+// Straight from the default pool (kdt_build.hip).
+hipError_t pool_alloc(void** ptr, size_t bytes, hipStream_t stream);
 // True if the allocation-failure hook wants this allocation to fail.
 bool alloc_should_fail();
 // The device counters of the instrumented build (KDT_COUNT_VISITS), else
@@ -287,7 +293,7 @@ class PoolBuffers {
   void release() {
     for (void*& q : held_)
       if (q) {
-        (void)hipFreeAsync(q, stream_);
+        dev_free(q, stream_);
         q = nullptr;
       }
   }

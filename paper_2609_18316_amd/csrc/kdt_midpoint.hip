@@ -594,9 +594,9 @@ bool grow_nodes(NodeArrays& a, int64_t need, int64_t used, hipStream_t stream) {
   if (dev_alloc((void**)&b.box, sizeof(float) * 2 * P * b.cap, stream) != hipSuccess ||
       dev_alloc((void**)&b.axis, sizeof(int32_t) * b.cap, stream) != hipSuccess ||
       dev_alloc((void**)&b.split, sizeof(float) * b.cap, stream) != hipSuccess) {
-    (void)hipFreeAsync(b.node, stream);
-    if (b.box) (void)hipFreeAsync(b.box, stream);
-    if (b.axis) (void)hipFreeAsync(b.axis, stream);
+    dev_free(b.node, stream);
+    if (b.box) dev_free(b.box, stream);
+    if (b.axis) dev_free(b.axis, stream);
     return false;
   }
   if (used > 0) {
@@ -607,14 +607,14 @@ bool grow_nodes(NodeArrays& a, int64_t need, int64_t used, hipStream_t stream) {
     (void)hipMemcpyAsync(b.split, a.split, sizeof(float) * used, hipMemcpyDeviceToDevice, stream);
   }
   for (void* p : {(void*)a.node, (void*)a.box, (void*)a.axis, (void*)a.split})
-    if (p) (void)hipFreeAsync(p, stream);
+    if (p) dev_free(p, stream);
   a = b;
   return true;
 }
 
 void free_nodes(NodeArrays& a, hipStream_t stream) {
   for (void* p : {(void*)a.node, (void*)a.box, (void*)a.axis, (void*)a.split})
-    if (p) (void)hipFreeAsync(p, stream);
+    if (p) dev_free(p, stream);
   a = NodeArrays();
 }
 
@@ -714,12 +714,12 @@ kdt_status build_midpoint_d(const float* d_pts, int64_t n, int leaf, bool check,
       }
       KDT_M(hipMemcpyAsync(tmp, seg, sizeof(int4) * (size_t)m, hipMemcpyDeviceToDevice, stream));
       if (!ensure(2 * m)) {
-        (void)hipFreeAsync(tmp, stream);
+        dev_free(tmp, stream);
         kdt_set_error("kdt_build (sliding midpoint): device allocation failed");
         return KDT_ENOMEM;
       }
       KDT_M(hipMemcpyAsync(seg, tmp, sizeof(int4) * (size_t)m, hipMemcpyDeviceToDevice, stream));
-      (void)hipFreeAsync(tmp, stream);
+      dev_free(tmp, stream);
     }
     if (!grow_nodes<D>(na, node_base + 2 * m, node_base, stream)) {
       kdt_set_error("kdt_build (sliding midpoint): cannot grow the nodes");
@@ -803,7 +803,7 @@ kdt_status build_midpoint_d(const float* d_pts, int64_t n, int leaf, bool check,
   if (e == hipSuccess) e = hipMemcpyAsync(t->nodes, na.node, b_node, hipMemcpyDeviceToDevice, stream);
   if (e == hipSuccess) e = hipGetLastError();
   if (e != hipSuccess) {
-    (void)hipFreeAsync(block, stream);
+    dev_free(block, stream);
     t->rec = nullptr;
     kdt_set_error("kdt_build (sliding midpoint): %s", hipGetErrorString(e));
     return KDT_EDEVICE;

@@ -2,6 +2,8 @@
 // (kNN, Sec. 2.3 / Algorithm 2; ball counts, Algorithm 3) for gfx950.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "kdt_packet.h"
 #include "kdt_torus.h"
 
@@ -16,6 +18,10 @@ constexpr int kRangePasses = 8;
 constexpr uint32_t kRangeBudgetFirst = 512;
 constexpr uint32_t kRangeBudget = 32;
 constexpr uint32_t kRangeTaskCap = 1u << 20;
+// Task slots per wave of the first pass, where that is fewer (launches below 2^16
+// queries): the lists' 117 MB for 2^20 slots are far more than a small call's own data.
+// (256 per wave cost the counts of large k: 50021 queries, k = 1000, 15.9 -> 17.6 ms.)
+constexpr int64_t kRangeTasksPerWave = 1024;
 constexpr unsigned kRangeTaskBlocks = 8192;
 // The first pass hands work on only once fewer than this many of its waves
 // are left (about what the chip holds at once).
@@ -344,9 +350,12 @@ static kdt_status count_packet_launch(const typename Q::View& v, int leaf, Q src
   PoolBuffers buf(stream);
   PacketTask* tasks = nullptr;
   uint32_t* counts = nullptr;
+  const int64_t waves = (nq + 63) / 64;
+  const uint32_t cap =
+      (uint32_t)std::min<int64_t>(kRangeTaskCap, std::max<int64_t>(1, waves) * kRangeTasksPerWave);
   // counts[0 .. kRangePasses - 1): tasks per pass; then the first pass's
   // finished-wave counters
-  if (!buf.get(&tasks, (size_t)kRangeTaskCap * (kRangePasses - 1)) ||
+  if (!buf.get(&tasks, (size_t)cap * (kRangePasses - 1)) ||
       !buf.get(&counts, kRangePasses + kDoneShards)) {
     kdt_set_error("%s: device allocation failed for the task lists", who);
     return KDT_ENOMEM;
@@ -355,13 +364,12 @@ static kdt_status count_packet_launch(const typename Q::View& v, int leaf, Q src
   // a caller's budget applies to every wave of every launch
   const uint32_t first = split_budget ? split_budget : kRangeBudgetFirst;
   const uint32_t later = split_budget ? split_budget : kRangeBudget;
-  const int64_t waves = (nq + 63) / 64;
   const uint32_t tail_from = split_budget                ? 0u
                              : waves > kRangeTailWaves ? (uint32_t)(waves - kRangeTailWaves)
                                                        : 0u;
   const FillOut fo = fill ? *fill : FillOut{nullptr, nullptr, nullptr};
   if (fill) k_zero_i32<<<(unsigned)((nq + 255) / 256), 256, 0, stream>>>(fill->cur, nq);
-  const PacketSpill sp0{tasks, counts, kRangeTaskCap, first, counts + kRangePasses, tail_from};
+  const PacketSpill sp0{tasks, counts, cap, first, counts + kRangePasses, tail_from};
   if (fill)
     k_count_packet<D, Q, true><<<grid, 64 * kPWaves, smem, stream>>>(v, src, nq, order, d_count,
                                                                      leaf, sp0, fo);
@@ -371,15 +379,14 @@ static kdt_status count_packet_launch(const typename Q::View& v, int leaf, Q src
   for (int pass = 1; pass < kRangePasses; ++pass) {
     const bool last = pass == kRangePasses - 1;
     const PacketSpill out = last ? PacketSpill{nullptr, nullptr, 0u, 0u, nullptr, 0u}
-                                : PacketSpill{tasks + (size_t)pass * kRangeTaskCap, counts + pass,
-                                             kRangeTaskCap, later, nullptr, 0u};
-    const PacketTask* in = tasks + (size_t)(pass - 1) * kRangeTaskCap;
+                                : PacketSpill{tasks + (size_t)pass * cap, counts + pass, cap, later, nullptr, 0u};
+    const PacketTask* in = tasks + (size_t)(pass - 1) * cap;
     if (fill)
       k_count_tasks<D, Q, true><<<kRangeTaskBlocks, 64 * kPWaves, smem, stream>>>(
-          v, src, nq, order, d_count, leaf, in, counts + pass - 1, kRangeTaskCap, out, fo);
+          v, src, nq, order, d_count, leaf, in, counts + pass - 1, cap, out, fo);
     else
       k_count_tasks<D, Q, false><<<kRangeTaskBlocks, 64 * kPWaves, smem, stream>>>(
-          v, src, nq, order, d_count, leaf, in, counts + pass - 1, kRangeTaskCap, out, fo);
+          v, src, nq, order, d_count, leaf, in, counts + pass - 1, cap, out, fo);
   }
   if (hipGetLastError() != hipSuccess) {
     kdt_set_error("%s: packet kernel launch failed", who);

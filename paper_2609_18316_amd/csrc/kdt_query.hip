@@ -378,7 +378,7 @@ static kdt_status knn_impl(const kdt_tree* t, const float* d_q, int64_t nq, int 
                       ? knn_dispatch<D>(t, d_q, nq, k, d_idx, d_d2, mode, use, stream)
                       : knn_packet_launch<D>(view_of(t), t->leaf, d_q, nq, k, d_idx, d_d2, mode,
                                              use, stream);
-  if (order && !ws) (void)hipFreeAsync(order, stream);
+  if (order && !ws) dev_free(order, stream);
   return st;
 }
 
@@ -415,7 +415,7 @@ static kdt_status range_impl(const kdt_tree* t, const float* d_q, int64_t nq, fl
                                                         nullptr);
   }
   if (st != KDT_OK) {
-    if (own) (void)hipFreeAsync(own, stream);
+    if (own) dev_free(own, stream);
     return st;
   }
   if (d_off) {
@@ -481,7 +481,7 @@ static kdt_status range_impl(const kdt_tree* t, const float* d_q, int64_t nq, fl
       }
     }
   }
-  if (own) (void)hipFreeAsync(own, stream);
+  if (own) dev_free(own, stream);
   if (st == KDT_OK) KDT_HIP(hipGetLastError());
   return st;
 }
