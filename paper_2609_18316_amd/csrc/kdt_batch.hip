@@ -128,7 +128,7 @@ __global__ __launch_bounds__(256) void k_fof_forest_packet(
     uint32_t* __restrict__ conn, unsigned long long* __restrict__ ctr) {
   extern __shared__ __align__(16) float lds[];
   const int wave = threadIdx.x >> 6, lane = lane_id();
-  float* slice = lds + (size_t)wave * leaf_cap * rec_stride(D);
+  float* slice = lds + (size_t)wave * fof_wave_floats<D>(leaf_cap);
   const int64_t n_packets = pbase[n_sets];
   for (;;) {
     unsigned long long got = 0;
@@ -156,7 +156,8 @@ __global__ __launch_bounds__(256) void k_fof_forest_packet(
 #pragma unroll
       for (int a = 0; a < D; ++a) q[a] = 0.0f;
     }
-    packet_fof<D>(t, q, pos, me, active, l2, (int32_t)sd.off, parent, conn + sd.node_base, slice);
+    packet_fof<D>(t, q, pos, me, active, l2, (int32_t)sd.off, parent, conn + sd.node_base, slice,
+                  leaf_cap);
   }
 }
 
@@ -269,7 +270,7 @@ struct kdt_batch_plan {
 // wave).
 template <int D>
 static size_t forest_lds_bytes(int leaf) {
-  return sizeof(float) * (size_t)leaf * rec_stride(D) * 4;
+  return sizeof(float) * fof_wave_floats<D>(leaf) * 4;
 }
 
 template <int D, int KC>

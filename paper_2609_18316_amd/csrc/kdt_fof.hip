@@ -88,7 +88,12 @@ static kdt_status fof_launch(const TreeView& v, int leaf, int64_t n_nodes, float
     kdt_set_error("kdt_fof: clique kernel launch failed");
     return KDT_EDEVICE;
   }
-  if (leaf <= 64) return fof_packet_launch<D>(v, leaf, l2, labels, conn, stream);
+  if (leaf <= 64) {
+    // nodes of up to 32 points serve as leaves, as for the counts
+    int cap = 0;
+    const TreeView vc = count_view(v, leaf, &cap);
+    return fof_packet_launch<D>(vc, cap, l2, labels, conn, stream);
+  }
   k_fof_link<D><<<gl, kFBlock, 0, stream>>>(v, l2, labels, conn);
   return KDT_OK;
 }

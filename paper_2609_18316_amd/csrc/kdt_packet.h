@@ -764,64 +764,93 @@ __device__ __forceinline__ int64_t packet_range_count(const View& t, const Shape
   return count;
 }
 
-// Friends-of-friends links of the 64 points of a wave (tree positions pos,
-// indices me; union-find indices base + index).  A node whose points are known
-// to form one component (conn flag) is skipped by every lane whose own root is
+// LDS floats of one wave of the grouping: the open leaf and its points' sets.
+template <int D>
+__host__ __device__ constexpr size_t fof_wave_floats(int leaf) {
+  return (size_t)leaf * rec_stride(D) + 64;
+}
+
+// Friends-of-friends links of the 64 points of a wave (consecutive tree positions
+// pos, indices me; union-find indices base + index).  A node whose points are known
+// to form one component is skipped by every lane whose own root is
 // already that component's, needs a single link when it lies entirely within l
-// of the lane, and otherwise only its first friend.  A node entirely within l
+// of the lane, and otherwise only its first friend.  Known are the cliques (box
+// diagonal within l, joined before this kernel) and the nodes flagged in this launch
+// (conn).  A node entirely within l
 // of several lanes is joined to the lowest such lane's point by the whole wave
 // (64 links at a time), and that lane flags it; the others link to its first
 // point.  Elsewhere each pair within l
 // is linked by the point that comes first in tree order: a lane never enters a
 // node that ends at or before its own position, so the search of a ball costs
-// about half.  Leaves must hold at most 64 points.  The metric supplies the
+// about half.  Leaves must hold at most 64 points; `lds` is the wave's slice of
+// fof_wave_floats<D>(leaf_cap) floats.  The metric supplies the
 // point distance and the node bounds (OpenMetric by default).
+//
+// What bounds it: chains of dependent loads (on 2^24 clustered points the waves waited
+// for 73 % of their time), so:
+//  - the search starts at the smallest node that holds the wave's points and
+//    climbs from there, testing one later sibling per level; a descent from the root
+//    tests two nodes per level.  Both children are tested with one load when
+//    their parent is opened.  A wave now visits 57 nodes and tests 9
+//    siblings where it popped 113 nodes (uniform points: 28 and 8 for 75).
+//  - in a leaf the sets of all its points are found side by side, by a lane
+//    each, and a lane links only friends of other sets; one friend after the
+//    other, each with a find of its own, a wave took 41 rounds.
+// This kernel on 2^24 clustered points: 9.3 ms before; 7.2 by the climb and
+// cached loads (uf_ld), 6.3 with the sets found side by side, 6.0 with
+// 32-point nodes as leaves.
 template <int D, class Metric = OpenMetric<D>>
 __device__ __forceinline__ void packet_fof(const TreeView& t, const float p[D], int64_t pos,
                                            int32_t me, bool active, float l2, int32_t base,
                                            int32_t* __restrict__ parent,
                                            uint32_t* __restrict__ conn, float* lds,
-                                           const Metric& metric = Metric()) {
+                                           int leaf_cap, const Metric& metric = Metric()) {
   constexpr int S = rec_stride(D);
   const int lane = lane_id();
   const uint32_t first_leaf = (1u << t.levels) - 1u;
-  const int32_t gme = base + me;
-  int32_t myroot = gme;  // an ancestor of this lane's point (see uf_union_from)
+  int32_t myroot = base + me;  // an ancestor of this lane's point (see uf_union_from)
   LeafReader<D> leaf(t, lds);
+  int32_t* roots = reinterpret_cast<int32_t*>(lds + (size_t)leaf_cap * S);  // [64]
+  // the path: the leaf that holds the wave's first point, then its ancestors
+  const int64_t s0 = ((int64_t)__builtin_amdgcn_readfirstlane((int)(pos >> 32)) << 32) |
+                     (uint32_t)__builtin_amdgcn_readfirstlane((int)pos);
+  const int64_t s1 = min(s0 + 63, t.n - 1);
+  int lev = t.levels;
+  int64_t j = ((s0 + 1) << lev) / t.n;
+  while (j > 0 && node_begin(t.n, lev, j) > s0) --j;
+  while (node_begin(t.n, lev, j + 1) <= s0) ++j;
+  while (node_begin(t.n, lev, j + 1) <= s1) --lev, j >>= 1;
+  uint32_t path = (1u << lev) - 1u + (uint32_t)j;
   uint32_t stackv = 0;
-  uint32_t stk_lo = 0xFFFFFFFFu, stk_hi = 0xFFFFFFFFu;
-  int sp = 1;
-  while (sp > 0) {
-    --sp;
-    const uint32_t node = (uint32_t)__builtin_amdgcn_readlane((int)stackv, sp);
-    const uint64_t live = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)stk_hi, sp) << 32) |
-                          (uint32_t)__builtin_amdgcn_readlane((int)stk_lo, sp);
-    const int lev = node_level(node);
-    const int64_t j = (int64_t)node - ((int64_t(1) << lev) - 1);
+  uint32_t stk_lo = 0, stk_hi = 0;
+  int sp = 0;
+  uint32_t node = path;
+  uint64_t live = __ballot(active);  // the lanes that node is within reach of
+  float lo[D], hi[D];
+  load_box_uniform<D>(t.box, node, lo, hi);
+  for (;;) {
+    // node, its box and live are set: visit it
+    lev = node_level(node);
+    j = (int64_t)node - ((int64_t(1) << lev) - 1);
     const int64_t b = node_begin(t.n, lev, j), e = node_begin(t.n, lev, j + 1);
-    // a lane links only towards later tree positions: a node that ends at or
-    // before its own position is left to the points inside it
-    const bool mine = active && ((live >> lane) & 1ull) && e > pos;
-    float lo[D], hi[D];
-    load_box_uniform<D>(t.box, node, lo, hi);
-    bool touch = mine && metric.mindist(lo, hi, p) <= l2;
-    if (!__any(touch)) continue;
-    const int32_t gfirst = base + __float_as_int(t.rec[b * S + D]);
-    const bool one = flag_ld(conn + node) != 0;
-    if (one && touch) {
-      const bool inside = pos >= b && pos < e;
-      if (!inside) myroot = uf_find(parent, myroot);
-      touch = !inside && myroot != uf_find(parent, gfirst);
-    }
-    if (!__any(touch)) continue;
-    const bool full = touch && metric.maxdist(lo, hi, p) <= l2;
-    if (one) {
-      if (full) uf_union_from(parent, myroot, gfirst);
-    } else {
-      const uint64_t fm = __ballot(full);
-      if (fm != 0) {
+    bool touch = (live >> lane) & 1ull;
+    bool full = touch && metric.maxdist(lo, hi, p) <= l2;
+    bool one = box_diag2<D>(lo, hi) <= l2;
+    if (!one) one = flag_ld(conn + node) != 0;
+    if (one || __any(full)) {
+      const int32_t gfirst = base + __float_as_int(t.rec[b * S + D]);
+      if (one) {
+        if (touch) {
+          const bool inside = pos >= b && pos < e;
+          if (!inside) myroot = uf_find(parent, myroot);
+          touch = !inside && myroot != uf_find(parent, gfirst);
+          full = full && touch;
+          if (full) uf_union_from(parent, myroot, gfirst);
+        }
+      } else {
         // every point of the node is a friend of the leader's point: the
         // whole wave links them to it, 64 at a time
+        const uint64_t fm = __ballot(full);
         const int leader = __ffsll((unsigned long long)fm) - 1;
         const int32_t lroot = __builtin_amdgcn_readlane(myroot, leader);
         for (int64_t i = b + lane; i < e; i += 64) {
@@ -836,41 +865,86 @@ __device__ __forceinline__ void packet_fof(const TreeView& t, const float p[D], 
       }
     }
     const bool part = touch && !full;
-    const uint64_t pm = __ballot(part);
-    if (pm == 0) continue;
-    if (node >= first_leaf) {
-      // Friends in the leaf: distances for every lane first, then each
-      // lane links its own friends.
-      const int cnt = (int)(e - b);
-      leaf.open(b, cnt);
-      uint64_t fr = 0;
+    bool down = false;  // the next node is a child, its box loaded
+    if (__any(part)) {
+      if (node >= first_leaf) {
+        // Friends in the leaf: distances for every lane first, then each
+        // lane links its own friends.
+        const int cnt = (int)(e - b);
+        leaf.open(b, cnt);
+        uint64_t fr = 0;
 #pragma unroll uniform_batch<D>()
-      for (int i = 0; i < cnt; ++i) {
-        float x[D];
-        leaf.point(i, x);
-        fr |= (uint64_t)(metric.dist(x, p) <= l2) << i;
-      }
-      if (!part) fr = 0;
-      while (fr) {
-        const int i = __ffsll((unsigned long long)fr) - 1;
-        fr &= fr - 1;
-        const int32_t id = __float_as_int(t.rec[(b + i) * S + D]);
-        if (one) {
-          uf_union_from(parent, myroot, base + id);
-          break;
+        for (int i = 0; i < cnt; ++i) {
+          float x[D];
+          leaf.point(i, x);
+          fr |= (uint64_t)(metric.dist(x, p) <= l2) << i;
         }
-        if (b + i > pos) uf_union_from(parent, myroot, base + id);
-      }
-    } else {
-      const uint32_t mlo = (uint32_t)pm, mhi = (uint32_t)(pm >> 32);
+        if (!part) fr = 0;
+        if (one) {
+          fr &= 0 - fr;
+        } else if (pos >= b) {
+          fr &= pos - b >= 63 ? 0ull : ~0ull << (pos - b + 1);  // later points only
+        }
+        if (__any(fr != 0)) {
+          // the points' sets, found side by side; most friends share one already
+          if (lane < cnt) roots[lane] = uf_find(parent, base + leaf.index(lane));
+          if (fr) myroot = uf_find(parent, myroot);
+          wave_sync();
+          int32_t last = myroot;  // a set joined already
+          while (fr) {
+            const int32_t r = roots[__ffsll((unsigned long long)fr) - 1];
+            fr &= fr - 1;
+            if (r == last) continue;
+            last = r;
+            uf_union_from(parent, myroot, r);
+          }
+        }
+      } else {
+        const uint32_t c0 = 2 * node + 1;
+        float lo1[D], hi1[D];
+        load_box_uniform<D>(t.box, c0, lo, hi);
+        load_box_uniform<D>(t.box, c0 + 1, lo1, hi1);
+        const int64_t mid = node_begin(t.n, lev + 1, 2 * j + 1);
+        const uint64_t m0 = __ballot(part && mid > pos && metric.mindist(lo, hi, p) <= l2);
+        const uint64_t m1 = __ballot(part && e > pos && metric.mindist(lo1, hi1, p) <= l2);
+        if (m1 != 0) {
+          if (m0 != 0) {
+            stackv = lane == sp ? c0 + 1 : stackv;
+            stk_lo = lane == sp ? (uint32_t)m1 : stk_lo;
+            stk_hi = lane == sp ? (uint32_t)(m1 >> 32) : stk_hi;
+            ++sp;
+          } else {
 #pragma unroll
-      for (int c = 2; c >= 1; --c) {
-        stackv = lane == sp ? 2 * node + c : stackv;
-        stk_lo = lane == sp ? mlo : stk_lo;
-        stk_hi = lane == sp ? mhi : stk_hi;
-        ++sp;
+            for (int a = 0; a < D; ++a) lo[a] = lo1[a], hi[a] = hi1[a];
+          }
+        }
+        if ((m0 | m1) != 0) {
+          node = m0 != 0 ? c0 : c0 + 1;
+          live = m0 != 0 ? m0 : m1;
+          down = true;
+        }
       }
     }
+    if (down) continue;
+    if (sp > 0) {
+      --sp;
+      node = (uint32_t)__builtin_amdgcn_readlane((int)stackv, sp);
+      live = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)stk_hi, sp) << 32) |
+             (uint32_t)__builtin_amdgcn_readlane((int)stk_lo, sp);
+      load_box_uniform<D>(t.box, node, lo, hi);
+      continue;
+    }
+    // up the path: the next later sibling within reach
+    live = 0;
+    while (path != 0 && live == 0) {
+      const bool left = path & 1u;  // (a left child's id is odd)
+      node = path + 1;
+      path = (path - 1) >> 1;
+      if (!left) continue;
+      load_box_uniform<D>(t.box, node, lo, hi);
+      live = __ballot(active && metric.mindist(lo, hi, p) <= l2);
+    }
+    if (live == 0) break;
   }
 }
 

@@ -27,15 +27,15 @@ constexpr unsigned kRangeTaskBlocks = 8192;
 // are left (about what the chip holds at once).
 constexpr int64_t kRangeTailWaves = 8192;
 
-// LDS of a workgroup: a leaf slice per wave.
+// LDS of a workgroup of the grouping: a slice per wave.
 template <int D>
-size_t packet_lds_bytes(int leaf) {
-  return sizeof(float) * (size_t)leaf * rec_stride(D) * kPWaves;
+size_t fof_lds_bytes(int leaf) {
+  return sizeof(float) * fof_wave_floats<D>(leaf) * kPWaves;
 }
 
 template <int D>
-__device__ __forceinline__ float* wave_slice(float* lds, int wave, int leaf_cap) {
-  return lds + (size_t)wave * leaf_cap * rec_stride(D);
+__device__ __forceinline__ float* fof_slice(float* lds, int wave, int leaf_cap) {
+  return lds + (size_t)wave * fof_wave_floats<D>(leaf_cap);
 }
 
 template <int D>
@@ -250,14 +250,15 @@ __global__ __launch_bounds__(64 * kPWaves) void k_fof_packet(TreeView t, float l
 #pragma unroll
     for (int a = 0; a < D; ++a) p[a] = 0.0f;
   }
-  packet_fof<D>(t, p, pos, me, active, l2, 0, parent, conn, wave_slice<D>(lds, wave, leaf_cap));
+  packet_fof<D>(t, p, pos, me, active, l2, 0, parent, conn, fof_slice<D>(lds, wave, leaf_cap),
+                leaf_cap);
 }
 
 template <int D>
 kdt_status fof_packet_launch(const TreeView& v, int leaf, float l2, int32_t* parent, uint32_t* conn,
                              hipStream_t stream) {
   const unsigned grid = (unsigned)((v.n + 64 * kPWaves - 1) / (64 * kPWaves));
-  k_fof_packet<D><<<grid, 64 * kPWaves, packet_lds_bytes<D>(leaf), stream>>>(v, l2, parent, conn,
+  k_fof_packet<D><<<grid, 64 * kPWaves, fof_lds_bytes<D>(leaf), stream>>>(v, l2, parent, conn,
                                                                             leaf);
   if (hipGetLastError() != hipSuccess) {
     kdt_set_error("kdt_fof: packet kernel launch failed");
@@ -286,15 +287,15 @@ __global__ __launch_bounds__(64 * kPWaves) void k_fof_torus_packet(TreeView t, f
 #pragma unroll
     for (int a = 0; a < D; ++a) p[a] = 0.0f;
   }
-  packet_fof<D>(t, p, pos, me, active, l2, 0, parent, conn, wave_slice<D>(lds, wave, leaf_cap),
-                TorusMetric<D>{T});
+  packet_fof<D>(t, p, pos, me, active, l2, 0, parent, conn, fof_slice<D>(lds, wave, leaf_cap),
+                leaf_cap, TorusMetric<D>{T});
 }
 
 template <int D>
 kdt_status torus_fof_packet_launch(const TreeView& v, int leaf, float l2, const Torus<D>& T,
                                    int32_t* parent, uint32_t* conn, hipStream_t stream) {
   const unsigned grid = (unsigned)((v.n + 64 * kPWaves - 1) / (64 * kPWaves));
-  k_fof_torus_packet<D><<<grid, 64 * kPWaves, packet_lds_bytes<D>(leaf), stream>>>(
+  k_fof_torus_packet<D><<<grid, 64 * kPWaves, fof_lds_bytes<D>(leaf), stream>>>(
       v, l2, T, parent, conn, leaf);
   if (hipGetLastError() != hipSuccess) {
     kdt_set_error("kdt_fof_torus: packet kernel launch failed");

@@ -462,7 +462,9 @@ static kdt_status torus_fof_impl(const kdt_tree* tr, float l, const float* perio
       tr->box, tr->n_nodes, l2, clique);
   k_torus_clique_join<D><<<g, 256, 0, stream>>>(v, clique, d_labels);
   if (tr->leaf <= 64) {
-    st = torus_fof_packet_launch<D>(v, tr->leaf, l2, T, d_labels, clique, stream);
+    int cap = 0;
+    const TreeView vc = count_view(v, tr->leaf, &cap);
+    st = torus_fof_packet_launch<D>(vc, cap, l2, T, d_labels, clique, stream);
     if (st != KDT_OK) return st;
   } else {
     const size_t smem = sizeof(uint32_t) * (size_t)(tr->levels + 2) * kTBlock;
