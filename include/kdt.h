@@ -594,8 +594,8 @@ const int32_t *kdt_tree_perm(const kdt_tree *tree);
  * bopts->leaf_size sets N_leaf for every set; 0 (or NULL bopts) gives each
  * set the tuned N_leaf of its own size (kdt_tuning_get(d, n_s, k));
  * qopts->traversal
- * picks the batched kNN kernel (0 and 2: wave packets, the measured default
- * for all-points queries; 1: one query per lane; leaf_size > 64 always uses
+ * picks the batched kNN kernel (1: one query per lane, 2: wave packets, 0: 1 for
+ * d <= 4, else 2, as measured for all-points queries; leaf_size > 64 always uses
  * 1); qopts may be NULL and its other fields are unused.  Results are
  * identical either way.
  *

@@ -2,10 +2,11 @@
 //
 // A batch plan fixes every shape on the host: the forest schedule (each level
 // kernel of the build covers the nodes of every set at that level, so a level
-// costs one launch for the whole batch), all buffers, and persistent
-// work-queue kernels for the queries: workgroups take packets of 128
-// consecutive points from a device counter until the batch is exhausted; each
-// lane finds its set and runs the same traversal as the single-tree kernels.
+// costs one launch for the whole batch), all buffers, and query kernels over
+// packets of 64 consecutive points of one set, a packet per wave: launched
+// outright for the kNN with one query per lane, taken from a device counter by
+// persistent waves for the wave-shared kNN and the grouping.  Each runs the same
+// traversal as the single-tree kernels.
 // The pipeline (build, kNN of every point, friends-of-friends) is captured
 // once into a hipGraph and replayed.  Mode 0 is the baseline: the single-tree
 // entry points called once per set, eagerly.
@@ -49,32 +50,44 @@ __device__ __forceinline__ int64_t next_packet(unsigned long long* ctr, int64_t*
   return p;
 }
 
-template <int D, int KC>
-__global__ __launch_bounds__(kBQ) void k_knn_forest(const SetDesc* __restrict__ sets, int n_sets,
-                                                    const float* __restrict__ rec,
-                                                    const float* __restrict__ box, int64_t total,
-                                                    int k, int32_t* __restrict__ oidx,
-                                                    float* __restrict__ od2,
-                                                    unsigned long long* __restrict__ ctr) {
-  __shared__ uint32_t stk[kMaxDepth][kBQ];
-  __shared__ int64_t slot;
-  const int64_t n_packets = (total + kBQ - 1) / kBQ;
-  for (;;) {
-    const int64_t pk = next_packet(ctr, &slot);
-    if (pk >= n_packets) break;
-    const int64_t row = pk * kBQ + threadIdx.x;
-    if (row < total) {
-      const SetDesc sd = sets[find_set(sets, n_sets, row)];
-      const TreeView t = set_view<D>(sd, rec, box);
-      float q[D];
-      int32_t id = 0;
-      load_rec<D>(t.rec, row - sd.off, q, id);
-      TopK<KC> best;
-      best.init(k);
-      knn_one<D, false>(t, q, best, &stk[0][threadIdx.x], kBQ);
-      knn_write<KC>(best, k, 0, sd.off + id, oidx, od2);
-    }
+// The set of packet pk: packets hold 64 consecutive points of one set and never
+// straddle sets (pbase: the sets' first packets), so a wave always walks one tree.
+__device__ __forceinline__ int packet_set(const int64_t* __restrict__ pbase, int n_sets,
+                                          int64_t pk) {
+  int lo = 0, hi = n_sets - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (pbase[mid] <= pk)
+      lo = mid;
+    else
+      hi = mid - 1;
   }
+  return __builtin_amdgcn_readfirstlane(lo);
+}
+
+// kNN of every point, one traversal per lane and one packet per wave.
+template <int D, int KC>
+__global__ __launch_bounds__(kBQ)
+__attribute__((amdgpu_waves_per_eu(lane_waves<D, KC, false>()))) void k_knn_forest(
+    const SetDesc* __restrict__ sets, int n_sets, const int64_t* __restrict__ pbase,
+    const float* __restrict__ rec, const float* __restrict__ box, int k,
+    int32_t* __restrict__ oidx, float* __restrict__ od2) {
+  extern __shared__ uint32_t knn_stk[];  // [levels + 1][kBQ] of the deepest tree
+  const int64_t pk = xcd_block<kXcdRunLane>() * (kBQ / 64) +
+                     __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  if (pk >= pbase[n_sets]) return;
+  const int s = packet_set(pbase, n_sets, pk);
+  const SetDesc sd = sets[s];
+  const TreeView t = set_view<D>(sd, rec, box);
+  const int64_t pos = (pk - pbase[s]) * 64 + lane_id();
+  if (pos >= sd.n) return;
+  float q[D];
+  int32_t id = 0;
+  load_rec<D>(t.rec, pos, q, id);
+  TopK<KC> best;
+  best.init(k);
+  knn_one<D>(t, q, best, knn_stk + threadIdx.x, kBQ);
+  knn_write<KC>(best, k, 0, sd.off + id, oidx, od2);
 }
 
 // Persistent wave-level work queue over packets of 64 consecutive points of
@@ -94,12 +107,7 @@ __global__ __launch_bounds__(256) void k_knn_forest_packet(
     const int64_t pk = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(got >> 32)) << 32) |
                                  (uint32_t)__builtin_amdgcn_readfirstlane((int)got));
     if (pk >= n_packets) break;
-    int lo = 0, hi = n_sets - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (pbase[mid] <= pk) lo = mid;
-      else hi = mid - 1;
-    }
+    const int lo = packet_set(pbase, n_sets, pk);
     const SetDesc sd = sets[lo];
     const TreeView t = set_view<D>(sd, rec, box);
     const int64_t pos = (pk - pbase[lo]) * 64 + lane;
@@ -136,12 +144,7 @@ __global__ __launch_bounds__(256) void k_fof_forest_packet(
     const int64_t pk = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(got >> 32)) << 32) |
                                  (uint32_t)__builtin_amdgcn_readfirstlane((int)got));
     if (pk >= n_packets) break;
-    int lo = 0, hi = n_sets - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (pbase[mid] <= pk) lo = mid;
-      else hi = mid - 1;
-    }
+    const int lo = packet_set(pbase, n_sets, pk);
     const SetDesc sd = sets[lo];
     const TreeView t = set_view<D>(sd, rec, box);
     const float l = lengths[lo];
@@ -260,6 +263,8 @@ struct kdt_batch_plan {
   int64_t* pbase = nullptr;  // first packet of each set, [n_sets + 1]
   unsigned long long* ctr = nullptr;
   int knn_blocks = 0, fof_blocks = 0;
+  int64_t n_packets = 0, min_points = 0;  // min_points: of the smallest set
+  int max_levels = 0;
   hipStream_t cap = nullptr;
   hipGraphExec_t exec = nullptr;
   hipGraph_t graph = nullptr;
@@ -301,18 +306,20 @@ static kdt_status forest_queries(kdt_batch_plan* bp, const float* d_l, int32_t* 
       k_knn_forest_packet<D, 32><<<g, 256, smem, s>>>(bp->dev.sets, ns, bp->pbase, bp->out.rec, bp->out.box, k, bp->leaf, d_idx, d_d2, bp->ctr);
     else
       k_knn_forest_packet<D, 64><<<g, 256, smem, s>>>(bp->dev.sets, ns, bp->pbase, bp->out.rec, bp->out.box, k, bp->leaf, d_idx, d_d2, bp->ctr);
-  } else if (k <= 8)
-    k_knn_forest<D, 8><<<bp->knn_blocks, kBQ, 0, s>>>(bp->dev.sets, ns, bp->out.rec, bp->out.box,
-                                                      tot, k, d_idx, d_d2, bp->ctr);
-  else if (k <= 16)
-    k_knn_forest<D, 16><<<bp->knn_blocks, kBQ, 0, s>>>(bp->dev.sets, ns, bp->out.rec, bp->out.box,
-                                                       tot, k, d_idx, d_d2, bp->ctr);
-  else if (k <= 32)
-    k_knn_forest<D, 32><<<bp->knn_blocks, kBQ, 0, s>>>(bp->dev.sets, ns, bp->out.rec, bp->out.box,
-                                                       tot, k, d_idx, d_d2, bp->ctr);
-  else
-    k_knn_forest<D, 64><<<bp->knn_blocks, kBQ, 0, s>>>(bp->dev.sets, ns, bp->out.rec, bp->out.box,
-                                                       tot, k, d_idx, d_d2, bp->ctr);
+  } else {
+    const unsigned g = (unsigned)((bp->n_packets + kBQ / 64 - 1) / (kBQ / 64));
+    const size_t smem = sizeof(uint32_t) * (size_t)(bp->max_levels + 1) * kBQ;
+#define KDT_FOREST(KC)                                                                      \
+  k_knn_forest<D, KC><<<g, kBQ, smem, s>>>(bp->dev.sets, ns, bp->pbase, bp->out.rec, bp->out.box, \
+                                           k, d_idx, d_d2)
+    switch (lane_list(k, bp->min_points)) {
+      case 8: KDT_FOREST(8); break;
+      case 16: KDT_FOREST(16); break;
+      case 32: KDT_FOREST(32); break;
+      default: KDT_FOREST(64);
+    }
+#undef KDT_FOREST
+  }
   const unsigned g = (unsigned)((tot + 255) / 256);
   k_iota_i32<<<g, 256, 0, s>>>(bp->parent, tot);
   const unsigned gn = (unsigned)((p.n_nodes + 255) / 256);
@@ -361,12 +368,6 @@ static void size_grids(kdt_batch_plan* bp) {
     else if (bp->k <= 32) kf = reinterpret_cast<const void*>(&k_knn_forest_packet<D, 32>);
     else kf = reinterpret_cast<const void*>(&k_knn_forest_packet<D, 64>);
     bp->knn_blocks = occupancy_blocks<D, 0>(kf, knn_smem, 256);
-  } else {
-    if (bp->k <= 8) kf = reinterpret_cast<const void*>(&k_knn_forest<D, 8>);
-    else if (bp->k <= 16) kf = reinterpret_cast<const void*>(&k_knn_forest<D, 16>);
-    else if (bp->k <= 32) kf = reinterpret_cast<const void*>(&k_knn_forest<D, 32>);
-    else kf = reinterpret_cast<const void*>(&k_knn_forest<D, 64>);
-    bp->knn_blocks = occupancy_blocks<D, 0>(kf, 0, kBQ);
   }
   if (bp->leaf <= 64)
     bp->fof_blocks = occupancy_blocks<D, 0>(reinterpret_cast<const void*>(&k_fof_forest_packet<D>), smem, 256);
@@ -431,11 +432,6 @@ extern "C" kdt_status kdt_batch_plan_create(const int64_t* h_offsets, int32_t n_
   bp->k = k;
   bp->leaf = leaf;
   bp->leaves = leaves;
-  // traversal 0 picks the measured default: wave packets (for the batch's
-  // all-points kNN they beat one query per lane: the whole 256-set clustered
-  // pipeline at k = 8 takes 57.1 ms with them, 65.4 ms without)
-  const int trav = qopts ? qopts->traversal : 0;
-  bp->knn_packets = leaf <= 64 && trav != 1;
   bp->offsets.assign(h_offsets, h_offsets + n_sets + 1);
   std::string err;
   if (!make_plan(h_offsets, n_sets, d, leaves.data(), bp->plan, err)) {
@@ -443,6 +439,16 @@ extern "C" kdt_status kdt_batch_plan_create(const int64_t* h_offsets, int32_t n_
     kdt_set_error("kdt_batch_plan_create: %s", err.c_str());
     return KDT_EINVAL;
   }
+  bp->min_points = bp->plan.sets[0].n;
+  for (const SetDesc& sd : bp->plan.sets) {
+    bp->min_points = std::min(bp->min_points, sd.n);
+    bp->max_levels = std::max(bp->max_levels, (int)sd.levels);
+  }
+  // traversal 0 picks the measured default: one query per lane up to 4 dimensions
+  // (the pipeline for 128 clustered sets, 7.0 million points, k = 8, leaves of 16 /
+  // 32 / 64 points: 7.5 / 6.8 / 7.0 ms, with wave packets 9.7 / 8.1 / 7.8)
+  const int trav = qopts ? qopts->traversal : 0;
+  bp->knn_packets = leaf <= 64 && (trav == 0 ? d > 4 : trav != 1);
   kdt_status st = plan_upload(bp->plan, bp->dev, nullptr);
   if (st == KDT_OK) st = build_scratch_alloc(bp->plan, bp->dev, bp->w, kPlainAlloc);
   const int64_t tot = bp->plan.total;
@@ -465,6 +471,7 @@ extern "C" kdt_status kdt_batch_plan_create(const int64_t* h_offsets, int32_t n_
   if (st == KDT_OK) {
     std::vector<int64_t> pb(n_sets + 1, 0);
     for (int i = 0; i < n_sets; ++i) pb[i + 1] = pb[i] + (h_offsets[i + 1] - h_offsets[i] + 63) / 64;
+    bp->n_packets = pb[n_sets];
     if (hipMalloc((void**)&bp->pbase, sizeof(int64_t) * (n_sets + 1)) != hipSuccess ||
         hipMemcpy(bp->pbase, pb.data(), sizeof(int64_t) * (n_sets + 1), hipMemcpyHostToDevice) !=
             hipSuccess) {

@@ -621,6 +621,15 @@ inline int lane_list(int k, int64_t n) {
   return k <= 8 ? 8 : k <= 16 ? 16 : k <= 32 && n >= kListBatch ? 32 : 64;
 }
 
+// Whether kNN takes one traversal per lane by default, whatever the tuning table
+// says of the shape: in up to 4 dimensions, where the largest leaf (`most`
+// points) is small or the list long.  All points as queries, us per lane / per
+// wave: 65536 uniform points, leaves of 32, k = 8 111 / 130, of 64 139 / 116,
+// k = 32 186 / 272 and 220 / 247; 1000 points, leaves of 32, 66 / 90
+// (k = 8); 2^20 clustered points, leaves of 32, k = 16 810 / 1051, of 64
+// 1019 / 948.
+inline bool lane_default(int d, int k, int most) { return d <= 4 && (most <= 32 || k > 16); }
+
 // Offers the cnt points from b on, a lane's leaf, to its list; most: no leaf
 // of the tree is larger (wave-uniform).  Without kMerge, in two passes per 32
 // points: the first computes every distance and marks the points that can

@@ -363,7 +363,11 @@ static kdt_status knn_impl(const kdt_tree* t, const float* d_q, int64_t nq, int 
                            float* d_d2, int mode, bool sort_q, int traversal,
                            const int32_t* given, hipStream_t stream, void* ws = nullptr,
                            size_t ws_bytes = 0) {
-  if (traversal == 0) traversal = tuned(D, t->n, k).qpw == 64 ? 2 : 1;  // the tuning table
+  if (traversal == 0) {
+    const int most = (int)((t->n + (int64_t(1) << t->levels) - 1) >> t->levels);
+    // else the tuning table's choice
+    traversal = lane_default(D, k, most) || tuned(D, t->n, k).qpw != 64 ? 1 : 2;
+  }
   if (t->leaf > 64) traversal = 1;  // the wave kernel marks at most 64 points per leaf
   if (t->nodes) traversal = 1;      // stored trees: one traversal per lane
   int32_t* order = nullptr;
