@@ -34,8 +34,26 @@
 
 namespace kdt {
 
-constexpr int kChunk = 16384;  // rows per workgroup in the global-level passes
+// Rows per workgroup in the global-level passes: a 1024th of all points, so that
+// every pass has four workgroups per CU where the points suffice, between kChunkMin
+// (below, the per-chunk work outweighs its rows) and kChunkMax.  Nodes of up
+// to kChunkSole points are one chunk whatever the rest, which spares their select launches.  Builds
+// with 16384 rows throughout and so (3-D, leaves of 24): 65536 points 583 and
+// 417 us, 2^18 791 and 512, 2^20 1036 and 697, 2^22 1640 and 1334, 2^24 equal.
+constexpr int kChunkMax = 16384;
+constexpr int kChunkMin = 2048;
+constexpr int kChunkSole = 4096;
 constexpr int kBuildBlock = 256;
+// Waves of a subtree workgroup.  With a wave per node, its time is the chain of LDS
+// reads of the waves that have the most to do; where there are few subtrees to fill the
+// chip, 16 waves share the lower levels (builds of 1000 points 123 and 83 us, 4096
+// points 253 and 166, 65536 points 415 and 327, 2^18 514 and 424).  Many
+// subtrees fill the chip with 4 waves each (2^22 points: 1332, with 16 1621 us),
+// and in 8 dimensions, whose subtrees are shallower, they are no slower
+// (300000 points: 553 and 573).
+constexpr int kSubWaves = 4;
+constexpr int kSubWide = 16;
+constexpr unsigned kSubWideMost = 512;  // subtrees of such a launch
 
 int levels_for(int64_t n, int leaf) {
   int L = 0;
@@ -49,8 +67,8 @@ int levels_for(int64_t n, int leaf) {
 int lds_capacity(int d) { return 32768 / (4 * d + 4); }
 
 // LDS of a subtree workgroup whose largest node holds `cap` points.
-static size_t lds_bytes(int d, int cap) {
-  return (size_t)cap * 4 * d + 4 * 256 * 4 + (size_t)cap * 2 * 2;
+static size_t lds_bytes(int d, int cap, int waves) {
+  return (size_t)cap * 4 * d + (size_t)waves * 256 * 4 + (size_t)cap * 2 * 2;
 }
 
 bool make_plan(const int64_t* offsets, int n_sets, int d, const int* leaves, Plan& p,
@@ -83,8 +101,10 @@ bool make_plan(const int64_t* offsets, int n_sets, int d, const int* leaves, Pla
   p.segs.resize(p.n_glevels);
   p.multi_chunk.assign(p.n_glevels, 0);
   p.chunks.resize(p.n_glevels);
-  auto add_chunks = [](std::vector<ChunkEntry>& out, int64_t b, int64_t e, int32_t seg) {
-    int64_t nch = std::max<int64_t>(1, (e - b + kChunk - 1) / kChunk);
+  const int64_t chunk =
+      std::min<int64_t>(kChunkMax, std::max<int64_t>(kChunkMin, p.total / 1024));
+  auto add_chunks = [chunk](std::vector<ChunkEntry>& out, int64_t b, int64_t e, int32_t seg) {
+    int64_t nch = e - b <= kChunkSole ? 1 : std::max<int64_t>(1, (e - b + chunk - 1) / chunk);
     for (int64_t c = 0; c < nch; ++c) {
       ChunkEntry ce;
       ce.b = b + (e - b) * c / nch;
@@ -675,8 +695,8 @@ __global__ __launch_bounds__(kBuildBlock) void k_scatter(const ChunkEntry* __res
 
 // Finishes every level below a node inside one workgroup's LDS and writes the
 // final tree-ordered records.
-template <int D>
-__global__ __launch_bounds__(kBuildBlock) void k_lds_subtree(
+template <int D, int W>
+__global__ __launch_bounds__(64 * W) void k_lds_subtree(
     const SubEntry* __restrict__ subs, const SetDesc* __restrict__ sets,
     const float* __restrict__ x0, const int32_t* __restrict__ p0, const float* __restrict__ x1,
     const int32_t* __restrict__ p1, int64_t tot, int cap, float* __restrict__ box,
@@ -687,7 +707,7 @@ __global__ __launch_bounds__(kBuildBlock) void k_lds_subtree(
   constexpr int S = rec_stride(D);
   float* lx = reinterpret_cast<float*>(smem);
   uint32_t* hist = reinterpret_cast<uint32_t*>(lx + (size_t)D * cap);
-  uint16_t* lpa = reinterpret_cast<uint16_t*>(hist + 4 * 256);
+  uint16_t* lpa = reinterpret_cast<uint16_t*>(hist + W * 256);
   uint16_t* lpb = lpa + cap;
 
   const SubEntry se = subs[blockIdx.x];
@@ -696,7 +716,7 @@ __global__ __launch_bounds__(kBuildBlock) void k_lds_subtree(
   const int32_t* pin = (sd.glevels & 1) ? p1 : p0;
   const int64_t g0 = sd.off + node_begin(sd.n, se.level, se.j);
   const int m = (int)(sd.off + node_begin(sd.n, se.level, se.j + 1) - g0);
-  for (int i = threadIdx.x; i < m; i += kBuildBlock) {
+  for (int i = threadIdx.x; i < m; i += 64 * W) {
 #pragma unroll
     for (int a = 0; a < D; ++a) lx[a * cap + i] = xin[a * tot + g0 + i];
     lpa[i] = (uint16_t)i;
@@ -709,7 +729,7 @@ __global__ __launch_bounds__(kBuildBlock) void k_lds_subtree(
   for (int lev = se.level; lev <= sd.levels; ++lev) {
     const int depth = lev - se.level;
     const int64_t nn = int64_t(1) << depth;
-    for (int64_t kk = wave; kk < nn; kk += 4) {
+    for (int64_t kk = wave; kk < nn; kk += W) {
       const int64_t j = (se.j << depth) + kk;
       const int lb = (int)(sd.off + node_begin(sd.n, lev, j) - g0);
       const int le = (int)(sd.off + node_begin(sd.n, lev, j + 1) - g0);
@@ -862,7 +882,7 @@ __global__ __launch_bounds__(kBuildBlock) void k_lds_subtree(
       nxt = t;
     }
   }
-  for (int i = threadIdx.x; i < m; i += kBuildBlock) {
+  for (int i = threadIdx.x; i < m; i += 64 * W) {
     const int s = cur[i];
     const int64_t row = g0 + i;
     float r[S];
@@ -970,18 +990,28 @@ static kdt_status run_build(const Plan& p, const PlanDev& pd, const float* d_pts
                                                   w.x[src], w.p[src], w.x[dst], w.p[dst], tot,
                                                   w.cbox, w.bad);
   }
-  const size_t smem = lds_bytes(D, p.sub_max);
-  k_lds_subtree<D><<<(unsigned)p.subs.size(), kBuildBlock, smem, stream>>>(
-      pd.subs, pd.sets, w.x[0], w.p[0], w.x[1], w.p[1], tot, p.sub_max, o.box, o.axis, o.split,
-      o.rec, o.perm);
+  const unsigned subs = (unsigned)p.subs.size();
+#define KDT_SUBTREE(W)                                                                         \
+  k_lds_subtree<D, W><<<subs, 64 * W, lds_bytes(D, p.sub_max, W), stream>>>(                   \
+      pd.subs, pd.sets, w.x[0], w.p[0], w.x[1], w.p[1], tot, p.sub_max, o.box, o.axis, o.split, \
+      o.rec, o.perm)
+  if (D <= 4 && subs <= kSubWideMost)
+    KDT_SUBTREE(kSubWide);
+  else
+    KDT_SUBTREE(kSubWaves);
+#undef KDT_SUBTREE
   KDT_HIP(hipGetLastError());
   return KDT_OK;
 }
 
 template <int D>
 static void set_smem_attr(int cap) {
-  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_lds_subtree<D>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes(D, cap));
+  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_lds_subtree<D, kSubWaves>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)lds_bytes(D, cap, kSubWaves));
+  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_lds_subtree<D, kSubWide>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)lds_bytes(D, cap, kSubWide));
 }
 
 hipError_t pool_alloc(void** ptr, size_t bytes, hipStream_t stream) {
