@@ -53,6 +53,29 @@ constexpr int kPBlock = 256;
 constexpr int kT = 16;                      // tile edge in cells
 constexpr int kTileCells = kT * kT * kT;    // float64 LDS tile: 32 KiB
 constexpr int64_t kChunk = 4096;            // particles per deposit work item
+constexpr int64_t kChunkMin = 128;          // of small deposits (chunk_of)
+
+// Lanes that share a particle's support in the SPH passes.  One lane each fills the
+// chip from about 2^20 particles on (2^22 on 160^3: forward and adjoint 1.18 and 0.56 ms;
+// with 4 lanes 1.19 and 0.58); below, a lane's support is a chain of hundreds of cells
+// with few waves to hide it (200003 on 60^3: 499 and 95 us, with 4 lanes 457 and
+// 73; 20000 on 28^3: 3790 and 952, with 4 lanes 2771 and 239, with 8 2480 and 152).
+inline int group_of(int64_t n) { return n >= (1 << 20) ? 1 : n >= (1 << 16) ? 4 : 8; }
+// Calls f with the group size of n particles as a compile-time constant.
+template <typename F>
+void by_group(int64_t n, F&& f) {
+  switch (group_of(n)) {
+    case 1: f(std::integral_constant<int, 1>()); break;
+    case 4: f(std::integral_constant<int, 4>()); break;
+    default: f(std::integral_constant<int, 8>());
+  }
+}
+// Particles per work item of a deposit of `total` list entries: about 1024 items.
+// A mesh of few tiles otherwise leaves most CUs idle (20000 particles on
+// 28^3, 8 tiles: forward 2430 us with items of 4096, 803 so).
+inline int64_t chunk_of(int64_t total) {
+  return std::min(kChunk, std::max(kChunkMin, total / 1024));
+}
 
 // Scratch slots the deposit keeps on its stream between calls.
 enum : int {
@@ -81,25 +104,30 @@ struct GridDev {
 // NGP, CIC and TSC spread a particle over 1, 2 and 3 cells per axis.
 enum : int { kSph = 0, kNgp = 1, kCic = 2, kTsc = 3 };
 
+// The M4 profile for q in [0, 2).
 __device__ __forceinline__ float m4_w(float q) {
-  if (q < 1.0f) {
-    float q2 = q * q;
-    return 1.0f - 1.5f * q2 + 0.75f * q2 * q;
-  }
-  if (q < 2.0f) {
-    float u = 2.0f - q;
-    return 0.25f * u * u * u;
-  }
-  return 0.0f;
+  const float u = 2.0f - q;
+  const float inner = fmaf(q * q, fmaf(0.75f, q, -1.5f), 1.0f);
+  return q < 1.0f ? inner : 0.25f * u * u * u;
 }
 
-__device__ __forceinline__ float m4_dw(float q) {
-  if (q < 1.0f) return -3.0f * q + 2.25f * q * q;
-  if (q < 2.0f) {
-    float u = 2.0f - q;
-    return -0.75f * u * u;
-  }
-  return 0.0f;
+// w'(q) / r for q = r inv2h in [0, 2), finite at r = 0: inv_r is 1 / r to an ulp or
+// two (any value below q = 1), and the quotient takes one Newton step to half an
+// ulp.  Over r and not over q, whose own rounding would count once more.
+__device__ __forceinline__ float m4_dw_over_r(float q, float r, float inv_r, float inv2h) {
+  const float u = 2.0f - q;
+  const float t = -0.75f * u * u, o = t * inv_r;
+  return q < 1.0f ? fmaf(2.25f, q, -3.0f) * inv2h : fmaf(fmaf(-o, r, t), inv_r, o);
+}
+
+// sqrt(v) for v >= 0 to about half an ulp: the hardware's reciprocal root `inv` and
+// one Newton step.  (v below the smallest normal float32 gives 0, and inv is +inf
+// at 0.)
+__device__ __forceinline__ float root(float v, float& inv) {
+  inv = __builtin_amdgcn_rsqf(v);
+  const float r = v * inv;
+  const float e = fmaf(-r, r, v);
+  return v >= 1.17549435e-38f ? fmaf(e, 0.5f * inv, r) : 0.0f;
 }
 
 // One image of a particle: its position, H, the cell offset of the image
@@ -241,7 +269,7 @@ __device__ __forceinline__ void for_images(const GridDev& g, const float x[3], f
 
 // Visits every cell of the box [b0, b1] (a part of the particle's support
 // box) whose centre lies within the support, with (flat index, ix, iy, iz, q,
-// dx, dy, dz, r).  The same float operations for every cell, whichever part
+// r, 1 / r, dz), and the end of every row of cells with row(dx, dy).  The same float operations for every cell, whichever part
 // of the support box is visited, so a cell's weight does not depend on it.
 //
 // Rows are clipped to the support sphere before the exact test: a z-row is
@@ -249,48 +277,76 @@ __device__ __forceinline__ void for_images(const GridDev& g, const float x[3], f
 // sqrt(H^2 (1 + 2e-4) - dx^2 - dy^2) + 1e-3 cell, a margin far above the
 // float rounding of q, so every cell with q < 2 is still visited (and the
 // test q < 2 decides, as before); rows and planes farther than H are skipped.
-template <typename F>
+//
+// G lanes share the rows: lane `sub` of the group takes every G-th.
+template <int G, typename F, typename R>
 __device__ __forceinline__ void for_cells_in(const GridDev& g, const Particle& p, const int b0[3],
-                                             const int b1[3], F&& f) {
+                                             const int b1[3], int sub, F&& f, R&& row) {
   const float inv2h = 2.0f / p.H;
   const float H2 = p.H * p.H * 1.0002f;
   const float inv = 1.0f / g.cell;
-  for (int ix = b0[0]; ix <= b1[0]; ++ix) {
-    const float dx = p.x[0] - (g.lo[0] + ((float)(ix + p.off[0]) + 0.5f) * g.cell);
-    if (dx * dx > H2) continue;
-    for (int iy = b0[1]; iy <= b1[1]; ++iy) {
-      const float dy = p.x[1] - (g.lo[1] + ((float)(iy + p.off[1]) + 0.5f) * g.cell);
-      const float dxy = dx * dx + dy * dy;
-      if (dxy > H2) continue;
-      const float zr = sqrtf(H2 - dxy) + 1e-3f * g.cell;
-      const int z0 = max(b0[2], (int)ceilf((p.x[2] - zr - g.lo[2]) * inv - 0.5f) - p.off[2]);
-      const int z1 = min(b1[2], (int)floorf((p.x[2] + zr - g.lo[2]) * inv - 0.5f) - p.off[2]);
-      const int64_t rowb = ((int64_t)ix * g.n[1] + iy) * g.n[2];
-      for (int iz = z0; iz <= z1; ++iz) {
-        const float dz = p.x[2] - (g.lo[2] + ((float)(iz + p.off[2]) + 0.5f) * g.cell);
-        const float r2 = dxy + dz * dz;
-        const float r = sqrtf(r2);
-        const float q = r * inv2h;
-        if (q < 2.0f) f(rowb + iz, ix, iy, iz, q, dx, dy, dz, r);
+  // the cells of row (ix, iy), whose centres are dx and dy away
+  const auto cells = [&](int ix, int iy, float dx, float dy, float dxy) {
+    const float zr = __builtin_amdgcn_sqrtf(H2 - dxy) + 1e-3f * g.cell;
+    const int z0 = max(b0[2], (int)ceilf((p.x[2] - zr - g.lo[2]) * inv - 0.5f) - p.off[2]);
+    const int z1 = min(b1[2], (int)floorf((p.x[2] + zr - g.lo[2]) * inv - 0.5f) - p.off[2]);
+    const int64_t rowb = ((int64_t)ix * g.n[1] + iy) * g.n[2];
+    for (int iz = z0; iz <= z1; ++iz) {
+      const float dz = p.x[2] - (g.lo[2] + ((float)(iz + p.off[2]) + 0.5f) * g.cell);
+      float inv_r;
+      const float r = root(dxy + dz * dz, inv_r), q = r * inv2h;
+      if (q < 2.0f) f(rowb + iz, ix, iy, iz, q, r, inv_r, dz);
+    }
+    row(dx, dy);
+  };
+  const auto from_x = [&](int ix) {
+    return p.x[0] - (g.lo[0] + ((float)(ix + p.off[0]) + 0.5f) * g.cell);
+  };
+  const auto from_y = [&](int iy) {
+    return p.x[1] - (g.lo[1] + ((float)(iy + p.off[1]) + 0.5f) * g.cell);
+  };
+  if constexpr (G == 1) {
+    for (int ix = b0[0]; ix <= b1[0]; ++ix) {
+      const float dx = from_x(ix);
+      if (dx * dx > H2) continue;
+      for (int iy = b0[1]; iy <= b1[1]; ++iy) {
+        const float dy = from_y(iy), dxy = dx * dx + dy * dy;
+        if (dxy <= H2) cells(ix, iy, dx, dy, dxy);
       }
+    }
+  } else {
+    const int ny = b1[1] - b0[1] + 1;
+    if (ny <= 0) return;
+    for (int ix = b0[0], iy = b0[1] + sub;; iy += G) {
+      while (iy > b1[1]) iy -= ny, ++ix;
+      if (ix > b1[0]) break;
+      const float dx = from_x(ix), dy = from_y(iy), dxy = dx * dx + dy * dy;
+      if (dxy <= H2) cells(ix, iy, dx, dy, dxy);
     }
   }
 }
 
-template <typename F>
-__device__ __forceinline__ void for_cells(const GridDev& g, const Particle& p, F&& f) {
-  for_cells_in(g, p, p.c0, p.c1, f);
+// Sum over the G lanes of a group (every lane of it active).
+template <int G>
+__device__ __forceinline__ double group_sum(double v) {
+#pragma unroll
+  for (int o = 1; o < G; o *= 2) v += __shfl_xor(v, o);
+  return v;
 }
 
 // Visits the cells of [b0, b1] that an image reaches with (flat index, ix,
 // iy, iz, weight): the M4 profile w(q) for the adaptive kernel, the product
 // of the per-axis stencil weights for the fixed clouds.
-template <int SCH, typename F>
+template <int SCH, int G, typename F>
 __device__ __forceinline__ void for_weights(const GridDev& g, const Particle& p, const Images& im,
-                                            const int b0[3], const int b1[3], F&& f) {
+                                            const int b0[3], const int b1[3], int sub, F&& f) {
   if constexpr (SCH == kSph) {
-    for_cells_in(g, p, b0, b1, [&](int64_t c, int ix, int iy, int iz, float q, float, float,
-                                   float, float) { f(c, ix, iy, iz, m4_w(q)); });
+    for_cells_in<G>(
+        g, p, b0, b1, sub,
+        [&](int64_t c, int ix, int iy, int iz, float q, float, float, float) {
+          f(c, ix, iy, iz, m4_w(q));
+        },
+        [](float, float) {});
   } else {
     for (int ix = b0[0]; ix <= b1[0]; ++ix) {
       const float wx = im.cw[0][ix + p.off[0] - im.lo_c[0]];
@@ -367,7 +423,7 @@ __device__ __forceinline__ bool tile_range(const Particle& p, int t0[3], int t1[
 // particle outside the box or with an invalid h, or for a tree whose
 // deferred finiteness check failed (tree_bad).  The gather's scattered
 // reads, if any, overlap the support sums.
-template <int SCH, int XS>
+template <int SCH, int XS, int G>
 __global__ __launch_bounds__(kPBlock) void k_p2m_prep(GridDev g, TileGrid tg,
                                                       const float* __restrict__ xin,
                                                       const float* __restrict__ min_,
@@ -392,8 +448,31 @@ __global__ __launch_bounds__(kPBlock) void k_p2m_prep(GridDev g, TileGrid tg,
     if (!ok) atomicOr(bad, 1);
   }
   // S in float64: a support of 10^5 cells (H near half the mesh) would
-  // drift by 1e-5 in float32
+  // drift by 1e-5 in float32.  The wave's particles are taken 64 / G at a time, G
+  // lanes each (group_of).
+  const int lane = lane_id();
   double S = 0.0;
+#pragma unroll 1
+  for (int b = 0; b < G; ++b) {
+    const int src = b * (64 / G) + lane / G;
+    float gx[3], gh = h;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) gx[a] = G > 1 ? __shfl(x[a], src) : x[a];
+    if (G > 1) gh = __shfl(h, src);
+    const bool gok = G > 1 ? __shfl((int)ok, src) != 0 : ok;
+    const Images im = images_of<SCH>(g, gx, fmaxf(gh, g.cell));
+    double part = 0.0;
+    for (int img = 0; gok && img < 8; ++img) {
+      if ((img & ~im.mask) != 0) continue;
+      Particle p;
+      make_image(g, gx, gh, 0.0f, true, im, img, p);
+      for_weights<SCH, G>(g, p, im, p.c0, p.c1, lane % G,
+                          [&](int64_t, int, int, int, float w) { part += (double)w; });
+    }
+    part = group_sum<G>(part);
+    const double mine = G > 1 ? __shfl(part, (lane - b * (64 / G)) * G & 63) : part;
+    if (lane / (64 / G) == b) S = mine;
+  }
   const Images im = images_of<SCH>(g, x, fmaxf(h, g.cell));
   // every lane walks the same image numbers (8 at most), so the tile
   // aggregation below runs with the whole wave
@@ -403,12 +482,7 @@ __global__ __launch_bounds__(kPBlock) void k_p2m_prep(GridDev g, TileGrid tg,
     Particle p;
     make_image(g, x, h, m, ok && mine, im, img, p);
     int t0[3] = {0, 0, 0}, t1[3] = {-1, -1, -1};
-    bool has = false;
-    if (mine) {
-      for_weights<SCH>(g, p, im, p.c0, p.c1,
-                       [&](int64_t, int, int, int, float w) { S += (double)w; });
-      has = tile_range(p, t0, t1);
-    }
+    const bool has = mine && tile_range(p, t0, t1);
     for_tiles_aggregated(tg, t0, t1, has, [&](int tile, uint64_t same, int leader, bool) {
       if (lane_id() == leader) atomicAdd(tcount + tile, (uint32_t)__popcll(same));
     });
@@ -483,7 +557,7 @@ struct DepositChunk {
 };
 
 // Step 4: one workgroup per chunk of one tile's entry list.
-template <int SCH>
+template <int SCH, int G>
 __global__ __launch_bounds__(kPBlock) void k_p2m_tile(GridDev g, TileGrid tg,
                                                       const float4* __restrict__ P, int64_t n,
                                                       const float* __restrict__ fbuf,
@@ -500,7 +574,14 @@ __global__ __launch_bounds__(kPBlock) void k_p2m_tile(GridDev g, TileGrid tg,
                      min(lo[2] + kT, g.n[2]) - 1};
   for (int c = threadIdx.x; c < kTileCells; c += kPBlock) tile[c] = 0.0;
   __syncthreads();
-  for (int64_t e = ck.begin + threadIdx.x; e < ck.end; e += kPBlock) {
+  // SPH: G lanes share an entry (group_of); the fixed clouds: a lane takes a run of
+  // entries, so that the lanes of a wave are spread over the list and rarely
+  // add to one cell at once (TSC of 2^22 particles on 160^3: 990 and 859 us).
+  const int64_t cnt = ck.end - ck.begin;
+  const int64_t per = SCH == kSph ? 1 : (cnt + kPBlock - 1) / kPBlock;
+  const int64_t first = SCH == kSph ? ck.begin + threadIdx.x / G : ck.begin + threadIdx.x * per;
+  const int64_t last = SCH == kSph ? ck.end : min(first + per, ck.end);
+  for (int64_t e = first; e < last; e += SCH == kSph ? kPBlock / G : 1) {
     const int32_t code = pairs[e];
     const int64_t t = g.periodic ? (int64_t)((uint32_t)code >> 3) : (int64_t)code;
     const int img = g.periodic ? (code & 7) : 0;
@@ -517,7 +598,8 @@ __global__ __launch_bounds__(kPBlock) void k_p2m_tile(GridDev g, TileGrid tg,
       b0[a] = max(p.c0[a], lo[a]);
       b1[a] = min(p.c1[a], hi[a]);
     }
-    for_weights<SCH>(g, p, im, b0, b1, [&](int64_t, int ix, int iy, int iz, float w) {
+    for_weights<SCH, G>(g, p, im, b0, b1, threadIdx.x % G, [&](int64_t, int ix, int iy, int iz,
+                                                               float w) {
       if (w > 0.0f)
         atomicAdd(&tile[((ix - lo[0]) * kT + (iy - lo[1])) * kT + (iz - lo[2])], (double)(f * w));
     });
@@ -559,7 +641,7 @@ __global__ __launch_bounds__(kPBlock) void k_p2m_reduce(GridDev g, TileGrid tg,
 
 // The adjoint: one lane per particle (visiting position t, row order[t] or
 // t of every per-particle array; positions with XS floats per row).
-template <int XS>
+template <int XS, int G>
 __global__ __launch_bounds__(kPBlock) void k_p2m_bwd(GridDev g, const float* __restrict__ x,
                                                      const float* __restrict__ m,
                                                      const float* __restrict__ h, int64_t n,
@@ -569,9 +651,10 @@ __global__ __launch_bounds__(kPBlock) void k_p2m_bwd(GridDev g, const float* __r
                                                      float* __restrict__ gm,
                                                      float* __restrict__ gx,
                                                      int32_t* __restrict__ bad) {
-  const int64_t t = xcd_block<kXcdRunP2M>() * kPBlock + threadIdx.x;
-  if (t == 0 && tree_bad && *tree_bad) atomicOr(bad, 1);
-  if (t >= n) return;
+  const int sub = threadIdx.x % G;
+  const int64_t t = xcd_block<kXcdRunP2M * G>() * (kPBlock / G) + threadIdx.x / G;
+  if (t == 0 && sub == 0 && tree_bad && *tree_bad) atomicOr(bad, 1);
+  if (t >= n) return;  // (whole groups)
   const int64_t i = order ? order[t] : t;
   float xi[3];
   load_position<XS>(x, i, xi);
@@ -581,32 +664,47 @@ __global__ __launch_bounds__(kPBlock) void k_p2m_bwd(GridDev g, const float* __r
     return;
   }
   const float inv2h = 2.0f / fmaxf(hi, g.cell);
+  // grad w = (2 / H) fct (x_i - x_c) with fct = w'(q) / r; along a row of cells dx
+  // and dy are the same, so the row sums fct and g fct and the two axes take
+  // their part once a row.  All sums in float64, the factor 2 / H at the end.
   double S = 0.0, A = 0.0, B[3] = {0.0, 0.0, 0.0}, C[3] = {0.0, 0.0, 0.0};
   for_images(g, xi, hi, mi, true, [&](const Particle& p, int) {
-    for_cells(g, p, [&](int64_t cidx, int, int, int, float q, float dx, float dy, float dz,
-                        float r) {
-      const float w = m4_w(q);
-      const double gc = (double)gg[cidx];
-      S += (double)w;
-      A += gc * (double)w;
-      if (r > 0.0f) {
-        const float fct = m4_dw(q) * inv2h / r;
-        const double bx = (double)(fct * dx), by = (double)(fct * dy), bz = (double)(fct * dz);
-        B[0] += bx;
-        B[1] += by;
-        B[2] += bz;
-        C[0] += gc * bx;
-        C[1] += gc * by;
-        C[2] += gc * bz;
-      }
-    });
+    double rf = 0.0, rgf = 0.0;
+    for_cells_in<G>(
+        g, p, p.c0, p.c1, sub,
+        [&](int64_t cidx, int, int, int, float q, float r, float inv_r, float dz) {
+          const double w = (double)m4_w(q), gc = (double)gg[cidx];
+          const double fct = (double)m4_dw_over_r(q, r, inv_r, inv2h);
+          const double bz = fct * (double)dz;
+          S += w;
+          A = fma(gc, w, A);
+          rf += fct;
+          rgf = fma(gc, fct, rgf);
+          B[2] += bz;
+          C[2] = fma(gc, bz, C[2]);
+        },
+        [&](float dx, float dy) {
+          B[0] = fma((double)dx, rf, B[0]);
+          B[1] = fma((double)dy, rf, B[1]);
+          C[0] = fma((double)dx, rgf, C[0]);
+          C[1] = fma((double)dy, rgf, C[1]);
+          rf = rgf = 0.0;
+        });
   });
-  const double G = A / S;
-  if (gm) gm[i] = (float)G;
-  if (gx) {
-    const double f = (double)mi / S;
+  S = group_sum<G>(S);
+  A = group_sum<G>(A);
 #pragma unroll
-    for (int a = 0; a < 3; ++a) gx[3 * i + a] = (float)(f * (C[a] - G * B[a]));
+  for (int a = 0; a < 3; ++a) {
+    B[a] = group_sum<G>(B[a]);
+    C[a] = group_sum<G>(C[a]);
+  }
+  if (sub != 0) return;
+  const double mean = A / S;
+  if (gm) gm[i] = (float)mean;
+  if (gx) {
+    const double f = (double)mi / S * (double)inv2h;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) gx[3 * i + a] = (float)(f * (C[a] - mean * B[a]));
   }
 }
 
@@ -662,14 +760,16 @@ __global__ void k_fill_u32(uint32_t* p, int64_t n, uint32_t v) {
 }  // namespace
 
 namespace {
-// Calls f with the scheme as a compile-time constant.
+// Calls f with the scheme and the group size (1 for the fixed clouds) as
+// compile-time constants.
 template <typename F>
-void by_scheme(int sch, F&& f) {
+void by_scheme(int sch, int64_t n, F&& f) {
+  using One = std::integral_constant<int, 1>;
   switch (sch) {
-    case kNgp: f(std::integral_constant<int, kNgp>()); break;
-    case kCic: f(std::integral_constant<int, kCic>()); break;
-    case kTsc: f(std::integral_constant<int, kTsc>()); break;
-    default: f(std::integral_constant<int, kSph>()); break;
+    case kNgp: f(std::integral_constant<int, kNgp>(), One()); break;
+    case kCic: f(std::integral_constant<int, kCic>(), One()); break;
+    case kTsc: f(std::integral_constant<int, kTsc>(), One()); break;
+    default: by_group(n, [&](auto g) { f(std::integral_constant<int, kSph>(), g); });
   }
 }
 }  // namespace
@@ -771,14 +871,14 @@ static kdt_status p2m_forward(int sch, const char* who, Source src, int64_t n,
   k_fill_u32<<<gt, 256, 0, stream>>>(tcount, n_tiles + 64, 0u);
   const unsigned gp = (unsigned)((n + kPBlock - 1) / kPBlock);
   if (n > 0)
-    by_scheme(sch, [&](auto c) {
-      constexpr int S = decltype(c)::value;
+    by_scheme(sch, n, [&](auto c, auto group) {
+      constexpr int S = decltype(c)::value, G = decltype(group)::value;
       if (src.xs == 4)
-        k_p2m_prep<S, 4><<<gp, kPBlock, 0, stream>>>(g, tg, src.x, src.m, src.h, n, src.order,
-                                                     src.tree_bad, P, fbuf, tcount, bad);
+        k_p2m_prep<S, 4, G><<<gp, kPBlock, 0, stream>>>(g, tg, src.x, src.m, src.h, n, src.order,
+                                                        src.tree_bad, P, fbuf, tcount, bad);
       else
-        k_p2m_prep<S, 3><<<gp, kPBlock, 0, stream>>>(g, tg, src.x, src.m, src.h, n, src.order,
-                                                     src.tree_bad, P, fbuf, tcount, bad);
+        k_p2m_prep<S, 3, G><<<gp, kPBlock, 0, stream>>>(g, tg, src.x, src.m, src.h, n, src.order,
+                                                        src.tree_bad, P, fbuf, tcount, bad);
     });
   // the per-tile counts size the lists: read them back (with the check flag)
   std::vector<uint32_t> cnt((size_t)n_tiles + 1);
@@ -804,7 +904,7 @@ static kdt_status p2m_forward(int sch, const char* who, Source src, int64_t n,
     total += cnt[t];
   }
   toff[n_tiles] = total;
-  int64_t chunk = kChunk;
+  int64_t chunk = chunk_of(total);
   auto slots_for = [&](int64_t c) {
     int64_t s = 0;
     for (int64_t t = 0; t < n_tiles; ++t) {
@@ -864,11 +964,11 @@ static kdt_status p2m_forward(int sch, const char* who, Source src, int64_t n,
     return KDT_EDEVICE;
   }
   k_fill_u32<<<gt, 256, 0, stream>>>(tcount, n_tiles, 0u);  // reused as list fill counters
-  by_scheme(sch, [&](auto c) {
-    constexpr int S = decltype(c)::value;
+  by_scheme(sch, n, [&](auto c, auto group) {
+    constexpr int S = decltype(c)::value, G = decltype(group)::value;
     if (n > 0) k_p2m_scatter<S><<<gp, kPBlock, 0, stream>>>(g, tg, P, n, d_toff, tcount, pairs);
-    k_p2m_tile<S><<<(unsigned)chunks.size(), kPBlock, 0, stream>>>(g, tg, P, n, fbuf, pairs,
-                                                                   d_chunks, d_grid, partial);
+    k_p2m_tile<S, G><<<(unsigned)chunks.size(), kPBlock, 0, stream>>>(g, tg, P, n, fbuf, pairs,
+                                                                      d_chunks, d_grid, partial);
   });
   if (!split.empty())
     k_p2m_reduce<<<dim3((unsigned)split.size(), kTileCells / kPBlock), kPBlock, 0, stream>>>(
@@ -937,13 +1037,16 @@ static kdt_status p2m_backward(const char* who, Source src, int64_t n, const kdt
     const kdt_status st = self_order(to_dev(grid), grid->n, src.x, n, stream, who, &src.order);
     if (st != KDT_OK) return st;
   }
-  const unsigned gp = (unsigned)((n + kPBlock - 1) / kPBlock);
-  if (src.xs == 4)
-    k_p2m_bwd<4><<<gp, kPBlock, 0, stream>>>(to_dev(grid), src.x, src.m, src.h, n, src.order,
-                                             src.tree_bad, d_ggrid, d_gm, d_gx, bad);
-  else
-    k_p2m_bwd<3><<<gp, kPBlock, 0, stream>>>(to_dev(grid), src.x, src.m, src.h, n, src.order,
-                                             src.tree_bad, d_ggrid, d_gm, d_gx, bad);
+  by_group(n, [&](auto group) {
+    constexpr int G = decltype(group)::value;
+    const unsigned gp = (unsigned)((n + kPBlock / G - 1) / (kPBlock / G));
+    if (src.xs == 4)
+      k_p2m_bwd<4, G><<<gp, kPBlock, 0, stream>>>(to_dev(grid), src.x, src.m, src.h, n, src.order,
+                                                  src.tree_bad, d_ggrid, d_gm, d_gx, bad);
+    else
+      k_p2m_bwd<3, G><<<gp, kPBlock, 0, stream>>>(to_dev(grid), src.x, src.m, src.h, n, src.order,
+                                                  src.tree_bad, d_ggrid, d_gm, d_gx, bad);
+  });
   if (hipGetLastError() != hipSuccess) {
     kdt_set_error("%s: kernel launch failed", who);
     return KDT_EDEVICE;
