@@ -109,7 +109,8 @@ typedef struct {
     int32_t split_budget; /* Ball counts with traversal 2.  0: default (a wave
                              still running in the launch's tail hands the big
                              subtrees of its stack on to later launches after
-                             512 node visits, then every 32).  > 0: every wave
+                             192 node visits, then every 8; 24 and 24 up to
+                             2^17 queries).  > 0: every wave
                              hands subtrees on after this many visits, in
                              every launch.  Results are identical either way;
                              it exists for tuning and for testing the

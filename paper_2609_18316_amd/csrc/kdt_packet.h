@@ -408,6 +408,7 @@ struct PacketTask {
 };
 constexpr uint32_t kNoNode = 0xFFFFFFFFu;  // a reserved task slot left empty
 constexpr uint32_t kSplitLevels = 2;       // subtrees of fewer leaves are never handed on
+constexpr uint32_t kWideBudget = 24;       // 25 entries, and 31 levels below one, fit 64 lanes
 
 // Where a traversal that exceeds its budget of node visits leaves the rest of
 // its stack (buf == nullptr: no budget).  With `done` set, it hands work on
@@ -624,9 +625,15 @@ __device__ __forceinline__ void fill_hits(const FillOut& fo, int64_t row, uint64
 // Counts of the 64 query shapes of a wave (closed balls: Algorithm 3
 // semantics; or closed boxes): a node that no lane's shape cuts is skipped, a
 // node entirely inside a lane's shape adds its size to that lane, and leaves
-// are scanned only for the lanes whose shape cuts them.  Each stack entry carries the mask of lanes that
-// still need that subtree, so a lane that has counted a whole node never
-// counts its descendants again.  Leaves must hold at most 64 points.
+// are scanned only for the lanes whose shape cuts them.  Each stack entry carries
+// the mask of lanes that must look inside that subtree, so a lane that has counted a
+// whole node never counts its descendants again.  Leaves must hold at most 64 points.
+//
+// What bounds it: chains of dependent loads, about 1.2 us a visit where a wave is alone.
+// So both children are tested when their parent is opened, their boxes in
+// one load, and only a node that some lane must look inside is ever visited
+// (one box per visit before, the stack filled with nodes yet to be tested; lists of
+// 1000003 balls of 60 points: count and fill 2.42 ms in the first passes, 1.63 now).
 //
 // Where the balls of a wave overlap a dense region, a leaf often cuts the
 // surface of only a few of them.  Then the queries that need the leaf are
@@ -641,7 +648,9 @@ __device__ __forceinline__ void fill_hits(const FillOut& fo, int64_t row, uint64
 // length of the whole launch.  So a wave that has visited `budget` nodes
 // writes its remaining stack entries (entry i sits in lane i) as tasks for a
 // later pass and returns its partial counts; the later passes add theirs, so
-// every count is the same integer sum.
+// every count is the same integer sum.  A task is walked widest first up to a budget
+// of kWideBudget (the stack is then a queue, entries head .. sp - 1), so that
+// what it hands on is in even parts.
 //
 // FILL: the same traversal writes the CSR lists (FillOut) of the lanes'
 // rows instead of only counting: a whole node is written for each lane that
@@ -666,100 +675,136 @@ __device__ __forceinline__ int64_t packet_range_count(const View& t, const Shape
   const uint32_t first_leaf = (1u << t.levels) - 1u;
   int64_t count = 0;
   uint32_t stackv = start;                         // lane i: node of entry i
-  uint32_t stk_lo = (uint32_t)start_mask;          // lane i: lane mask of entry i
+  uint32_t stk_lo = (uint32_t)start_mask;          // lane i: lanes whose shape cuts entry i
   uint32_t stk_hi = (uint32_t)(start_mask >> 32);
-  int sp = 1;
+  int sp = 0, head = 0;                            // entries head .. sp - 1
   uint32_t left = spill.buf ? spill.budget : 0xFFFFFFFFu;  // node visits before handing off
-  while (sp > 0) {
-    if (left == 0 && hand_off(spill, t.levels, group, stackv, stk_lo, stk_hi, sp, left))
-      return count;
-    --left;
-    --sp;
-    const uint32_t node = (uint32_t)__builtin_amdgcn_readlane((int)stackv, sp);
-    const uint64_t live = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)stk_hi, sp) << 32) |
-                          (uint32_t)__builtin_amdgcn_readlane((int)stk_lo, sp);
-    const bool mine = active && ((live >> lane) & 1ull);
-    Real lo[D], hi[D];
-    load_node_uniform<D>(t, node, lo, hi);
+  bool wide = spill.buf && !spill.done && spill.budget <= kWideBudget;
+  // Tests a node (points [b, e), box lo, hi) for the lanes of `live`, counts or lists
+  // it for the lanes that hold it whole; returns the lanes that must look inside.
+  const auto test = [&](int64_t b, int64_t e, const Real lo[D], const Real hi[D],
+                        uint64_t live) -> uint64_t {
     KDT_WAVE_VISIT(t, kVisitWaveNodes, 1);
-    const bool touch = mine && sh.cuts(lo, hi);
-    if (!__any(touch)) continue;
+    const bool touch = ((live >> lane) & 1ull) && sh.cuts(lo, hi);
+    const uint64_t tm = __ballot(touch);
+    if (tm == 0) return 0;
     const bool full = touch && sh.holds_box(lo, hi);
-    const int lev = node_level(node);
-    const int64_t j = (int64_t)node - ((int64_t(1) << lev) - 1);
-    const int64_t b = node_begin(t.n, lev, j), e = node_begin(t.n, lev, j + 1);
     if (full) count += e - b;
-    if (FILL) {
-      uint64_t fm = __ballot(full);
-      if (fm) {
-        const int64_t at = full ? fill_reserve(fo, row, (int)(e - b)) : 0;
-        while (fm) {
-          const int l = __ffsll((unsigned long long)fm) - 1;
-          fm &= fm - 1;
-          const int64_t dst = ((int64_t)__builtin_amdgcn_readlane((int)(at >> 32), l) << 32) |
-                              (uint32_t)__builtin_amdgcn_readlane((int)at, l);
-          for (int64_t i = b + lane; i < e; i += 64)
-            fo.out[dst + (i - b)] = input_index<D>(t, i);
-        }
+    uint64_t fm = __ballot(full);
+    const uint64_t pm = tm & ~fm;
+    if (FILL && fm != 0) {
+      const int64_t at = full ? fill_reserve(fo, row, (int)(e - b)) : 0;
+      while (fm) {
+        const int l = __ffsll((unsigned long long)fm) - 1;
+        fm &= fm - 1;
+        const int64_t dst = ((int64_t)__builtin_amdgcn_readlane((int)(at >> 32), l) << 32) |
+                            (uint32_t)__builtin_amdgcn_readlane((int)at, l);
+        for (int64_t i = b + lane; i < e; i += 64) fo.out[dst + (i - b)] = input_index<D>(t, i);
       }
     }
-    const bool part = touch && !full;
-    const uint64_t pm = __ballot(part);
-    if (pm == 0) continue;
-    if (node >= first_leaf) {
-      const int cnt = (int)(e - b);
-      leaf.open(b, cnt);
-      KDT_WAVE_VISIT(t, kVisitWavePoints, cnt);
-      const int na = __popcll(pm);
-      const int W = cnt <= 8 ? 8 : cnt <= 16 ? 16 : cnt <= 32 ? 32 : 64;
-      const int G = 64 / W;
-      const int steps = (na + G - 1) / G;
-      if (2 * steps <= cnt) {  // a packed step costs about two broadcast steps
-        const int me = lanes_below(pm);
-        if (part) sh.pack(cq + me * K);
-        wave_sync();
-        const int slot = lane / W, i = lane % W;
-        const uint64_t wmask = ~0ull >> (64 - W);
-        Real x[D];
-        leaf.point(min(i, cnt - 1), x);
-        for (int s = 0; s < steps; ++s) {
-          const int a = s * G + slot;
-          const int ac = min(a, na - 1);
-          const Shape qs = sh.unpack(cq + ac * K);
-          const bool hit = i < cnt && a < na && qs.holds(x);
-          const uint64_t hm = __ballot(hit);
-          if (i == 0 && a < na) {
-            cc[a] = __popcll((hm >> (slot * W)) & wmask);
-            if (FILL) cm[a] = (hm >> (slot * W)) & wmask;
-          }
+    return pm;
+  };
+  uint32_t node = start;
+  uint64_t pm = start_mask & __ballot(active);  // the lanes whose shape cuts node
+  Real lo[D], hi[D];
+  if (start == 0) {
+    load_node_uniform<D>(t, 0, lo, hi);
+    pm = test(0, t.n, lo, hi, pm);
+  }
+  for (;;) {
+    bool down = false;  // the next node is a child
+    if (pm != 0) {
+      if (left != 0) --left;
+      const int lev = node_level(node);
+      const int64_t j = (int64_t)node - ((int64_t(1) << lev) - 1);
+      const int64_t b = node_begin(t.n, lev, j), e = node_begin(t.n, lev, j + 1);
+      if (node < first_leaf) {
+        const uint32_t c0 = 2 * node + 1;
+        Real lo1[D], hi1[D];
+        load_node_uniform<D>(t, c0, lo, hi);
+        load_node_uniform<D>(t, c0 + 1, lo1, hi1);
+        const int64_t mid = node_begin(t.n, lev + 1, 2 * j + 1);
+        const uint64_t m0 = test(b, mid, lo, hi, pm), m1 = test(mid, e, lo1, hi1, pm);
+        if (m1 != 0 && (wide || m0 != 0)) {
+          stackv = lane == sp ? c0 + 1 : stackv;
+          stk_lo = lane == sp ? (uint32_t)m1 : stk_lo;
+          stk_hi = lane == sp ? (uint32_t)(m1 >> 32) : stk_hi;
+          ++sp;
         }
-        wave_sync();
-        if (part) count += cc[me];
-        if (FILL && part) fill_hits(fo, row, cm[me], leaf);
+        if (m0 != 0 && wide) {
+          stackv = lane == sp ? c0 : stackv;
+          stk_lo = lane == sp ? (uint32_t)m0 : stk_lo;
+          stk_hi = lane == sp ? (uint32_t)(m0 >> 32) : stk_hi;
+          ++sp;
+        }
+        down = !wide && (m0 | m1) != 0;
+        node = m0 != 0 ? c0 : c0 + 1;
+        pm = m0 != 0 ? m0 : m1;
       } else {
-        int c = 0;
-        uint64_t hits = 0;
-#pragma unroll uniform_batch<D>()
-        for (int i = 0; i < cnt; ++i) {
+        const bool part = (pm >> lane) & 1ull;
+        const int cnt = (int)(e - b);
+        leaf.open(b, cnt);
+        KDT_WAVE_VISIT(t, kVisitWavePoints, cnt);
+        const int na = __popcll(pm);
+        const int W = cnt <= 8 ? 8 : cnt <= 16 ? 16 : cnt <= 32 ? 32 : 64;
+        const int G = 64 / W;
+        const int steps = (na + G - 1) / G;
+        if (2 * steps <= cnt) {  // a packed step costs about two broadcast steps
+          const int me = lanes_below(pm);
+          if (part) sh.pack(cq + me * K);
+          wave_sync();
+          const int slot = lane / W, i = lane % W;
+          const uint64_t wmask = ~0ull >> (64 - W);
           Real x[D];
-          leaf.point(i, x);
-          const bool h = sh.holds(x);
-          c += h;
-          if (FILL) hits |= (uint64_t)h << i;
+          leaf.point(min(i, cnt - 1), x);
+          for (int s = 0; s < steps; ++s) {
+            const int a = s * G + slot;
+            const int ac = min(a, na - 1);
+            const Shape qs = sh.unpack(cq + ac * K);
+            const bool hit = i < cnt && a < na && qs.holds(x);
+            const uint64_t hm = __ballot(hit);
+            if (i == 0 && a < na) {
+              cc[a] = __popcll((hm >> (slot * W)) & wmask);
+              if (FILL) cm[a] = (hm >> (slot * W)) & wmask;
+            }
+          }
+          wave_sync();
+          if (part) count += cc[me];
+          if (FILL && part) fill_hits(fo, row, cm[me], leaf);
+        } else {
+          int c = 0;
+          uint64_t hits = 0;
+#pragma unroll uniform_batch<D>()
+          for (int i = 0; i < cnt; ++i) {
+            Real x[D];
+            leaf.point(i, x);
+            const bool h = sh.holds(x);
+            c += h;
+            if (FILL) hits |= (uint64_t)h << i;
+          }
+          if (part) count += c;
+          if (FILL && part) fill_hits(fo, row, hits, leaf);
         }
-        if (part) count += c;
-        if (FILL && part) fill_hits(fo, row, hits, leaf);
-      }
-    } else {
-      const uint32_t mlo = (uint32_t)pm, mhi = (uint32_t)(pm >> 32);
-#pragma unroll
-      for (int c = 2; c >= 1; --c) {
-        stackv = lane == sp ? 2 * node + c : stackv;
-        stk_lo = lane == sp ? mlo : stk_lo;
-        stk_hi = lane == sp ? mhi : stk_hi;
-        ++sp;
       }
     }
+    if (down) continue;
+    if (sp == head) break;
+    if (left == 0) {
+      if (wide) {
+        const int from = (lane + head) & 63;
+        stackv = (uint32_t)__shfl((int)stackv, from);
+        stk_lo = (uint32_t)__shfl((int)stk_lo, from);
+        stk_hi = (uint32_t)__shfl((int)stk_hi, from);
+        sp -= head;
+        head = 0;
+        wide = false;
+      }
+      if (hand_off(spill, t.levels, group, stackv, stk_lo, stk_hi, sp, left)) break;
+    }
+    const int at = wide ? head++ : --sp;
+    node = (uint32_t)__builtin_amdgcn_readlane((int)stackv, at);
+    pm = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)stk_hi, at) << 32) |
+         (uint32_t)__builtin_amdgcn_readlane((int)stk_lo, at);
   }
   return count;
 }

@@ -11,15 +11,24 @@ namespace kdt {
 
 constexpr int kPWaves = 4;  // waves per workgroup (independent packets)
 // Ball-count work splitting: passes; node visits per wave before it hands the
-// rest of its stack on, in the first pass (where most waves are light and a
-// hand-off costs atomics) and in the later ones; task slots per pass;
-// workgroups of a task pass.
-constexpr int kRangePasses = 8;
-constexpr uint32_t kRangeBudgetFirst = 512;
-constexpr uint32_t kRangeBudget = 32;
+// rest of its stack on, in the first pass and in the later ones; task slots per
+// pass; workgroups of a task pass.  A later pass walks its subtrees widest first
+// (kWideBudget) and so cuts the largest of them into about as many parts as its
+// budget; depth first, a hand-off's largest part was half of the subtree, and after
+// 8 passes single waves still had 500 visits of 1.2 us before them.  Launches of few
+// waves hand on at once, since most of the chip is idle (50021 queries, k = 1000 of
+// 2^23 clustered points: 15.5 ms with 8 depth-first passes of 512 and 32 visits
+// of one node; 14.3 with 256 and 16 of two nodes, 11.7 widest first, 10.2 with 24 and
+// 24); in large ones a hand-off's atomics cost more (lists of 1000003 balls:
+// first budgets of 96, 160, 192, 256 and 384 give 5.7, 4.66, 4.68, 4.79 and 5.18 ms).
+constexpr int kRangePasses = 5;
+constexpr uint32_t kRangeBudgetFirst = 192;
+constexpr uint32_t kRangeBudget = 8;
+constexpr int64_t kRangeFewWaves = 2048;  // up to here:
+constexpr uint32_t kRangeBudgetFew = 24;  // both budgets
 constexpr uint32_t kRangeTaskCap = 1u << 20;
 // Task slots per wave of the first pass, where that is fewer (launches below 2^16
-// queries): the lists' 117 MB for 2^20 slots are far more than a small call's own data.
+// queries): the lists' 67 MB for 2^20 slots are far more than a small call's own data.
 // (256 per wave cost the counts of large k: 50021 queries, k = 1000, 15.9 -> 17.6 ms.)
 constexpr int64_t kRangeTasksPerWave = 1024;
 constexpr unsigned kRangeTaskBlocks = 8192;
@@ -363,8 +372,9 @@ static kdt_status count_packet_launch(const typename Q::View& v, int leaf, Q src
   }
   k_zero_tasks<<<1, 64, 0, stream>>>(counts, kRangePasses + kDoneShards);
   // a caller's budget applies to every wave of every launch
-  const uint32_t first = split_budget ? split_budget : kRangeBudgetFirst;
-  const uint32_t later = split_budget ? split_budget : kRangeBudget;
+  const bool few = waves <= kRangeFewWaves;
+  const uint32_t first = split_budget ? split_budget : few ? kRangeBudgetFew : kRangeBudgetFirst;
+  const uint32_t later = split_budget ? split_budget : few ? kRangeBudgetFew : kRangeBudget;
   const uint32_t tail_from = split_budget                ? 0u
                              : waves > kRangeTailWaves ? (uint32_t)(waves - kRangeTailWaves)
                                                        : 0u;
