@@ -30,6 +30,13 @@ constexpr int kLBlock = 128;
 // widest rows, so fewer, larger chunks keep more rows in flight (at k = 10^4
 // the balls average about 28 000 keys: 4800 rows per chunk of 2^27 keys)
 constexpr int64_t kBigKeysPerChunk = int64_t(1) << 30;
+// Up to this many balls are counted by a wave each, above (and from d = 16 on, where a
+// ball cuts most nodes) by the wave-shared traversal of 64 balls, whose few waves leave
+// the chip idle in smaller launches: the 7 counts of 50021 balls of 2^23 clustered
+// points took 4.0 ms and take 1.05; kNN with k = 100, d = 3: 5000 queries 1.18 and
+// 0.77 ms, 50000 2.34 and 1.58, 262000 4.86 and 3.94, 2^20 (k = 128) 13.7 and 15.1; d =
+// 16, 5000: 50.6 and 54.0.
+constexpr int64_t kWaveRows = int64_t(1) << 18;
 constexpr int kBigGrowRounds = 24;  // then the radius becomes infinite
 // Largest k sorted in LDS (16384 keys, 136 KiB with the padding slots, per workgroup; gfx950 gives a
 // workgroup up to 160 KiB); larger k takes the segmented radix sort.
@@ -138,63 +145,182 @@ __global__ __launch_bounds__(kLBlock) void k_ball_count(TreeView t, const float*
   count[s] = (int32_t)c;
 }
 
-// Per query, one wave each: the keys of the points k_ball_count counted,
-// written from offsets[s] - base on.  The wave walks the tree together and
-// scans a node's points 64 at a time with coalesced loads; lanes holding a
-// point append its key at their rank in the wave's ballot.  The node tests
-// are those of k_ball_count, so exactly count[s] keys are written.
+// The search of one ball by a whole wave.  Each step takes up to 64 nodes off the top of
+// the stack, a lane each: the deepest first, so that a level leaves at most 64 nodes
+// behind it and the stack holds at most 64 per level and the 128 children of the
+// last step.  The leaves that the ball cuts are then scanned side by side, 64 / W
+// of W points at a time and kWaveLeaves loads of them in flight.
+//
+// What bounds it: the chain of dependent loads, one box and one set of leaves per step.
+// The wave took its nodes one at a time before: a ball of 1500 of 2^23 points
+// visits about 300 nodes, in about 25 steps now.  The widest balls (3e5 points around
+// a halo) set the fill's end, so a node inside the ball is read in one run with 4 loads
+// a lane in flight: fill of 50021 balls, 1.8e8 keys: 3.63 ms one node at a time, 2.61
+// side by side, 1.9 with runs (shrinking such balls first for every k costs
+// more in recounts: the call 7.74 -> 8.27 ms).
 constexpr int kFillWaves = 4;
+constexpr int kWaveLeaves = 4;
+constexpr int kWaveRun = 128;     // a node inside the ball with so many points is read in one run,
+constexpr int kWaveLoads = 4;     // so many loads per lane in flight
+constexpr int kWaveLeafCap = 32;  // points per leaf of the view that is walked
+constexpr uint32_t kWholeBit = 0x80000000u;  // a stack entry inside the ball; list: all points in
+
+inline int wave_stack_len(int levels) { return 64 * (levels + 1) + 128; }
+inline size_t wave_ball_bytes(int levels) {
+  return sizeof(uint32_t) * (size_t)(wave_stack_len(levels) + 128);
+}
+
+// With KEYS the keys of the ball's points go to keys[0 ..]; returns their number (the
+// same on every lane).  `lds` is the wave's slice of wave_ball_bytes.
+template <int D, bool KEYS, class M>
+__device__ __forceinline__ int64_t wave_ball(const TreeView& t, const float p[D], float r2,
+                                             uint32_t* lds, int leaf_cap, int ib,
+                                             uint64_t* __restrict__ keys, const M& metric) {
+  const int lane = threadIdx.x & 63;
+  uint32_t* list_b = lds;
+  uint32_t* list_n = lds + 64;
+  uint32_t* stk = lds + 128;
+  const uint32_t first_leaf = (1u << t.levels) - 1u;
+  const int W = leaf_cap <= 8 ? 8 : leaf_cap <= 16 ? 16 : leaf_cap <= 32 ? 32 : 64;
+  const int G = 64 / W, slot = lane / W, i = lane % W;
+  const uint64_t below = (1ull << lane) - 1ull;
+  int64_t pos = 0, whole_n = 0;
+  int sp = 1;
+  if (lane == 0) stk[0] = 0;
+  while (sp > 0) {
+    wave_sync();
+    const int m = min(sp, 64);
+    uint32_t node = lane < m ? stk[sp - 1 - lane] : 0u;
+    sp -= m;
+    bool whole = (node & kWholeBit) != 0;
+    node &= ~kWholeBit;
+    float lo[D], hi[D];
+    load_box<D>(t.box, node, lo, hi);
+    const bool cut = lane < m && (whole || metric.mindist(lo, hi, p) <= r2);
+    whole = whole || (cut && metric.maxdist(lo, hi, p) <= r2);
+    const bool is_leaf = node >= first_leaf;
+    const int lev = node_level(node);
+    const int64_t j = (int64_t)node - ((int64_t(1) << lev) - 1);
+    const int64_t b = node_begin(t.n, lev, j);
+    const int64_t n = node_begin(t.n, lev, j + 1) - b;
+    if (!KEYS && cut && whole) whole_n += n;
+    const bool run = KEYS && cut && whole && n >= kWaveRun;
+    const uint64_t om = __ballot(cut && !run && !is_leaf && (KEYS || !whole));
+    if ((om >> lane) & 1ull) {
+      const int at = sp + 2 * __popcll(om >> lane >> 1);
+      const uint32_t mark = whole ? kWholeBit : 0u;
+      stk[at] = (2 * node + 2) | mark;
+      stk[at + 1] = (2 * node + 1) | mark;
+    }
+    sp += 2 * __popcll(om);
+    const uint64_t lm = __ballot(cut && !run && is_leaf && (KEYS || !whole));
+    if ((lm >> lane) & 1ull) {
+      const int at = __popcll(lm & below);
+      list_b[at] = (uint32_t)b;
+      list_n[at] = (uint32_t)n | (whole ? kWholeBit : 0u);
+    }
+    const int nl = __popcll(lm);
+    wave_sync();
+    if (KEYS) {
+      uint64_t rm = __ballot(run);
+      while (rm) {
+        const int l = __ffsll((unsigned long long)rm) - 1;
+        rm &= rm - 1;
+        const int64_t rb = (uint32_t)__builtin_amdgcn_readlane((int)b, l);
+        const int rn = __builtin_amdgcn_readlane((int)n, l);
+        for (int c = lane; c < rn; c += 64 * kWaveLoads) {
+          float x[kWaveLoads][D];
+          int32_t id[kWaveLoads];
+#pragma unroll
+          for (int u = 0; u < kWaveLoads; ++u)
+            if (c + 64 * u < rn) load_rec<D>(t.rec, rb + c + 64 * u, x[u], id[u]);
+#pragma unroll
+          for (int u = 0; u < kWaveLoads; ++u)
+            if (c + 64 * u < rn)
+              keys[pos + c + 64 * u] =
+                  ((uint64_t)__float_as_uint(metric.dist(x[u], p)) << ib) | (uint32_t)id[u];
+        }
+        pos += rn;
+      }
+    }
+    for (int k = 0; k < nl; k += kWaveLeaves * G) {
+      for (int c = 0; c < leaf_cap; c += W) {
+        float x[kWaveLeaves][D];
+        int32_t id[kWaveLeaves];
+        uint32_t ln[kWaveLeaves];
+#pragma unroll
+        for (int u = 0; u < kWaveLeaves; ++u) {
+          const int at = k + u * G + slot;
+          ln[u] = at < nl ? list_n[at] : 0u;
+          id[u] = 0;
+          if ((uint32_t)(c + i) < (ln[u] & ~kWholeBit)) {
+            load_rec<D>(t.rec, (int64_t)list_b[at] + c + i, x[u], id[u]);
+          } else {
+            ln[u] = 0u;
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < kWaveLeaves; ++u) {
+          bool in = false;
+          float d2 = 0.0f;
+          if (ln[u] != 0u) {
+            d2 = metric.dist(x[u], p);
+            in = (ln[u] & kWholeBit) != 0 || d2 <= r2;
+          }
+          const uint64_t hm = __ballot(in);
+          if (KEYS && in)
+            keys[pos + __popcll(hm & below)] =
+                ((uint64_t)__float_as_uint(d2) << ib) | (uint32_t)id[u];
+          pos += __popcll(hm);
+        }
+      }
+    }
+  }
+  if (!KEYS) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) whole_n += __shfl_xor(whole_n, o);
+    pos += whole_n;
+  }
+  return pos;
+}
+
+// Per query, one wave each: the number of points of its ball, rows list[0 .. rows) or
+// all of them.
+template <int D, class M>
+__global__ __launch_bounds__(64 * kFillWaves) void k_ball_count_wave(
+    TreeView t, const float* __restrict__ q, int64_t rows, const int32_t* __restrict__ list,
+    const float* __restrict__ r2v, int32_t* __restrict__ count, int leaf_cap, int slice, M metric) {
+  extern __shared__ uint32_t ball_lds[];
+  const int wave = threadIdx.x >> 6;
+  const int64_t g = (int64_t)blockIdx.x * kFillWaves + wave;
+  if (g >= rows) return;  // uniform over the wave
+  const int64_t s = list ? list[g] : g;
+  float p[D];
+#pragma unroll
+  for (int a = 0; a < D; ++a) p[a] = q[s * D + a];
+  const int64_t c =
+      wave_ball<D, false>(t, p, r2v[s], ball_lds + wave * slice, leaf_cap, 0, nullptr, metric);
+  if ((threadIdx.x & 63) == 0) count[s] = (int32_t)c;
+}
+
+// Per query, one wave each: the keys of the points that were counted, written from
+// offsets[s] - base on.  The node and point tests are those of the counts (whole-node and
+// per-point tests decide the same points at any level), so exactly count[s] keys
+// are written.
 template <int D, class M>
 __global__ __launch_bounds__(64 * kFillWaves) void k_ball_fill(
     TreeView t, const float* __restrict__ q, int64_t s0, int64_t s1,
     const float* __restrict__ r2v, const int64_t* __restrict__ offsets, int64_t base,
-    uint64_t* __restrict__ keys, int stack_len, int ib, M metric) {
-  extern __shared__ uint32_t fill_stk[];
-  const int lane = threadIdx.x & 63;
-  uint32_t* stk = fill_stk + (threadIdx.x >> 6) * stack_len;
-  const int64_t s = s0 + (int64_t)blockIdx.x * kFillWaves + (threadIdx.x >> 6);
+    uint64_t* __restrict__ keys, int leaf_cap, int slice, int ib, M metric) {
+  extern __shared__ uint32_t ball_lds[];
+  const int wave = threadIdx.x >> 6;
+  const int64_t s = s0 + (int64_t)blockIdx.x * kFillWaves + wave;
   if (s >= s1) return;  // uniform over the wave
   float p[D];
 #pragma unroll
   for (int a = 0; a < D; ++a) p[a] = q[s * D + a];
-  const float r2 = r2v[s];
-  const uint32_t first_leaf = (1u << t.levels) - 1u;
-  const uint64_t below = (1ull << lane) - 1ull;
-  int64_t pos = offsets[s] - base;
-  // every lane writes the same entries, so each reads back its own writes
-  int sp = 0;
-  stk[sp++] = 0;
-  while (sp > 0) {
-    const uint32_t node = stk[--sp];
-    float lo[D], hi[D];
-    load_box<D>(t.box, node, lo, hi);
-    if (metric.mindist(lo, hi, p) > r2) continue;
-    const int lev = node_level(node);
-    const int64_t j = (int64_t)node - ((int64_t(1) << lev) - 1);
-    const int64_t b = node_begin(t.n, lev, j), e = node_begin(t.n, lev, j + 1);
-    const bool whole = metric.maxdist(lo, hi, p) <= r2;
-    if (whole || node >= first_leaf) {
-      for (int64_t c = b; c < e; c += 64) {
-        const int64_t i = c + lane;
-        bool in = false;
-        uint64_t key = 0;
-        if (i < e) {
-          float x[D];
-          int32_t id = 0;
-          load_rec<D>(t.rec, i, x, id);
-          const float d2 = metric.dist(x, p);
-          in = whole || d2 <= r2;
-          key = ((uint64_t)__float_as_uint(d2) << ib) | (uint32_t)id;
-        }
-        const uint64_t m = __ballot(in);
-        if (in) keys[pos + __popcll(m & below)] = key;
-        pos += __popcll(m);
-      }
-      continue;
-    }
-    stk[sp++] = 2 * node + 2;
-    stk[sp++] = 2 * node + 1;
-  }
+  wave_ball<D, true>(t, p, r2v[s], ball_lds + wave * slice, leaf_cap, ib,
+                     keys + (offsets[s] - base), metric);
 }
 
 // Rows whose ball holds fewer than k points get a larger radius, from the
@@ -607,6 +733,11 @@ static kdt_status knn_large_impl(const kdt_tree* tr, const float* d_q, int64_t n
   const int stack_len = tr->levels + 2;
   const size_t smem = sizeof(uint32_t) * (size_t)stack_len * kLBlock;
   const unsigned gl = (unsigned)((nq + kLBlock - 1) / kLBlock);
+  // The searches of one ball per wave read the tree at its nodes of at most
+  // kWaveLeafCap points.
+  int fill_cap = 0;
+  const TreeView vfill = coarse_view(v, tr->leaf, kWaveLeafCap, &fill_cap);
+  const size_t ball_bytes = wave_ball_bytes(vfill.levels);
   // Counts: the wave-shared count traversal (leaves of at most 64 points)
   // over every query first, then over the list of grown rows; else one
   // traversal per lane, skipping rows that did not grow.
@@ -617,9 +748,14 @@ static kdt_status knn_large_impl(const kdt_tree* tr, const float* d_q, int64_t n
   }
   int32_t h_again = (int32_t)nq;
   for (int round = 0; round < kBigGrowRounds; ++round) {
-    if (tr->leaf <= 64) {
-      st = var_ball_count_launch<D>(v, tr->leaf, q, r2, round == 0 ? nq : (int64_t)h_again,
-                                    round == 0 ? nullptr : list, metric, count, stream);
+    const int64_t rows = round == 0 ? nq : (int64_t)h_again;
+    if (D <= 8 && rows <= kWaveRows) {
+      k_ball_count_wave<D><<<(unsigned)((rows + kFillWaves - 1) / kFillWaves), 64 * kFillWaves,
+                             ball_bytes * kFillWaves, stream>>>(
+          vfill, q, rows, round == 0 ? nullptr : list, r2, count, fill_cap,
+          (int)(ball_bytes / sizeof(uint32_t)), metric);
+    } else if (tr->leaf <= 64) {
+      st = var_ball_count_launch<D>(v, tr->leaf, q, r2, rows, round == 0 ? nullptr : list, metric, count, stream);
       if (st != KDT_OK) return st;
     } else {
       k_ball_count<D><<<gl, kLBlock, smem, stream>>>(v, q, nq, r2, count, round > 0 ? 1 : 0,
@@ -681,12 +817,6 @@ static kdt_status knn_large_impl(const kdt_tree* tr, const float* d_q, int64_t n
   // 32 + ib bits only.
   int ib = 1;
   while (ib < 31 && (int64_t(1) << ib) < tr->n) ++ib;
-  // the fill reads the tree at its nodes of at most 64 points: a wave scans
-  // such a node in one step, and a ball of 10^4 points takes a quarter of
-  // the steps of 16-point leaves (whole-node and per-point tests decide the
-  // same points at any level, so the keys are the ones counted)
-  int fill_cap = 0;
-  const TreeView vfill = coarse_view(v, tr->leaf, 64, &fill_cap);
   void* stmp = nullptr;
   size_t stmp_bytes = 0;
   for (int64_t s0 = 0; s0 < nq;) {
@@ -696,8 +826,9 @@ static kdt_status knn_large_impl(const kdt_tree* tr, const float* d_q, int64_t n
     k_chunk_offsets<<<(unsigned)((m + 256) / 256), 256, 0, stream>>>(off, s0, m, rel, cls_ctr);
     if (total > 0) {
       k_ball_fill<D><<<(unsigned)((m + kFillWaves - 1) / kFillWaves), 64 * kFillWaves,
-                       sizeof(uint32_t) * (size_t)stack_len * kFillWaves, stream>>>(
-          vfill, q, s0, s1, r2, off, h_off[s0], keys, stack_len, ib, metric);
+                       ball_bytes * kFillWaves, stream>>>(
+          vfill, q, s0, s1, r2, off, h_off[s0], keys, fill_cap,
+          (int)(ball_bytes / sizeof(uint32_t)), ib, metric);
     }
     if (mode != 0) {  // only the k-th distance: selected, not sorted
       k_row_kth<<<(unsigned)m, 64, 0, stream>>>(keys, rel, rowof, s0, k, mode, ib, d_d2);
