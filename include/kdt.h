@@ -110,7 +110,8 @@ typedef struct {
                              still running in the launch's tail hands the big
                              subtrees of its stack on to later launches after
                              192 node visits, then every 8; 24 and 24 up to
-                             2^17 queries).  > 0: every wave
+                             2^17 queries; counts of up to 2^17 queries, d <=
+                             8, take a wave each instead).  > 0: every wave
                              hands subtrees on after this many visits, in
                              every launch.  Results are identical either way;
                              it exists for tuning and for testing the
@@ -519,7 +520,7 @@ kdt_status kdt_query_order(const kdt_tree *tree, const float *d_q, int64_t nq, i
  * with (-1, +inf) when k > n.  d_idx [nq][k] int32 (may be NULL), d_d2
  * [nq][k] float64.  opts: sort_queries and order as for kdt_knn (the order
  * may come from kdt_query_order); traversal and split_budget are ignored
- * (one traversal per lane); a period gives KDT_EUNSUPPORTED.
+ * (kNN: one traversal per lane); a period gives KDT_EUNSUPPORTED.
  *
  * kdt_range_f64: closed-ball counts (d2 <= fl64(r * r)) into d_count [nq]
  * int32, and with d_offsets [nq + 1] int64 the CSR lists as in kdt_range

@@ -36,6 +36,17 @@ constexpr unsigned kRangeTaskBlocks = 8192;
 // are left (about what the chip holds at once).
 constexpr int64_t kRangeTailWaves = 8192;
 
+// Up to this many shapes are counted by a wave each (wave_ball), above (and from d = 16
+// on, where a ball cuts most nodes) by the wave-shared traversal of 64 shapes, whose few
+// waves leave the chip idle in smaller launches.  Ball counts, shared and by wave: 1000
+// balls of 1000 points 59 and 13 us, 65536 of 65536 146 and 100, 130000 of 2^20 433 and
+// 370, 250000 433 and 585; d = 8, 100000 of 2^18 1771 and 655.
+constexpr int64_t kWaveRows = int64_t(1) << 17;
+// The balls of large k hold many points: the 7 counts of 50021 balls of 2^23 clustered
+// points took 4.0 ms and take 1.05; kNN with k = 100, 262000 queries 4.86 and 3.94 ms,
+// 2^20 (k = 128) 13.7 and 15.1; d = 16, 5000: 50.6 and 54.0.
+constexpr int64_t kWaveRowsLarge = int64_t(1) << 18;
+
 // LDS of a workgroup of the grouping: a slice per wave.
 template <int D>
 size_t fof_lds_bytes(int leaf) {
@@ -106,6 +117,7 @@ __global__ __launch_bounds__(64 * kPWaves) void k_knn_packet(TreeView t, const f
 // points, and one squared radius) or boxes (corners).
 template <int D, class V = TreeView>
 struct BallQueries {
+  static constexpr int64_t kWaveMax = kWaveRows;
   using View = V;
   using Real = typename View::Real;
   using Shape = BallShape<D, Real>;
@@ -120,6 +132,7 @@ struct BallQueries {
 
 template <int D>
 struct TorusBallQueries {
+  static constexpr int64_t kWaveMax = kWaveRows;
   using View = TreeView;
   using Shape = TorusBallShape<D>;
   const float* q;  // [nq][D], or nullptr: the tree's own points
@@ -135,6 +148,7 @@ struct TorusBallQueries {
 
 template <int D, class Metric>
 struct VarBallQueries {
+  static constexpr int64_t kWaveMax = kWaveRowsLarge;
   using View = TreeView;
   using Shape = VarBallShape<D, Metric>;
   const float* q;   // [rows][D]
@@ -151,6 +165,7 @@ struct VarBallQueries {
 
 template <int D>
 struct BoxQueries {
+  static constexpr int64_t kWaveMax = kWaveRows;
   using View = TreeView;
   using Shape = BoxShape<D>;
   const float* lo;  // [nq][D]
@@ -229,6 +244,23 @@ __global__ __launch_bounds__(64 * kPWaves) void k_count_tasks(
         t, sh, active, slice, leaf_cap, task.node, mask, task.group, spill, row, fo);
     if (!FILL && active && c != 0) atomicAdd(count + row, (int32_t)c);
   }
+}
+
+// One query shape per wave.
+template <int D, class Q>
+__global__ __launch_bounds__(64 * kPWaves) void k_count_wave(TreeView t, Q src, int64_t nq,
+                                                             const int32_t* __restrict__ order,
+                                                             int32_t* __restrict__ count,
+                                                             int leaf_cap, int slice) {
+  extern __shared__ uint32_t wave_lds[];
+  const int wave = threadIdx.x >> 6;
+  const int64_t s = (int64_t)blockIdx.x * kPWaves + wave;
+  if (s >= nq) return;  // uniform over the wave
+  typename Q::Shape sh;
+  int64_t row = 0;
+  src.load(t, nq, order, s, sh, row);
+  const int64_t c = wave_ball<D, false>(t, sh, wave_lds + wave * slice, leaf_cap);
+  if ((threadIdx.x & 63) == 0) count[row] = (int32_t)c;
 }
 
 __global__ void k_zero_tasks(uint32_t* c, int n) {
@@ -355,6 +387,21 @@ static kdt_status count_packet_launch(const typename Q::View& v, int leaf, Q src
                                       const int32_t* order, int32_t* d_count,
                                       uint32_t split_budget, hipStream_t stream,
                                       const char* who, const FillOut* fill = nullptr) {
+  if constexpr (std::is_same_v<typename Q::View, TreeView> && D <= 8) {
+    if (!fill && split_budget == 0 && nq <= Q::kWaveMax) {
+      int cap = 0;
+      const TreeView w = coarse_view(v, leaf, kWaveLeafCap, &cap);
+      const size_t slice = wave_ball_bytes(w.levels);
+      k_count_wave<D, Q><<<(unsigned)((nq + kPWaves - 1) / kPWaves), 64 * kPWaves, slice * kPWaves,
+                           stream>>>(w, src, nq, order, d_count, cap,
+                                     (int)(slice / sizeof(uint32_t)));
+      if (hipGetLastError() != hipSuccess) {
+        kdt_set_error("%s: packet kernel launch failed", who);
+        return KDT_EDEVICE;
+      }
+      return KDT_OK;
+    }
+  }
   const unsigned grid = (unsigned)((nq + 64 * kPWaves - 1) / (64 * kPWaves));
   const size_t smem = count_wave_bytes<D, Q>(leaf) * kPWaves;
   PoolBuffers buf(stream);

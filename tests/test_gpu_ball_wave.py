@@ -61,3 +61,29 @@ def test_large_k_by_launch_size(nq):
     oi, od = oracle.knn_brute(x, q[some], 65)
     np.testing.assert_array_equal(idx[some], oi)
     np.testing.assert_array_equal(d2[some], od)
+
+
+@pytest.mark.parametrize("leaf", (2, 16, 64))
+@pytest.mark.parametrize("d", (2, 3, 4, 8, 16))
+def test_counts_by_wave(d, leaf):
+    dev()
+    for n in (1, 3, 70, 3000):
+        x, q = points(n, d, n + d)
+        t = kdt.build(to_dev(x), leaf_size=leaf)
+        ot = oracle.Tree(x, leaf)
+        for r in (0.0, 0.1, 0.5, 5.0):
+            say(f"wave counts d={d} leaf={leaf} n={n} r={r}")
+            oc = ot.range(q, r)
+            np.testing.assert_array_equal(to_host(t.range(to_dev(q), r)), oc)
+            np.testing.assert_array_equal(to_host(t.range(to_dev(q), r, split_budget=7)), oc)
+            np.testing.assert_array_equal(to_host(t.range(None, r)), ot.range(x, r))
+
+
+@pytest.mark.parametrize("nq", (1 << 17, (1 << 17) + 1))
+def test_counts_by_launch_size(nq):
+    dev()
+    x, _ = points(20000, 3, 1)
+    q = np.random.Generator(np.random.PCG64(nq)).random((nq, 3)).astype(np.float32)
+    t, ot = kdt.build(to_dev(x), leaf_size=16), oracle.Tree(x, 16)
+    say(f"wave counts nq={nq}")
+    np.testing.assert_array_equal(to_host(t.range(to_dev(q), 0.03)), ot.range(q, 0.03))
