@@ -109,7 +109,7 @@ typedef struct {
     int32_t split_budget; /* Ball counts with traversal 2.  0: default (a wave
                              still running in the launch's tail hands the big
                              subtrees of its stack on to later launches after
-                             192 node visits, then every 8; 24 and 24 up to
+                             320 node visits, then every 8; 24 and 24 up to
                              2^17 queries; counts of up to 2^17 queries, d <=
                              8, take a wave each instead).  > 0: every wave
                              hands subtrees on after this many visits, in

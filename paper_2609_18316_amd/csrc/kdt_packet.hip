@@ -19,10 +19,11 @@ constexpr int kPWaves = 4;  // waves per workgroup (independent packets)
 // waves hand on at once, since most of the chip is idle (50021 queries, k = 1000 of
 // 2^23 clustered points: 15.5 ms with 8 depth-first passes of 512 and 32 visits
 // of one node; 14.3 with 256 and 16 of two nodes, 11.7 widest first, 10.2 with 24 and
-// 24); in large ones a hand-off's atomics cost more (lists of 1000003 balls:
-// first budgets of 96, 160, 192, 256 and 384 give 5.7, 4.66, 4.68, 4.79 and 5.18 ms).
+// 24); in large ones ordinary waves must not reach the budget (2^22 uniform balls,
+// r = 0.01, of 2^24 uniform points: 4.29, 3.63 and 3.56 ms with 192, 320 and 384; lists of
+// 1000003 balls of clustered points 4.68, 4.98 and 5.22).
 constexpr int kRangePasses = 5;
-constexpr uint32_t kRangeBudgetFirst = 192;
+constexpr uint32_t kRangeBudgetFirst = 320;
 constexpr uint32_t kRangeBudget = 8;
 constexpr int64_t kRangeFewWaves = 2048;  // up to here:
 constexpr uint32_t kRangeBudgetFew = 24;  // both budgets
@@ -33,8 +34,9 @@ constexpr uint32_t kRangeTaskCap = 1u << 20;
 constexpr int64_t kRangeTasksPerWave = 1024;
 constexpr unsigned kRangeTaskBlocks = 8192;
 // The first pass hands work on only once fewer than this many of its waves
-// are left (about what the chip holds at once).
-constexpr int64_t kRangeTailWaves = 8192;
+// are left (half of what the chip holds at once: with all of it ordinary waves hand on too,
+// 256 visits, 2^20 uniform balls 1.88 and 2.06 ms).
+constexpr int64_t kRangeTailWaves = 4096;
 
 // Up to this many shapes are counted by a wave each (wave_ball), above (and from d = 16
 // on, where a ball cuts most nodes) by the wave-shared traversal of 64 shapes, whose few
@@ -202,8 +204,11 @@ __device__ __forceinline__ typename Q::View::Real* count_slice(char* lds, int wa
 // First pass of the counts: one 64-query group per wave from the root; writes
 // each count (partial if the wave handed subtrees on), or with FILL the
 // lists.
+// (8 waves a SIMD: at 67 registers and 7 waves 2^22 GRF balls took 3.48 ms, now 3.30.)
 template <int D, class Q, bool FILL>
-__global__ __launch_bounds__(64 * kPWaves) void k_count_packet(typename Q::View t, Q src, int64_t nq,
+__global__ __launch_bounds__(64 * kPWaves)
+    __attribute__((amdgpu_waves_per_eu(sizeof(typename Q::View::Real) == 4 && D <= 4 ? 8 : 1))) void
+    k_count_packet(typename Q::View t, Q src, int64_t nq,
                                                                const int32_t* __restrict__ order,
                                                                int32_t* __restrict__ count,
                                                                int leaf_cap, PacketSpill spill,
