@@ -574,14 +574,15 @@ __global__ __launch_bounds__(kPBlock) void k_p2m_tile(GridDev g, TileGrid tg,
                      min(lo[2] + kT, g.n[2]) - 1};
   for (int c = threadIdx.x; c < kTileCells; c += kPBlock) tile[c] = 0.0;
   __syncthreads();
-  // SPH: G lanes share an entry (group_of); the fixed clouds: a lane takes a run of
-  // entries, so that the lanes of a wave are spread over the list and rarely
-  // add to one cell at once (TSC of 2^22 particles on 160^3: 990 and 859 us).
+  // SPH: G lanes share an entry (group_of).  TSC: a lane takes a run of entries, so that
+  // the lanes of a wave are spread over the list and rarely add to one cell at once
+  // (2^24 particles on 256^3: 3.22 and 2.93 ms); NGP and CIC add too little for that to
+  // pay for the scattered reads (1.32 and 1.76, 1.91 and 2.09 ms with runs).
   const int64_t cnt = ck.end - ck.begin;
-  const int64_t per = SCH == kSph ? 1 : (cnt + kPBlock - 1) / kPBlock;
-  const int64_t first = SCH == kSph ? ck.begin + threadIdx.x / G : ck.begin + threadIdx.x * per;
-  const int64_t last = SCH == kSph ? ck.end : min(first + per, ck.end);
-  for (int64_t e = first; e < last; e += SCH == kSph ? kPBlock / G : 1) {
+  const int64_t per = SCH != kTsc ? 1 : (cnt + kPBlock - 1) / kPBlock;
+  const int64_t first = SCH != kTsc ? ck.begin + threadIdx.x / G : ck.begin + threadIdx.x * per;
+  const int64_t last = SCH != kTsc ? ck.end : min(first + per, ck.end);
+  for (int64_t e = first; e < last; e += SCH != kTsc ? kPBlock / G : 1) {
     const int32_t code = pairs[e];
     const int64_t t = g.periodic ? (int64_t)((uint32_t)code >> 3) : (int64_t)code;
     const int img = g.periodic ? (code & 7) : 0;
