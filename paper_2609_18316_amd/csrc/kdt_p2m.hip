@@ -41,6 +41,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cfloat>
 #include <cmath>
 #include <type_traits>
 #include <vector>
@@ -91,12 +92,17 @@ constexpr int64_t kSelfOrderMin = 1 << 16;
 
 inline size_t align256(size_t b) { return (b + 255) / 256 * 256; }
 
+// The mesh in lengths times `unit`, the power of two that puts a cell's edge in [1, 2), as
+// particles are once they are checked (to_unit).  That changes no rounding, and squares
+// stay in float32's range whatever the caller's units (the hardware's roots take
+// squares below the smallest normal number, distances below 1.1e-19, for 0).
 struct GridDev {
   float lo[3];
   float cell;
   int32_t n[3];
   int32_t periodic;  // 1: the mesh box is a 3-torus of periods n[a] * cell
-  float L[3];        // the periods n[a] * cell
+  float unit;
+  float in_lo[3], in_cell, in_L[3];  // the caller's corner, cell and periods
 };
 
 // Deposit schemes: the adaptive SPH kernel (M4, Sec. 4.2) and the fixed
@@ -121,8 +127,8 @@ __device__ __forceinline__ float m4_dw_over_r(float q, float r, float inv_r, flo
 }
 
 // sqrt(v) for v >= 0 to about half an ulp: the hardware's reciprocal root `inv` and
-// one Newton step.  (v below the smallest normal float32 gives 0, and inv is +inf
-// at 0.)
+// one Newton step.  (v below the smallest normal float32 gives 0: nothing beside a
+// cell's edge; and inv is +inf at 0.)
 __device__ __forceinline__ float root(float v, float& inv) {
   inv = __builtin_amdgcn_rsqf(v);
   const float r = v * inv;
@@ -160,19 +166,25 @@ __device__ __forceinline__ void load_position(const float* __restrict__ x, int64
   }
 }
 
-// Validity of a particle: inside the mesh box; for the adaptive kernel also
+// Validity of a particle as the caller gives it: inside the mesh box; for the adaptive kernel also
 // h finite and >= 0, and on a periodic mesh H below half of every period.
 template <int SCH = kSph>
 __device__ __forceinline__ bool particle_ok(const GridDev& g, const float x[3], float h) {
   bool ok = SCH != kSph || (h >= 0.0f && isfinite(h));
-  const float H = fmaxf(h, g.cell);
+  const float H = fmaxf(h, g.in_cell);
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
-    const float top = g.lo[a] + g.L[a];
-    ok &= (x[a] >= g.lo[a]) && (x[a] < top);
-    if (SCH == kSph && g.periodic) ok &= 2.0f * H < g.L[a];
+    const float top = g.in_lo[a] + g.in_L[a];
+    ok &= (x[a] >= g.in_lo[a]) && (x[a] < top);
+    if (SCH == kSph && g.periodic) ok &= 2.0f * H < g.in_L[a];
   }
   return ok;
+}
+// A valid particle in the mesh's units (a finite h stays finite).
+__device__ __forceinline__ void to_unit(const GridDev& g, float x[3], float& h) {
+#pragma unroll
+  for (int a = 0; a < 3; ++a) x[a] *= g.unit;
+  h = fminf(h * g.unit, FLT_MAX);
 }
 
 // Per axis, the unclipped cell range [lo_c, hi_c] the particle can reach, and
@@ -443,9 +455,10 @@ __global__ __launch_bounds__(kPBlock) void k_p2m_prep(GridDev g, TileGrid tg,
     load_position<XS>(xin, i, x);
     h = hin ? hin[i] : 0.0f;
     m = min_[i];
-    P[t] = make_float4(x[0], x[1], x[2], h);
     ok = particle_ok<SCH>(g, x, h);
     if (!ok) atomicOr(bad, 1);
+    to_unit(g, x, h);
+    P[t] = make_float4(x[0], x[1], x[2], h);
   }
   // S in float64: a support of 10^5 cells (H near half the mesh) would
   // drift by 1e-5 in float32.  The wave's particles are taken 64 / G at a time, G
@@ -505,7 +518,7 @@ __global__ void k_p2m_tilekey(GridDev g, TileGrid tg, const float* __restrict__ 
   bool in = true;
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
-    float s = floorf((x[3 * t + a] - g.lo[a]) / g.cell);
+    float s = floorf((x[3 * t + a] - g.in_lo[a]) / g.in_cell);
     if (g.periodic && s == s) s -= floorf(s / (float)g.n[a]) * (float)g.n[a];
     in &= s >= 0.0f && s < (float)g.n[a];
     c[a] = in ? (int)s : 0;
@@ -529,7 +542,7 @@ __global__ __launch_bounds__(kPBlock) void k_p2m_scatter(GridDev g, TileGrid tg,
   if (t < n) {
     const float4 v = load_packed(P, t);
     x[0] = v.x, x[1] = v.y, x[2] = v.z, h = v.w;
-    ok = particle_ok<SCH>(g, x, h);
+    ok = true;  // (the prep pass refuses the call otherwise)
   }
   const Images im = images_of<SCH>(g, x, fmaxf(h, g.cell));
   for (int img = 0; img < 8; ++img) {
@@ -659,11 +672,13 @@ __global__ __launch_bounds__(kPBlock) void k_p2m_bwd(GridDev g, const float* __r
   const int64_t i = order ? order[t] : t;
   float xi[3];
   load_position<XS>(x, i, xi);
-  const float hi = h[i], mi = m[i];
+  float hi = h[i];
+  const float mi = m[i];
   if (!particle_ok(g, xi, hi)) {
     atomicOr(bad, 1);
     return;
   }
+  to_unit(g, xi, hi);
   const float inv2h = 2.0f / fmaxf(hi, g.cell);
   // grad w = (2 / H) fct (x_i - x_c) with fct = w'(q) / r; along a row of cells dx
   // and dy are the same, so the row sums fct and g fct and the two axes take
@@ -703,7 +718,7 @@ __global__ __launch_bounds__(kPBlock) void k_p2m_bwd(GridDev g, const float* __r
   const double mean = A / S;
   if (gm) gm[i] = (float)mean;
   if (gx) {
-    const double f = (double)mi / S * (double)inv2h;
+    const double f = (double)mi / S * (double)inv2h * (double)g.unit;
 #pragma unroll
     for (int a = 0; a < 3; ++a) gx[3 * i + a] = (float)(f * (C[a] - mean * B[a]));
   }
@@ -717,12 +732,17 @@ static bool grid_ok(const kdt_grid* g) {
 
 static GridDev to_dev(const kdt_grid* g) {
   GridDev d;
+  int e = 0;
+  (void)std::frexp(g->cell, &e);  // cell / 2^e in [1/2, 1)
+  d.unit = std::ldexp(1.0f, std::min(126, std::max(-126, 1 - e)));
+  d.in_cell = g->cell;
+  d.cell = g->cell * d.unit;
   for (int a = 0; a < 3; ++a) {
-    d.lo[a] = g->lo[a];
+    d.in_lo[a] = g->lo[a];
+    d.lo[a] = g->lo[a] * d.unit;
     d.n[a] = g->n[a];
-    d.L[a] = g->cell * (float)g->n[a];
+    d.in_L[a] = g->cell * (float)g->n[a];
   }
-  d.cell = g->cell;
   d.periodic = g->periodic;
   return d;
 }
