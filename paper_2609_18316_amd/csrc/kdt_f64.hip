@@ -50,7 +50,7 @@ __device__ __forceinline__ TreeView shape_view(const View64& v) {
 }
 
 View64 view64(const kdt_tree* t) {
-  return View64{t->rec64, t->box64, t->perm, t->n, t->levels, t->nodes};
+  return View64{t->rec64, t->box64, t->perm, t->n, t->levels, t->nodes, visit_counters()};
 }
 
 __global__ void k_to_f32(const double* __restrict__ x, int64_t m, float* __restrict__ y,
@@ -183,16 +183,17 @@ template <int D, int KC>
 constexpr int lane64_waves() {
   return ListMerge<TopK<KC>, D>::kOn ? 4 : 1;
 }
-// kNN over a median tree by keys of the float32 rounding of each float64
-// distance and the tree position: they take the float32 path's lists and
+// kNN over a median tree by keys of 64 bits, the float64 squared distance with the tree
+// position in its lowest bits (Space64): they take the float32 path's lists and
 // traversal (knn_median), where a (float64, index) list is 96 registers and
 // 12 instructions per slot and insertion at k = 32 (216 VGPRs, two waves per SIMD;
-// the call for 500009 queries on 2000003 clustered points 9.0 ms; now 2.03).  Rounding
-// keeps the order of all but equal keys, so the list holds the k nearest points unless
-// the k-th rounded distance is also that of a point that was turned away.
+// the call for 500009 queries on 2000003 clustered points 9.0 ms; now 1.95).  The keys keep the
+// order of all but nearly equal distances, so the list holds the k nearest points
+// unless the k-th key's distance bits are also those of a point that was turned away, or the
+// list has room left (infinite distances and NaN have no key).
 // Such a query is left to k_knn64 (todo); every other row gets its exact
 // float64 distances, computed again from the list's positions, and runs of
-// equal rounded distances are put into (d2, index) order in place.
+// equal bits are put into (d2, index) order in place.
 template <int D, int KC>
 __global__ __launch_bounds__(kF64Block)
 __attribute__((amdgpu_waves_per_eu(lane64_waves<D, KC>()))) void k_knn64_median(
@@ -206,25 +207,29 @@ __attribute__((amdgpu_waves_per_eu(lane64_waves<D, KC>()))) void k_knn64_median(
   const int64_t row = load_query64<D>(v, q, order, i, qq);
   TopKTie<KC> best;
   best.init(k);
-  knn_median<D, ListMerge<TopK<KC>, D>::kOn>(Space64<D>{v}, qq, best, stk + threadIdx.x,
+  const uint32_t low = Space64<D>::low_bits(v.n);
+  knn_median<D, ListMerge<TopK<KC>, D>::kOn>(Space64<D>{v, low}, qq, best, stk + threadIdx.x,
                                              kF64Block);
   double* d2 = out_d2 + row * k;
   int32_t* idx = out_idx ? out_idx + row * k : nullptr;
   bool runs = false;
+  int have = 0;
 #pragma unroll
   for (int j = 0; j < KC; ++j) {
     if (j < KC - k) continue;
     const uint64_t key = best.key(j);
-    const bool empty = key == kEmptyKey;
-    const int64_t pos = empty ? 0 : (int64_t)(uint32_t)key;
-    if (j > KC - k) runs |= !empty && (key >> 32) == (best.key(j - 1) >> 32);
+    const bool empty = key == kEmptyKeyTie;
+    have += !empty;
+    const int64_t pos = empty ? 0 : (int64_t)((uint32_t)key & low);
+    if (j > KC - k) runs |= !empty && ((key ^ best.key(j - 1)) & ~(uint64_t)low) == 0;
     d2[j - (KC - k)] = empty ? INFINITY : sq_dist<D>(v.rec + pos * D, qq);
     if (idx) idx[j - (KC - k)] = empty ? -1 : v.perm[pos];
   }
-  if (v.n > k && !(best.lost > best.worst_d2())) {
+  const int m = (int)(v.n < k ? v.n : k);
+  const uint64_t lost = (uint64_t)__double_as_longlong(best.lost);
+  if (have < m || (v.n > k && (lost & ~(uint64_t)low) <= (best.worst() & ~(uint64_t)low))) {
     todo[atomicAdd(n_todo, 1)] = (int32_t)i;
   } else if (runs) {
-    const int m = (int)(v.n < k ? v.n : k);
     for (int a = 1; a < m; ++a) {
       const double d = d2[a];
       const int32_t id = idx ? idx[a] : 0;

@@ -432,19 +432,29 @@ __device__ __forceinline__ void TopK<KC>::offer(float d2, int32_t id) {
   if (key < worst()) insert(key);
 }
 
-// TopK that also knows the smallest squared distance it has turned away: if
-// that is the k-th distance, which of the equals belongs into the list is open
-// to the caller (float64 trees, whose keys are rounded).
+// Key of an empty slot of TopKTie: it sorts after every point and is a finite float64.
+constexpr uint64_t kEmptyKeyTie = 0x7FEFFFFFFFFFFFFFull;
+
+// TopK for float64 trees: its keys are float64 squared distances whose lowest bits hold the
+// point's tree position (Space64).  It also knows the smallest key that it has turned away: if
+// all but the position is the k-th key's, which of the equals belongs into the list is
+// open to the caller.  Distances are compared by their upper words.
 template <int KC>
 struct TopKTie : TopK<KC> {
-  float lost = INFINITY;
-  __device__ __forceinline__ void turn_away(uint64_t key) {
-    lost = fminf(lost, __uint_as_float((uint32_t)(key >> 32)));
+  double lost;
+  __device__ __forceinline__ void init(int k) {
+    lost = __longlong_as_double((long long)kEmptyKeyTie);
+#pragma unroll
+    for (int i = 0; i < KC; ++i) this->a[i] = (i < KC - k) ? 0.0 : lost;
   }
-  __device__ __forceinline__ void offer(float d2, int32_t id) {
-    uint64_t key = make_key(d2, id);
+  __device__ __forceinline__ uint32_t worst_d2() const { return (uint32_t)(this->worst() >> 32); }
+  __device__ __forceinline__ void turn_away(double key) {
+    asm("v_min_f64 %0, %0, %1" : "+v"(lost) : "v"(key));
+  }
+  __device__ __forceinline__ void offer(uint32_t d2, int32_t id) {
+    uint64_t key = ((uint64_t)d2 << 32) | (uint32_t)id;
     if (key < this->worst()) key = this->insert(key);
-    turn_away(key);
+    turn_away(__longlong_as_double((long long)key));
   }
   __device__ __forceinline__ void merge(double (&c)[kListBatch]) {
     static_assert(KC >= kListBatch, "the whole batch fits the list");
@@ -453,7 +463,7 @@ struct TopKTie : TopK<KC> {
     for (int i = 0; i < kListBatch; ++i) {
       double& mine = this->a[KC - 1 - i];
       order_in_place(mine, c[i]);
-      turn_away((uint64_t)__double_as_longlong(c[i]));
+      turn_away(c[i]);
     }
     sort_bitonic(this->a);
   }
@@ -502,6 +512,12 @@ __device__ __forceinline__ double batch_key(const TopK<KC>&, bool there, float d
   return __longlong_as_double((long long)(there ? make_key(d2, id) : kEmptyKey));
 }
 template <int KC>
+__device__ __forceinline__ double batch_key(const TopKTie<KC>&, bool there, uint32_t d2,
+                                            int32_t id) {
+  return __longlong_as_double(
+      (long long)(there ? ((uint64_t)d2 << 32) | (uint32_t)id : kEmptyKeyTie));
+}
+template <int KC>
 __device__ __forceinline__ uint32_t batch_key(const TopD<KC>&, bool there, float d2, int32_t) {
   return there ? __float_as_uint(d2) : 0x7F800000u;
 }
@@ -532,8 +548,11 @@ struct OpenMetric {
 template <int D, class Metric>
 struct Space32 {
   using Coord = float;
+  using Dist = float;
   const TreeView& t;
   const Metric& m;
+  static __device__ __forceinline__ uint32_t bits(float d) { return __float_as_uint(d); }
+  static __device__ __forceinline__ float from_bits(uint32_t d) { return __uint_as_float(d); }
   // Box distances of the nodes c and c + 1.
   __device__ __forceinline__ void pair(uint32_t c, const float p[D], float& d0, float& d1) const {
     float lo[D], hi[D];
@@ -555,29 +574,44 @@ struct Space32 {
   }
 };
 
-// The points of a float64 tree, by the float32 rounding of their float64
-// distances and by tree position.  Rounding is monotone, so a box distance
-// rounded this way never exceeds the rounded distance of a point inside.
+// The points of a float64 tree by keys of 64 bits: the float64 squared distance, its lowest
+// bits (`low`, as many as a position has) replaced by the tree position.  That keeps
+// float64's whole range, so coordinates of any scale are told apart, and 31 bits of the
+// mantissa at 2^21 points.  Cutting bits off is monotone; nodes and candidates are
+// tested by the upper words alone, which lets a few more through.  (An infinite distance is
+// above every key's, and a NaN too.)
 template <int D>
 struct Space64 {
   using Coord = double;
+  using Dist = uint32_t;
   const View64& t;
-  __device__ __forceinline__ void pair(uint32_t c, const double p[D], float& d0,
-                                       float& d1) const {
+  uint32_t low;
+  static __device__ __forceinline__ uint32_t low_bits(int64_t n) {
+    return n > 1 ? 0xFFFFFFFFu >> __clz((uint32_t)(n - 1)) : 0u;
+  }
+  static __device__ __forceinline__ uint32_t bits(uint32_t d) { return d; }
+  static __device__ __forceinline__ uint32_t from_bits(uint32_t d) { return d; }
+  static __device__ __forceinline__ uint32_t upper(double d) {
+    return (uint32_t)__double2hiint(d);
+  }
+  __device__ __forceinline__ void pair(uint32_t c, const double p[D], uint32_t& d0,
+                                       uint32_t& d1) const {
     const double* b = t.box + (size_t)c * 2 * D;
     double x[4 * D];
 #pragma unroll
     for (int a = 0; a < 4 * D; ++a) x[a] = b[a];
-    d0 = (float)box_mindist<D>(x, x + D, p);
-    d1 = (float)box_mindist<D>(x + 2 * D, x + 3 * D, p);
+    d0 = upper(box_mindist<D>(x, x + D, p));
+    d1 = upper(box_mindist<D>(x + 2 * D, x + 3 * D, p));
   }
   __device__ __forceinline__ const double* run(int32_t base) const {
     return t.rec + (int64_t)base * D;
   }
-  __device__ __forceinline__ float dist(const double* r, int32_t base, int i, const double p[D],
-                                        int32_t& id) const {
-    id = base + i;
-    return (float)sq_dist<D>(r + i * D, p);
+  // id: the key's lower word
+  __device__ __forceinline__ uint32_t dist(const double* r, int32_t base, int i,
+                                           const double p[D], int32_t& id) const {
+    const double d2 = sq_dist<D>(r + i * D, p);
+    id = (int32_t)(((uint32_t)__double2loint(d2) & ~low) | (uint32_t)(base + i));
+    return upper(d2);
   }
 };
 
@@ -647,7 +681,7 @@ __device__ __forceinline__ void leaf_offer(const Space& sp, int32_t b, int cnt, 
   constexpr int B = kMerge ? kListBatch : 32;
   constexpr int kFewPoints = 8;
   for (int o = 0; o < cnt; o += B) {
-    const float w = best.worst_d2();
+    const typename Space::Dist w = best.worst_d2();
     const int m = min(cnt - o, B);
     const int32_t c = b + o;
     int32_t base = c;
@@ -664,7 +698,7 @@ __device__ __forceinline__ void leaf_offer(const Space& sp, int32_t b, int cnt, 
 #pragma unroll
         for (int i = 0; i < B; ++i) {
           int32_t id = 0;
-          const float d2 = sp.dist(r, base, i, p, id);
+          const typename Space::Dist d2 = sp.dist(r, base, i, p, id);
           const bool ok = ((valid >> i) & 1u) && d2 <= w;  // (false for NaN)
           mask |= (uint32_t)ok << i;
           key[i] = batch_key(best, ok, d2, id);
@@ -696,7 +730,7 @@ __device__ __forceinline__ void leaf_offer(const Space& sp, int32_t b, int cnt, 
       const int i = __builtin_ctz(mask);
       mask &= mask - 1;
       int32_t id = 0;
-      const float d2 = sp.dist(r, base, i, p, id);
+      const typename Space::Dist d2 = sp.dist(r, base, i, p, id);
       best.offer(d2, id);
     }
   }
@@ -723,6 +757,7 @@ __device__ __forceinline__ void leaf_offer(const Space& sp, int32_t b, int cnt, 
 template <int D, bool kMerge, class Space, class List>
 __device__ __forceinline__ void knn_median(const Space& sp, const typename Space::Coord p[D],
                                            List& best, uint32_t* stk, int ld) {
+  using Dist = typename Space::Dist;
   const auto& t = sp.t;
   constexpr int kWait = D > 4 ? 2 : kMerge ? 4 : 6;
   const uint32_t first = 1u << t.levels;
@@ -751,26 +786,26 @@ __device__ __forceinline__ void knn_median(const Space& sp, const typename Space
       }
     } else if (!leaf) {
       const uint32_t c0 = 2 * h;
-      float d0, d1;
+      Dist d0, d1;
       KDT_LANE_VISIT(t, kVisitNodes, 2);
       sp.pair(c0 - 1, p, d0, d1);
-      const float dn = fminf(d0, d1), df = fmaxf(d0, d1);
-      const float w = best.worst_d2();
+      const Dist dn = min(d0, d1), df = max(d0, d1);
+      const Dist w = best.worst_d2();
       const int lev = 32 - __clz(h);  // of the children
       if (df <= w) {
         pend |= 1u << lev;
-        stk[lev * ld] = __float_as_uint(df);
+        stk[lev * ld] = Space::bits(df);
       }
       h = c0 + (d0 <= d1 ? 0u : 1u);
       pop = !(dn <= w);
     }
-    const float w = best.worst_d2();
+    const Dist w = best.worst_d2();
     while (pop) {
       if (pend != 0) {
         const int l = 31 - __clz(pend);
         pend ^= 1u << l;
         h = (h >> (31 - __clz(h) - l)) ^ 1u;
-        pop = !(__uint_as_float(stk[l * ld]) <= w);
+        pop = !(Space::from_bits(stk[l * ld]) <= w);
       } else {
         more = pop = false;
       }
