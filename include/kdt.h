@@ -212,15 +212,16 @@ kdt_status kdt_build(const float *d_pts, int64_t n, int32_t d, const kdt_build_o
 kdt_status kdt_free(kdt_tree *tree);
 
 /*
- * Releases the device memory the library keeps for `stream` between calls: the
- * scratch of the particle-to-mesh deposits (sized by the largest call so
- * far) and idle blocks of earlier trees and calls (blocks of up to 128 MiB, at
- * most 512 MiB per stream and 2 GiB in all; they are also given back when an
- * allocation of the library fails), so that repeated calls allocate
- * nothing.  The memory is returned in
- * stream order (work already queued on `stream` finishes first).  Call it
- * before destroying a stream that ran the library's calls, or to give the memory back;
- * the next call on the stream allocates again.  Errors: KDT_EDEVICE.
+ * Releases the device memory the library keeps for `stream` between calls, so
+ * that repeated calls allocate nothing: the scratch of the particle-to-mesh deposits
+ * (sized by the largest call so far) and the idle blocks of earlier trees and calls
+ * (blocks of up to 128 MiB, at most 512 MiB per stream and 2 GiB in all).  The memory
+ * is returned in stream order (work already queued on `stream` finishes first); the
+ * next call on the stream allocates again.  Call it to give the memory back, and
+ * before destroying a stream that ran deposits.  Idle blocks need no call:
+ * those of a stream that was destroyed serve other streams, and all go back
+ * to the device before an allocation of the library fails for lack of memory (a stream
+ * under capture excepted).  A tree may be freed before or after.  Errors: KDT_EDEVICE.
  */
 kdt_status kdt_stream_release(hipStream_t stream);
 

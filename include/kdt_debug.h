@@ -21,6 +21,20 @@ extern "C" {
 kdt_status kdt_debug_fail_alloc(int64_t after);
 
 /*
+ * Makes the `after`-th next request of the library for device memory (counting from 1,
+ * process-wide, those of batched plans included) find none; after <= 0 disarms the hook.
+ * The library then gives its idle blocks back and asks once more, which succeeds.
+ */
+kdt_status kdt_debug_fail_memory(int64_t after);
+
+/*
+ * Writes to *h_bytes (host) the bytes of the idle blocks that the library keeps on the
+ * current device for `stream`, or with all = 1 for every stream.
+ * Errors: KDT_EINVAL (NULL), KDT_EDEVICE.
+ */
+kdt_status kdt_debug_kept(hipStream_t stream, int32_t all, int64_t *h_bytes);
+
+/*
  * Work counters of the instrumented build of the library (compiled with
  * KDT_COUNT_VISITS; the product build returns KDT_EUNSUPPORTED): waits for
  * the device, then writes 8 uint64 totals to h_counts (host, may be NULL)

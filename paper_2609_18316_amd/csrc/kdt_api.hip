@@ -12,10 +12,9 @@
 #include <memory>
 #include <mutex>
 #include <string>
-#include <unordered_map>
-#include <utility>
 #include <vector>
 
+#include "kdt_blocks.h"
 #include "kdt_debug.h"
 #include "kdt_query.h"
 
@@ -83,117 +82,112 @@ unsigned long long* visit_counters() {
 #endif
 }
 
-// Blocks of device memory kept between calls.  The pool's allocations and
-// frees cost a call more than its kernels when it is small -- every free puts
-// a marker on the stream, and after some 1500 calls the pool of this
-// runtime answered in milliseconds: a build, a kNN and a count call over
-// 1000 points 0.67 ms at first, 3.3 ms later; with the blocks kept 0.28 ms
-// throughout.  65536 points: 1.18 and 3.3 ms, now 0.81; lists of 1000003 balls on
-// 4000037 points: 7.6, now 5.6 ms.
-//
-// A block belongs to one stream: the work of its next user is ordered after that of its
-// last one by the stream itself, whichever thread queued it, and a block in use
-// is in nobody else's reach.  Kept are blocks of up to kKeepBlock bytes, at
-// most kKeepStream bytes per stream and kKeepAll in all, until
-// kdt_stream_release or an allocation that fails for lack of memory; larger ones are
-// the pool's, whose cost their work outweighs.  The pool serves two more cases: a stream
-// under capture, whose graph has to own its memory, and the per-thread
-// default stream, one handle for as many streams as there are threads.
 namespace {
-constexpr size_t kKeepBlock = size_t(128) << 20;
-constexpr size_t kKeepStream = size_t(512) << 20;
-constexpr size_t kKeepAll = size_t(2) << 30;
-struct KeptStream {
-  std::multimap<size_t, void*> idle;  // by size
-  size_t bytes = 0;                   // of the idle blocks
+std::atomic<int64_t> g_fail_memory{-1};
+
+// While it lives, waiting for events does not disturb a graph that another thread captures.
+class RelaxedCapture {
+ public:
+  RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode_); }
+  ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode_); }
+
+ private:
+  hipStreamCaptureMode mode_ = hipStreamCaptureModeRelaxed;
 };
-struct LiveBlock {
-  size_t bytes;
-  int device;
+
+// The memory behind the kept blocks (kdt_blocks.h).
+struct HipBlocks {
+  using Stream = hipStream_t;
+  using Event = hipEvent_t;
+  bool permanent(hipStream_t s) { return s == nullptr; }
+  bool record(hipEvent_t* e, hipStream_t s) {
+    if (hipEventCreateWithFlags(e, hipEventDisableTiming) != hipSuccess) return false;
+    if (hipEventRecord(*e, s) == hipSuccess) return true;
+    (void)hipEventDestroy(*e);
+    return false;
+  }
+  bool passed(hipEvent_t e) {
+    const RelaxedCapture relaxed;
+    const hipError_t before = hipPeekAtLastError();
+    const bool yes = hipEventQuery(e) == hipSuccess;
+    // "not ready" is no error to report, an error from before is
+    if (!yes && before == hipSuccess) (void)hipGetLastError();
+    return yes;
+  }
+  bool order_after(hipStream_t s, hipEvent_t e) {
+    return hipStreamWaitEvent(s, e, 0) == hipSuccess;
+  }
+  void forget(hipEvent_t e) { (void)hipEventDestroy(e); }
+  bool free(void* p, hipStream_t s) { return hipFreeAsync(p, s) == hipSuccess; }
+  bool finish(hipStream_t s, const hipEvent_t* e) {
+    const RelaxedCapture relaxed;
+    return (e ? hipEventSynchronize(*e) : hipStreamSynchronize(s)) == hipSuccess;
+  }
 };
-std::mutex g_keep_mu;
+
 // never destroyed, as g_scratch
-auto* g_kept = new std::map<std::pair<int, hipStream_t>, KeptStream>();
-auto* g_live = new std::unordered_map<void*, LiveBlock>();  // blocks of these sizes in use
-size_t g_idle_bytes = 0;
+BlockCache<HipBlocks>& g_blocks = *new BlockCache<HipBlocks>();
 
-// Four sizes per octave, so that calls of slightly different sizes share blocks.
-size_t block_size(size_t bytes) {
-  size_t step = 256;
-  while (step * 8 < bytes) step *= 2;
-  return (bytes + step - 1) / step * step;
-}
-
-bool keeps(size_t bytes, hipStream_t stream) {
-  if (bytes > kKeepBlock || stream == hipStreamPerThread) return false;
+bool capturing(hipStream_t stream) {
+  if (!stream) return false;  // the null stream cannot be captured
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(stream, &cap) != hipSuccess) {
     (void)hipGetLastError();
-    return false;
+    return true;
   }
-  return cap == hipStreamCaptureStatusNone;
+  return cap != hipStreamCaptureStatusNone;
+}
+
+bool memory_should_fail() {
+  int64_t v = g_fail_memory.load();
+  while (v > 0) {
+    if (g_fail_memory.compare_exchange_weak(v, v - 1)) return v == 1;
+  }
+  return false;
+}
+
+// `get` again, after every idle block of the device and what its pool holds unused went back
+// to the device, where memory did not suffice.
+template <typename F>
+hipError_t with_all_memory(F&& get) {
+  hipError_t e = memory_should_fail() ? hipErrorOutOfMemory : get();
+  if (e != hipErrorOutOfMemory) return e;
+  int dev = 0;
+  hipMemPool_t pool;
+  if (hipGetDevice(&dev) != hipSuccess) return e;
+  (void)g_blocks.release_all(dev, nullptr);
+  if (hipDeviceGetDefaultMemPool(&pool, dev) == hipSuccess) (void)hipMemPoolTrimTo(pool, 0);
+  (void)hipGetLastError();
+  return memory_should_fail() ? hipErrorOutOfMemory : get();
 }
 }  // namespace
 
+// Blocks up to kKeepBlock are kept (kdt_blocks.h); the pool serves the rest, and two more
+// cases: a stream under capture, whose graph has to own its memory, and the per-thread
+// default stream, one handle for as many streams as there are threads.
 hipError_t dev_alloc(void** ptr, size_t bytes, hipStream_t stream) {
   if (alloc_should_fail()) return hipErrorOutOfMemory;
   int dev = 0;
-  if (!keeps(bytes, stream) || hipGetDevice(&dev) != hipSuccess)
-    return pool_alloc(ptr, bytes, stream);
-  const size_t size = block_size(bytes);
-  std::vector<void*> dead;
-  {
-    std::lock_guard<std::mutex> lock(g_keep_mu);
-    KeptStream& k = (*g_kept)[{dev, stream}];
-    const auto it = k.idle.find(size);
-    if (it != k.idle.end()) {
-      *ptr = it->second;
-      k.idle.erase(it);
-      k.bytes -= size;
-      g_idle_bytes -= size;
-      (*g_live)[*ptr] = {size, dev};
-      return hipSuccess;
-    }
+  if (capturing(stream)) return pool_alloc(ptr, bytes, stream);
+  const bool keep = bytes <= kKeepBlock && stream != hipStreamPerThread &&
+                    hipGetDevice(&dev) == hipSuccess;
+  if (keep) {
+    *ptr = g_blocks.take(dev, bytes, stream);
+    if (*ptr) return hipSuccess;
+    bytes = block_size(bytes);
   }
-  hipError_t e = pool_alloc(ptr, size, stream);
-  if (e != hipSuccess) {
-    // give every idle block of the device back, then ask once more
-    {
-      std::lock_guard<std::mutex> lock(g_keep_mu);
-      for (auto& ks : *g_kept) {
-        if (ks.first.first != dev) continue;
-        for (const auto& b : ks.second.idle) dead.push_back(b.second);
-        g_idle_bytes -= ks.second.bytes;
-        ks.second = KeptStream();
-      }
-    }
-    for (void* q : dead) (void)hipFree(q);  // waits for the work that used them
-    (void)hipGetLastError();
-    if (!dead.empty()) e = pool_alloc(ptr, size, stream);
-    if (e != hipSuccess) return e;
-  }
-  std::lock_guard<std::mutex> lock(g_keep_mu);
-  (*g_live)[*ptr] = {size, dev};
-  return hipSuccess;
+  const hipError_t e = with_all_memory([&] { return pool_alloc(ptr, bytes, stream); });
+  if (e == hipSuccess && keep) g_blocks.adopt(*ptr, dev, bytes);
+  return e;
 }
 
-void dev_free(void* ptr, hipStream_t stream) {
-  {
-    std::lock_guard<std::mutex> lock(g_keep_mu);
-    const auto it = g_live->find(ptr);
-    if (it != g_live->end()) {
-      const LiveBlock b = it->second;
-      g_live->erase(it);
-      KeptStream& k = (*g_kept)[{b.device, stream}];
-      if (k.bytes + b.bytes <= kKeepStream && g_idle_bytes + b.bytes <= kKeepAll) {
-        k.idle.emplace(b.bytes, ptr);
-        k.bytes += b.bytes;
-        g_idle_bytes += b.bytes;
-        return;
-      }
-    }
-  }
-  (void)hipFreeAsync(ptr, stream);
+void dev_free(void* const* ptrs, size_t n, hipStream_t stream) {
+  g_blocks.give(ptrs, n, stream, !capturing(stream));
+}
+void dev_free(void* ptr, hipStream_t stream) { dev_free(&ptr, 1, stream); }
+
+hipError_t plain_alloc(void** ptr, size_t bytes) {
+  return with_all_memory([&] { return hipMalloc(ptr, std::max<size_t>(bytes, 256)); });
 }
 
 void* stream_scratch(hipStream_t stream, int slot, size_t bytes) {
@@ -231,25 +225,12 @@ extern "C" kdt_status kdt_stream_release(hipStream_t stream) {
       ++it;
     }
   }
-  KeptStream mine;
-  {
-    std::lock_guard<std::mutex> keep(g_keep_mu);
-    const auto it = g_kept->find({dev, stream});
-    if (it != g_kept->end()) {
-      mine = std::move(it->second);
-      g_idle_bytes -= mine.bytes;
-      g_kept->erase(it);
-    }
+  if (!g_blocks.release(dev, stream)) {
+    kdt_set_error("kdt_stream_release: hipFreeAsync failed");
+    return KDT_EDEVICE;
   }
-  kdt_status st = KDT_OK;
-  for (const auto& b : mine.idle)
-    if (hipFreeAsync(b.second, stream) != hipSuccess) {
-      kdt_set_error("kdt_stream_release: hipFreeAsync failed");
-      st = KDT_EDEVICE;
-    }
-  return st;
+  return KDT_OK;
 }
-
 
 // Build schedules depend only on (device, n, d, leaf); repeated builds of the
 // same shape reuse the uploaded tables.
@@ -653,6 +634,27 @@ extern "C" kdt_status kdt_tree_export(const kdt_tree* tree, float* h_pts, int32_
 extern "C" kdt_status kdt_debug_fail_alloc(int64_t after) {
   kdt_clear_error();
   g_fail_after.store(after > 0 ? after : -1);
+  return KDT_OK;
+}
+
+extern "C" kdt_status kdt_debug_fail_memory(int64_t after) {
+  kdt_clear_error();
+  g_fail_memory.store(after > 0 ? after : -1);
+  return KDT_OK;
+}
+
+extern "C" kdt_status kdt_debug_kept(hipStream_t stream, int32_t all, int64_t* h_bytes) {
+  kdt_clear_error();
+  if (!h_bytes) {
+    kdt_set_error("kdt_debug_kept: NULL h_bytes");
+    return KDT_EINVAL;
+  }
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) {
+    kdt_set_error("kdt_debug_kept: no current device");
+    return KDT_EDEVICE;
+  }
+  *h_bytes = (int64_t)g_blocks.idle_bytes(dev, all ? nullptr : &stream);
   return KDT_OK;
 }
 

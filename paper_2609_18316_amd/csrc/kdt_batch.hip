@@ -459,12 +459,12 @@ extern "C" kdt_status kdt_batch_plan_create(const int64_t* h_offsets, int32_t n_
   const size_t b_split = sizeof(float) * (size_t)bp->plan.n_nodes;
   auto up = [](size_t b) { return (b + 255) & ~size_t(255); };
   if (st == KDT_OK &&
-      (hipMalloc(&bp->tree_block, up(b_rec) + up(b_box) + up(b_perm) + up(b_axis) + up(b_split)) !=
+      (plain_alloc(&bp->tree_block, up(b_rec) + up(b_box) + up(b_perm) + up(b_axis) + up(b_split)) !=
            hipSuccess ||
-       hipMalloc((void**)&bp->parent, sizeof(int32_t) * std::max<int64_t>(tot, 1)) != hipSuccess ||
-       hipMalloc((void**)&bp->conn, sizeof(uint32_t) * std::max<int64_t>(bp->plan.n_nodes, 1)) !=
+       plain_alloc((void**)&bp->parent, sizeof(int32_t) * std::max<int64_t>(tot, 1)) != hipSuccess ||
+       plain_alloc((void**)&bp->conn, sizeof(uint32_t) * std::max<int64_t>(bp->plan.n_nodes, 1)) !=
            hipSuccess ||
-       hipMalloc((void**)&bp->ctr, 256) != hipSuccess)) {
+       plain_alloc((void**)&bp->ctr, 256) != hipSuccess)) {
     kdt_set_error("kdt_batch_plan_create: device allocation failed (%lld points)", (long long)tot);
     st = KDT_ENOMEM;
   }
@@ -472,7 +472,7 @@ extern "C" kdt_status kdt_batch_plan_create(const int64_t* h_offsets, int32_t n_
     std::vector<int64_t> pb(n_sets + 1, 0);
     for (int i = 0; i < n_sets; ++i) pb[i + 1] = pb[i] + (h_offsets[i + 1] - h_offsets[i] + 63) / 64;
     bp->n_packets = pb[n_sets];
-    if (hipMalloc((void**)&bp->pbase, sizeof(int64_t) * (n_sets + 1)) != hipSuccess ||
+    if (plain_alloc((void**)&bp->pbase, sizeof(int64_t) * (n_sets + 1)) != hipSuccess ||
         hipMemcpy(bp->pbase, pb.data(), sizeof(int64_t) * (n_sets + 1), hipMemcpyHostToDevice) !=
             hipSuccess) {
       kdt_set_error("kdt_batch_plan_create: cannot upload the packet table");

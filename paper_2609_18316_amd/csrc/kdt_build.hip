@@ -938,7 +938,7 @@ kdt_status plan_upload(const Plan& p, PlanDev& pd, hipStream_t stream) {
     memcpy(host.data() + o_chunks[l], p.chunks[l].data(), sizeof(ChunkEntry) * p.chunks[l].size());
   }
   memcpy(host.data() + o_subs, p.subs.data(), sizeof(SubEntry) * p.subs.size());
-  if (hipMalloc(&pd.block, bytes) != hipSuccess) {
+  if (plain_alloc(&pd.block, bytes) != hipSuccess) {
     kdt_set_error("cannot allocate %zu bytes for the build schedule", bytes);
     return KDT_ENOMEM;
   }
@@ -1033,7 +1033,7 @@ kdt_status build_scratch_alloc(const Plan& p, const PlanDev& pd, BuildScratch& w
   const int64_t tot = p.total;
   const int d = p.d;
   auto A = [&](void** ptr, size_t bytes) -> bool {
-    if (stream == kPlainAlloc) return hipMalloc(ptr, std::max<size_t>(bytes, 256)) == hipSuccess;
+    if (stream == kPlainAlloc) return plain_alloc(ptr, bytes) == hipSuccess;
     return dev_alloc(ptr, bytes, stream) == hipSuccess;
   };
   const int64_t nroot = (int64_t)p.root_chunks.size();
@@ -1054,13 +1054,12 @@ kdt_status build_scratch_alloc(const Plan& p, const PlanDev& pd, BuildScratch& w
 
 void build_scratch_free(BuildScratch& w, hipStream_t stream) {
   void* ptrs[] = {w.x[0], w.x[1], w.p[0], w.p[1], w.pbox, w.cbox, w.st, w.chist, w.cnt, w.bad};
-  for (void* q : ptrs)
-    if (q) {
-      if (stream == kPlainAlloc)
-        (void)hipFree(q);
-      else
-        dev_free(q, stream);
-    }
+  if (stream == kPlainAlloc) {
+    for (void* q : ptrs)
+      if (q) (void)hipFree(q);
+  } else {
+    dev_free(ptrs, std::size(ptrs), stream);
+  }
   w = BuildScratch();
 }
 

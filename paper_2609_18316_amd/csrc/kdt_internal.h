@@ -255,11 +255,15 @@ kdt_status build_launch(const Plan& p, const PlanDev& pd, const float* d_pts,
 // Stream-ordered device memory: what dev_alloc returns may be used by work
 // queued on `stream` from here on, and dev_free (the same stream) gives it back once the work
 // queued so far has run.  Small blocks are kept by the library for later calls
-// on the same stream, the rest goes through the default pool (kdt_api.hip says which).
+// (kdt_blocks.h), the rest goes through the default pool.
 // dev_alloc fails on purpose when the allocation-failure hook (kdt_debug_fail_alloc)
 // says so.
 hipError_t dev_alloc(void** ptr, size_t bytes, hipStream_t stream);
 void dev_free(void* ptr, hipStream_t stream);
+void dev_free(void* const* ptrs, size_t n, hipStream_t stream);  // (NULL entries are skipped)
+// hipMalloc for memory that no stream owns; like dev_alloc, it asks again after the kept blocks
+// went back where memory does not suffice.
+hipError_t plain_alloc(void** ptr, size_t bytes);
 // Straight from the default pool (kdt_build.hip).
 hipError_t pool_alloc(void** ptr, size_t bytes, hipStream_t stream);
 // True if the allocation-failure hook wants this allocation to fail.
@@ -291,11 +295,8 @@ class PoolBuffers {
   // the end releases first: a free can block the host for milliseconds, and
   // queued behind the stream's work it costs no GPU time.
   void release() {
-    for (void*& q : held_)
-      if (q) {
-        dev_free(q, stream_);
-        q = nullptr;
-      }
+    if (!held_.empty()) dev_free(held_.data(), held_.size(), stream_);
+    held_.clear();
   }
   // count elements of T (at least one); false if the pool is exhausted
   template <typename T>

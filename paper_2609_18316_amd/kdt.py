@@ -33,7 +33,8 @@ EXPORTS = ("kdt_build", "kdt_free", "kdt_tree_get_info", "kdt_tree_export", "kdt
            "kdt_tree_gather", "kdt_tree_scatter", "kdt_p2m_tree", "kdt_p2m_tree_backward",
            "kdt_last_error")
 # The test and measurement hooks of include/kdt_debug.h.
-DEBUG_EXPORTS = ("kdt_debug_fail_alloc", "kdt_debug_visits", "kdt_debug_valu_probe",
+DEBUG_EXPORTS = ("kdt_debug_fail_alloc", "kdt_debug_fail_memory", "kdt_debug_kept",
+                 "kdt_debug_visits", "kdt_debug_valu_probe",
                  "kdt_debug_radix_sort", "kdt_debug_exclusive_scan", "kdt_debug_sort_rows")
 LIB_COUNTS_PATH = os.path.join(HERE, "libkdt_counts.so")
 NOALLOC_MAX_SORTED = 1 << 22   # queries kdt_knn_noalloc can order in its static scratch
@@ -127,6 +128,8 @@ def load(path: str = LIB_PATH):
         lib.kdt_batch_launch.argtypes = [vp, vp, vp, vp, vp, vp, i32, vp]
         lib.kdt_batch_plan_free.argtypes = [vp]
     lib.kdt_debug_fail_alloc.argtypes = [i64]
+    lib.kdt_debug_fail_memory.argtypes = [i64]
+    lib.kdt_debug_kept.argtypes = [vp, i32, C.POINTER(i64)]
     lib.kdt_debug_visits.argtypes = [vp, i32]
     lib.kdt_debug_valu_probe.argtypes = [vp, i32, i32, vp]
     lib.kdt_debug_radix_sort.argtypes = [vp, vp, i64, i32, i32, vp]
@@ -156,7 +159,8 @@ def tuning_get(d: int, n: int, k: int) -> tuple[int, int, int]:
 
 
 def stream_release(stream=None) -> None:
-    """Frees the deposit scratch the library keeps for ``stream`` (stream-ordered)."""
+    """Frees the deposit scratch and the idle blocks the library keeps for ``stream``
+    (stream-ordered)."""
     _check(load().kdt_stream_release(_stream(stream)))
 
 
@@ -205,6 +209,19 @@ def fail_alloc(after: int) -> None:
 
 VISIT_SLOTS = ("lane_nodes", "lane_points", "lane_inserts", "wave_nodes", "wave_points",
                "lane_node_reloads")
+
+
+def fail_memory(after: int) -> None:
+    """Test hook: the ``after``-th next request for device memory finds none at first, so
+    that the library gives its idle blocks back and asks again; 0 disarms it."""
+    _check(load().kdt_debug_fail_memory(int(after)))
+
+
+def kept_bytes(stream=None, every: bool = False) -> int:
+    """Test hook: bytes of the idle blocks kept for ``stream``, or for every stream."""
+    n = C.c_int64(0)
+    _check(load().kdt_debug_kept(_stream(stream), 1 if every else 0, C.byref(n)))
+    return n.value
 
 
 def visits(reset: bool = True) -> dict:
