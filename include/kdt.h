@@ -98,10 +98,13 @@ typedef struct {
                              independent traversal per lane.  2: one traversal
                              shared by the 64 queries of a wave, leaves staged
                              in LDS (trees with leaf_size <= 64; larger leaves
-                             use 1).  0 picks, for kNN, the queries per
-                             traversal the tuning table gives for (d, the
-                             tree's n, k) (kdt_tuning_get: 1 -> 1, 64 -> 2;
-                             as measured, 1 up to d = 8 and 2 for d = 16),
+                             use 1).  0 picks, for kNN, what the tuning
+                             table's nearest entry for (d, the tree's n, k)
+                             says (1 -> 1, 64 -> 2) where that entry was set
+                             with kdt_tuning_set; else 1 where d <= 4 and no
+                             leaf holds more than 32 points or k > 16, and
+                             the compiled-in entry's choice (1 up to d = 8, 2
+                             for d = 16) for the rest;
                              and 2 for ball counts.  Results are identical
                              either way. */
     const int32_t *order; /* NULL, or a device permutation [nq] from
@@ -555,8 +558,9 @@ kdt_status kdt_range_f64(const kdt_tree *tree, const double *d_q, int64_t nq, do
  * shape again).  A lookup takes the entry of dimension d nearest in
  * (log2 n, log2 k).
  *
- * kdt_tuning_get writes (host pointers, each may be NULL) the looked-up
- * leaf size and queries per traversal, and the traversal stack depth a
+ * kdt_tuning_get writes (host pointers, each may be NULL) the looked-up entry's
+ * leaf size and queries per traversal (a compiled-in entry's is not the last word
+ * for small leaves and long lists: kdt_query_opts.traversal), and the traversal stack depth a
  * median tree of that shape needs: its depth L + 1 with
  * L = ceil(log2(ceil(n / leaf))) -- fixed by n and the leaf size, so it is
  * derived rather than tuned.

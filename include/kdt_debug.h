@@ -48,6 +48,14 @@ kdt_status kdt_debug_kept(hipStream_t stream, int32_t all, int64_t *h_bytes);
 kdt_status kdt_debug_visits(uint64_t *h_counts, int32_t reset);
 
 /*
+ * Writes to *traversal (host) the traversal (1: per lane, 2: shared by a wave) that kdt_knn
+ * takes with traversal 0 for k neighbours, open boundaries, on a median tree of n points and
+ * the given leaf_size.  Host only.  Errors: KDT_EINVAL.
+ */
+kdt_status kdt_debug_knn_traversal(int32_t d, int64_t n, int32_t leaf_size, int32_t k,
+                                   int32_t *traversal);
+
+/*
  * Launches a kernel of `blocks` workgroups of 256 threads that only issues
  * VALU instructions (eight independent multiply-add chains per lane, `iters`
  * rounds, 16 float32 instructions per round), asynchronously on `stream`.

@@ -203,6 +203,7 @@ kdt_status count_roots(const int32_t* labels, int64_t n, int64_t* out, void* scr
 struct Tuning {
   int leaf;
   int qpw;
+  bool set;  // by kdt_tuning_set
 };
 Tuning tuned(int d, int64_t n, int k);
 int lds_capacity(int d);

@@ -655,8 +655,8 @@ inline int lane_list(int k, int64_t n) {
   return k <= 8 ? 8 : k <= 16 ? 16 : k <= 32 && n >= kListBatch ? 32 : 64;
 }
 
-// Whether kNN takes one traversal per lane by default, whatever the tuning table
-// says of the shape: in up to 4 dimensions, where the largest leaf (`most`
+// Whether kNN takes one traversal per lane by default, whatever the compiled-in tuning
+// table says of the shape (an entry set at run time decides by itself): in up to 4 dimensions, where the largest leaf (`most`
 // points) is small or the list long.  All points as queries, us per lane / per
 // wave: 65536 uniform points, leaves of 32, k = 8 111 / 130, of 64 139 / 116,
 // k = 32 186 / 272 and 220 / 247; 1000 points, leaves of 32, 66 / 90

@@ -13,6 +13,7 @@
 
 #include <algorithm>
 
+#include "kdt_debug.h"
 #include "kdt_query.h"
 
 namespace kdt {
@@ -357,19 +358,28 @@ static kdt_status knn_dispatch(const kdt_tree* t, const float* d_q, int64_t nq, 
   return KDT_OK;
 }
 
+// The traversal of kNN on a median tree whose largest leaf holds `most` points: 1 per
+// lane, 2 shared by a wave; `asked`: of the caller (0: the default).
+static int knn_traversal(int d, int64_t n, int leaf, int most, int k, int asked) {
+  if (leaf > 64) return 1;  // the wave kernel marks at most 64 points per leaf
+  if (asked != 0) return asked;
+  const Tuning t = tuned(d, n, k);
+  return t.qpw == 64 && (t.set || !lane_default(d, k, most)) ? 2 : 1;
+}
+static int largest_leaf(int64_t n, int levels) {
+  return (int)((n + (int64_t(1) << levels) - 1) >> levels);
+}
+
 // ws: optional workspace for the query order (then nothing is allocated).
 template <int D>
 static kdt_status knn_impl(const kdt_tree* t, const float* d_q, int64_t nq, int k, int32_t* d_idx,
                            float* d_d2, int mode, bool sort_q, int traversal,
                            const int32_t* given, hipStream_t stream, void* ws = nullptr,
                            size_t ws_bytes = 0) {
-  if (traversal == 0) {
-    const int most = (int)((t->n + (int64_t(1) << t->levels) - 1) >> t->levels);
-    // else the tuning table's choice
-    traversal = lane_default(D, k, most) || tuned(D, t->n, k).qpw != 64 ? 1 : 2;
-  }
-  if (t->leaf > 64) traversal = 1;  // the wave kernel marks at most 64 points per leaf
-  if (t->nodes) traversal = 1;      // stored trees: one traversal per lane
+  // (stored trees, whose depth may pass a shift's: one traversal per lane)
+  traversal = t->nodes ? 1
+                       : knn_traversal(D, t->n, t->leaf, largest_leaf(t->n, t->levels), k,
+                                       traversal);
   int32_t* order = nullptr;
   if (d_q && !given && sort_q && nq > 1) {
     kdt_status st = order_queries<D>(t, d_q, nq, traversal == 1 ? 0 : 1, &order, stream, nullptr,
@@ -585,6 +595,19 @@ kdt_status knn_in_workspace(const kdt_tree* t, const float* d_q, int64_t nq, int
 }
 
 }  // namespace kdt
+
+extern "C" kdt_status kdt_debug_knn_traversal(int32_t d, int64_t n, int32_t leaf_size, int32_t k,
+                                              int32_t* traversal) {
+  kdt_clear_error();
+  if ((d != 2 && d != 3 && d != 4 && d != 8 && d != 16) || n < 1 || n > INT32_MAX ||
+      leaf_size < 2 || k < 1 || k > KDT_MAX_K || !traversal) {
+    kdt_set_error("kdt_debug_knn_traversal: d in {2,3,4,8,16}, n in [1, 2^31-1], leaf_size >= 2, "
+                  "k in [1, %d] and a result are required", KDT_MAX_K);
+    return KDT_EINVAL;
+  }
+  *traversal = knn_traversal(d, n, leaf_size, largest_leaf(n, levels_for(n, leaf_size)), k, 0);
+  return KDT_OK;
+}
 
 extern "C" kdt_status kdt_knn(const kdt_tree* tree, const float* d_q, int64_t nq, int32_t k,
                               int32_t* d_idx, float* d_d2, int32_t kth_only,

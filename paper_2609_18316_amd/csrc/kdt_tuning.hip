@@ -77,8 +77,8 @@ Tuning tuned(int d, int64_t n, int k) {
       bd = dist;
     }
   }
-  if (!best) return Tuning{32, d <= 8 ? 1 : 64};
-  return Tuning{best->leaf, best->qpw};
+  if (!best) return Tuning{32, d <= 8 ? 1 : 64, false};
+  return Tuning{best->leaf, best->qpw, best == &rt};
 }
 
 }  // namespace kdt

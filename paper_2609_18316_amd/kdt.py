@@ -34,7 +34,7 @@ EXPORTS = ("kdt_build", "kdt_free", "kdt_tree_get_info", "kdt_tree_export", "kdt
            "kdt_last_error")
 # The test and measurement hooks of include/kdt_debug.h.
 DEBUG_EXPORTS = ("kdt_debug_fail_alloc", "kdt_debug_fail_memory", "kdt_debug_kept",
-                 "kdt_debug_visits", "kdt_debug_valu_probe",
+                 "kdt_debug_visits", "kdt_debug_knn_traversal", "kdt_debug_valu_probe",
                  "kdt_debug_radix_sort", "kdt_debug_exclusive_scan", "kdt_debug_sort_rows")
 LIB_COUNTS_PATH = os.path.join(HERE, "libkdt_counts.so")
 NOALLOC_MAX_SORTED = 1 << 22   # queries kdt_knn_noalloc can order in its static scratch
@@ -131,6 +131,7 @@ def load(path: str = LIB_PATH):
     lib.kdt_debug_fail_memory.argtypes = [i64]
     lib.kdt_debug_kept.argtypes = [vp, i32, C.POINTER(i64)]
     lib.kdt_debug_visits.argtypes = [vp, i32]
+    lib.kdt_debug_knn_traversal.argtypes = [i32, i64, i32, i32, C.POINTER(i32)]
     lib.kdt_debug_valu_probe.argtypes = [vp, i32, i32, vp]
     lib.kdt_debug_radix_sort.argtypes = [vp, vp, i64, i32, i32, vp]
     lib.kdt_debug_exclusive_scan.argtypes = [vp, vp, i64, i32, vp]
@@ -156,6 +157,14 @@ def tuning_get(d: int, n: int, k: int) -> tuple[int, int, int]:
     _check(load().kdt_tuning_get(int(d), int(n), int(k), C.byref(leaf), C.byref(qpw),
                                  C.byref(depth)))
     return leaf.value, qpw.value, depth.value
+
+
+def knn_traversal(d: int, n: int, leaf_size: int, k: int) -> int:
+    """Test hook: the traversal (1 per lane, 2 shared by a wave) that ``knn`` takes by default
+    on a median tree of that shape."""
+    t = C.c_int32(0)
+    _check(load().kdt_debug_knn_traversal(int(d), int(n), int(leaf_size), int(k), C.byref(t)))
+    return t.value
 
 
 def stream_release(stream=None) -> None:
