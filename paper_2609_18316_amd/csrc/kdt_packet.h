@@ -634,6 +634,9 @@ __device__ __forceinline__ void fill_hits(const FillOut& fo, int64_t row, uint64
 // one load, and only a node that some lane must look inside is ever visited
 // (one box per visit before, the stack filled with nodes yet to be tested; lists of
 // 1000003 balls of 60 points: count and fill 2.42 ms in the first passes, 1.63 now).
+// In launches of small balls it is the scalar work of a visit: a node's range of points is
+// computed where a lane holds it whole or it is a leaf (2^24 self counts of r = 0.002,
+// uniform, 3.51 ms with the range of every node, 3.15 so; 2^22 balls of r = 0.01 3.36 and 3.14).
 //
 // Where the balls of a wave overlap a dense region, a leaf often cuts the
 // surface of only a few of them.  Then the queries that need the leaf are
@@ -680,19 +683,21 @@ __device__ __forceinline__ int64_t packet_range_count(const View& t, const Shape
   int sp = 0, head = 0;                            // entries head .. sp - 1
   uint32_t left = spill.buf ? spill.budget : 0xFFFFFFFFu;  // node visits before handing off
   bool wide = spill.buf && !spill.done && spill.budget <= kWideBudget;
-  // Tests a node (points [b, e), box lo, hi) for the lanes of `live`, counts or lists
+  // Tests node j of level lev (box lo, hi) for the lanes of `live`, counts or lists
   // it for the lanes that hold it whole; returns the lanes that must look inside.
-  const auto test = [&](int64_t b, int64_t e, const Real lo[D], const Real hi[D],
+  const auto test = [&](int lev, int64_t j, const Real lo[D], const Real hi[D],
                         uint64_t live) -> uint64_t {
     KDT_WAVE_VISIT(t, kVisitWaveNodes, 1);
     const bool touch = ((live >> lane) & 1ull) && sh.cuts(lo, hi);
     const uint64_t tm = __ballot(touch);
     if (tm == 0) return 0;
     const bool full = touch && sh.holds_box(lo, hi);
-    if (full) count += e - b;
     uint64_t fm = __ballot(full);
     const uint64_t pm = tm & ~fm;
-    if (FILL && fm != 0) {
+    if (fm == 0) return pm;
+    const int64_t b = node_begin(t.n, lev, j), e = node_begin(t.n, lev, j + 1);
+    if (full) count += e - b;
+    if (FILL) {
       const int64_t at = full ? fill_reserve(fo, row, (int)(e - b)) : 0;
       while (fm) {
         const int l = __ffsll((unsigned long long)fm) - 1;
@@ -709,7 +714,7 @@ __device__ __forceinline__ int64_t packet_range_count(const View& t, const Shape
   Real lo[D], hi[D];
   if (start == 0) {
     load_node_uniform<D>(t, 0, lo, hi);
-    pm = test(0, t.n, lo, hi, pm);
+    pm = test(0, 0, lo, hi, pm);
   }
   for (;;) {
     bool down = false;  // the next node is a child
@@ -717,14 +722,13 @@ __device__ __forceinline__ int64_t packet_range_count(const View& t, const Shape
       if (left != 0) --left;
       const int lev = node_level(node);
       const int64_t j = (int64_t)node - ((int64_t(1) << lev) - 1);
-      const int64_t b = node_begin(t.n, lev, j), e = node_begin(t.n, lev, j + 1);
       if (node < first_leaf) {
         const uint32_t c0 = 2 * node + 1;
         Real lo1[D], hi1[D];
         load_node_uniform<D>(t, c0, lo, hi);
         load_node_uniform<D>(t, c0 + 1, lo1, hi1);
-        const int64_t mid = node_begin(t.n, lev + 1, 2 * j + 1);
-        const uint64_t m0 = test(b, mid, lo, hi, pm), m1 = test(mid, e, lo1, hi1, pm);
+        const uint64_t m0 = test(lev + 1, 2 * j, lo, hi, pm);
+        const uint64_t m1 = test(lev + 1, 2 * j + 1, lo1, hi1, pm);
         if (m1 != 0 && (wide || m0 != 0)) {
           stackv = lane == sp ? c0 + 1 : stackv;
           stk_lo = lane == sp ? (uint32_t)m1 : stk_lo;
@@ -742,7 +746,8 @@ __device__ __forceinline__ int64_t packet_range_count(const View& t, const Shape
         pm = m0 != 0 ? m0 : m1;
       } else {
         const bool part = (pm >> lane) & 1ull;
-        const int cnt = (int)(e - b);
+        const int64_t b = node_begin(t.n, lev, j);
+        const int cnt = (int)(node_begin(t.n, lev, j + 1) - b);
         leaf.open(b, cnt);
         KDT_WAVE_VISIT(t, kVisitWavePoints, cnt);
         const int na = __popcll(pm);

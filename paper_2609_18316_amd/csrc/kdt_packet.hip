@@ -19,14 +19,22 @@ constexpr int kPWaves = 4;  // waves per workgroup (independent packets)
 // waves hand on at once, since most of the chip is idle (50021 queries, k = 1000 of
 // 2^23 clustered points: 15.5 ms with 8 depth-first passes of 512 and 32 visits
 // of one node; 14.3 with 256 and 16 of two nodes, 11.7 widest first, 10.2 with 24 and
-// 24); in large ones ordinary waves must not reach the budget (2^22 uniform balls,
-// r = 0.01, of 2^24 uniform points: 4.29, 3.63 and 3.56 ms with 192, 320 and 384; lists of
-// 1000003 balls of clustered points 4.68, 4.98 and 5.22).
+// 24), unless the balls are small (131072 balls of 2 of 65536 points, us with the few
+// waves' budget and without: 212 / 90); in large ones ordinary waves must not reach the budget
+// (2^22 uniform balls, r = 0.01, of 2^24 uniform points: 4.29, 3.63 and 3.56 ms with 192, 320
+// and 384; lists of 1000003 balls of clustered points 4.68, 4.98 and 5.22).  Where a pass has
+// so many tasks that the chip stays full, cutting them into parts only fills the list, and a
+// task that finds no room runs to its end whatever its size: there a task keeps
+// kRangeManyBudget visits (131073 balls of r = 0.3 of 2^22 uniform points, ms: 18.6 with
+// 8 depth-first passes, 22.5 without this rule, 18.6 so; clustered 14.8, 17.3, 13.8; lists of
+// 1000003 balls 4.73 and 4.75).
 constexpr int kRangePasses = 5;
 constexpr uint32_t kRangeBudgetFirst = 320;
-constexpr uint32_t kRangeBudget = 8;
-constexpr int64_t kRangeFewWaves = 2048;  // up to here:
+constexpr uint32_t kRangeBudget = 10;
+constexpr int64_t kRangeFewWaves = 512;   // up to here:
 constexpr uint32_t kRangeBudgetFew = 24;  // both budgets
+constexpr uint32_t kRangeManyTasks = 300000;  // from here on:
+constexpr uint32_t kRangeManyBudget = 96;     // the later budget
 constexpr uint32_t kRangeTaskCap = 1u << 20;
 // Task slots per wave of the first pass, where that is fewer (launches below 2^16
 // queries): the lists' 67 MB for 2^20 slots are far more than a small call's own data.
@@ -40,10 +48,20 @@ constexpr int64_t kRangeTailWaves = 4096;
 
 // Up to this many shapes are counted by a wave each (wave_ball), above (and from d = 16
 // on, where a ball cuts most nodes) by the wave-shared traversal of 64 shapes, whose few
-// waves leave the chip idle in smaller launches.  Ball counts, shared and by wave: 1000
-// balls of 1000 points 59 and 13 us, 65536 of 65536 146 and 100, 130000 of 2^20 433 and
-// 370, 250000 433 and 585; d = 8, 100000 of 2^18 1771 and 655.
-constexpr int64_t kWaveRows = int64_t(1) << 17;
+// waves leave the chip idle in smaller launches.  A wave's search has a fixed cost of its own
+// that a shared traversal of small balls in a small tree, above all in 2 dimensions, does
+// not; the larger the tree and the higher the dimension, the longer the shared one.
+// Ball counts, shared and by wave, us (balls of 30 points unless said): 1000 balls of 1000
+// points 78 and 14; 65536 of 65536 169 and 107; 131072 of 4096 points 74 and 142, of 65536 120
+// and 196, of 2^20 371 and 255; d = 2, 65536 of 65536 points 66 and 95, 131072 of 2^20 146 and
+// 237; d = 4, 131072 of 65536 points 302 and 221; d = 8, 65536 of 300 points 77 and 87, 131072
+// of 1000 139 and 192, of 16384 858 and 376.
+inline int64_t wave_rows(int d, int64_t n) {
+  constexpr int64_t rows = int64_t(1) << 16;
+  if (d == 2) return n >= (1 << 18) ? rows : rows / 2;
+  const int64_t large = d == 3 ? 1 << 18 : d == 4 ? 1 << 16 : 1 << 12;
+  return n >= large ? 2 * rows : d == 8 ? rows / 2 : rows;
+}
 // The balls of large k hold many points: the 7 counts of 50021 balls of 2^23 clustered
 // points took 4.0 ms and take 1.05; kNN with k = 100, 262000 queries 4.86 and 3.94 ms,
 // 2^20 (k = 128) 13.7 and 15.1; d = 16, 5000: 50.6 and 54.0.
@@ -119,7 +137,7 @@ __global__ __launch_bounds__(64 * kPWaves) void k_knn_packet(TreeView t, const f
 // points, and one squared radius) or boxes (corners).
 template <int D, class V = TreeView>
 struct BallQueries {
-  static constexpr int64_t kWaveMax = kWaveRows;
+  static constexpr bool kLarge = false;  // kWaveRowsLarge
   using View = V;
   using Real = typename View::Real;
   using Shape = BallShape<D, Real>;
@@ -134,7 +152,7 @@ struct BallQueries {
 
 template <int D>
 struct TorusBallQueries {
-  static constexpr int64_t kWaveMax = kWaveRows;
+  static constexpr bool kLarge = false;  // kWaveRowsLarge
   using View = TreeView;
   using Shape = TorusBallShape<D>;
   const float* q;  // [nq][D], or nullptr: the tree's own points
@@ -150,7 +168,7 @@ struct TorusBallQueries {
 
 template <int D, class Metric>
 struct VarBallQueries {
-  static constexpr int64_t kWaveMax = kWaveRowsLarge;
+  static constexpr bool kLarge = true;
   using View = TreeView;
   using Shape = VarBallShape<D, Metric>;
   const float* q;   // [rows][D]
@@ -167,7 +185,7 @@ struct VarBallQueries {
 
 template <int D>
 struct BoxQueries {
-  static constexpr int64_t kWaveMax = kWaveRows;
+  static constexpr bool kLarge = false;  // kWaveRowsLarge
   using View = TreeView;
   using Shape = BoxShape<D>;
   const float* lo;  // [nq][D]
@@ -228,16 +246,19 @@ __global__ __launch_bounds__(64 * kPWaves)
 }
 
 // A later pass: each wave takes tasks left by the previous pass (a fixed
-// count, read at start, so every wave's loop ends) and adds its counts.
+// count, read at start, so every wave's loop ends) and adds its counts.  given: the budget is
+// the caller's.
 template <int D, class Q, bool FILL>
 __global__ __launch_bounds__(64 * kPWaves) void k_count_tasks(
     typename Q::View t, Q src, int64_t nq, const int32_t* __restrict__ order,
     int32_t* __restrict__ count, int leaf_cap, const PacketTask* __restrict__ in,
-    const uint32_t* __restrict__ in_count, uint32_t in_cap, PacketSpill spill, FillOut fo) {
+    const uint32_t* __restrict__ in_count, uint32_t in_cap, PacketSpill spill, FillOut fo,
+    bool given) {
   extern __shared__ __align__(16) char count_lds[];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const uint32_t n = min(*in_count, in_cap);
   auto* slice = count_slice<D, Q>(count_lds, wave, leaf_cap);
+  if (!given && n >= kRangeManyTasks) spill.budget = kRangeManyBudget;
   for (uint32_t k = blockIdx.x * kPWaves + wave; k < n; k += gridDim.x * kPWaves) {
     const PacketTask task = in[k];
     if (task.node == kNoNode) continue;
@@ -393,7 +414,7 @@ static kdt_status count_packet_launch(const typename Q::View& v, int leaf, Q src
                                       uint32_t split_budget, hipStream_t stream,
                                       const char* who, const FillOut* fill = nullptr) {
   if constexpr (std::is_same_v<typename Q::View, TreeView> && D <= 8) {
-    if (!fill && split_budget == 0 && nq <= Q::kWaveMax) {
+    if (!fill && split_budget == 0 && nq <= (Q::kLarge ? kWaveRowsLarge : wave_rows(D, v.n))) {
       int cap = 0;
       const TreeView w = coarse_view(v, leaf, kWaveLeafCap, &cap);
       const size_t slice = wave_ball_bytes(w.levels);
@@ -446,10 +467,12 @@ static kdt_status count_packet_launch(const typename Q::View& v, int leaf, Q src
     const PacketTask* in = tasks + (size_t)(pass - 1) * cap;
     if (fill)
       k_count_tasks<D, Q, true><<<kRangeTaskBlocks, 64 * kPWaves, smem, stream>>>(
-          v, src, nq, order, d_count, leaf, in, counts + pass - 1, cap, out, fo);
+          v, src, nq, order, d_count, leaf, in, counts + pass - 1, cap, out, fo,
+          split_budget != 0);
     else
       k_count_tasks<D, Q, false><<<kRangeTaskBlocks, 64 * kPWaves, smem, stream>>>(
-          v, src, nq, order, d_count, leaf, in, counts + pass - 1, cap, out, fo);
+          v, src, nq, order, d_count, leaf, in, counts + pass - 1, cap, out, fo,
+          split_budget != 0);
   }
   if (hipGetLastError() != hipSuccess) {
     kdt_set_error("%s: packet kernel launch failed", who);

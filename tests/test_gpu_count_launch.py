@@ -1,0 +1,48 @@
+"""Ball counts on both sides of the numbers of balls, by dimension and tree, up to which each
+ball is searched by a wave of its own, and a launch with more hand-offs than the list of tasks
+wants: equal to one traversal per lane, and a sample to the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2609_18316_amd import kdt
+from tests.gpu_util import dev, say, to_dev, to_host
+
+pytestmark = pytest.mark.gpu
+
+ROWS = 1 << 16
+
+
+@pytest.mark.parametrize("d,n,nq", [
+    (2, (1 << 18) - 1, ROWS // 2), (2, 1 << 18, ROWS), (3, (1 << 18) - 1, ROWS),
+    (3, 1 << 18, 2 * ROWS), (4, ROWS - 1, ROWS), (4, ROWS, 2 * ROWS), (8, 4095, ROWS // 2),
+    (8, 4096, 2 * ROWS), (3, 1, ROWS), (16, 300, ROWS // 2),
+])
+def test_counts_by_launch_size(d, n, nq):
+    dev()
+    rng = np.random.Generator(np.random.PCG64(n + nq))
+    x = rng.random((n, d)).astype(np.float32)
+    q = rng.random((nq + 1, d)).astype(np.float32)
+    r = 0.6 * (20 / max(n, 40)) ** (1 / d)
+    t = kdt.build(to_dev(x), leaf_size=24)
+    for m in (nq, nq + 1):
+        say(f"counts d={d} n={n} nq={m}")
+        got = to_host(t.range(to_dev(q[:m]), r))
+        np.testing.assert_array_equal(got, to_host(t.range(to_dev(q[:m]), r, traversal=1)))
+        some = np.concatenate([[0, m - 1], rng.integers(0, m, 100)])
+        np.testing.assert_array_equal(got[some], oracle.range_brute(x, q[some], r))
+
+
+def test_counts_with_many_hand_offs():
+    dev()
+    rng = np.random.Generator(np.random.PCG64(4))
+    n, nq = 1 << 22, 2 * ROWS + 1
+    x = rng.random((n, 3)).astype(np.float32)
+    q = rng.random((nq, 3)).astype(np.float32)
+    t = kdt.build(to_dev(x), leaf_size=24)
+    say("counts with many hand-offs")
+    got = to_host(t.range(to_dev(q), 0.3))
+    some = rng.integers(0, nq, 12)
+    np.testing.assert_array_equal(got[some], oracle.range_brute(x, q[some], 0.3))
+    # a budget for every wave: no rule on the number of tasks
+    np.testing.assert_array_equal(got, to_host(t.range(to_dev(q), 0.3, split_budget=400)))
