@@ -644,9 +644,21 @@ struct ListMerge<TopD<KC>, D> {
 };
 // Waves per SIMD that a per-lane kNN kernel is compiled for: its list with a
 // batch takes 128 VGPRs, which the compiler reaches only when asked to.
-template <int D, int KC, bool KTH, class Shape = MedianShape>
+template <int D, int KC, bool KTH, class Shape = MedianShape, bool kMerge = true>
 constexpr int lane_waves() {
-  return !KTH && std::is_same_v<Shape, MedianShape> && ListMerge<TopK<KC>, D>::kOn ? 4 : 1;
+  return !KTH && kMerge && std::is_same_v<Shape, MedianShape> && ListMerge<TopK<KC>, D>::kOn ? 4
+                                                                                             : 1;
+}
+// Where a list that can merge does (most: points of the largest leaf): everywhere but in
+// 4 dimensions on large trees whose leaves take more than one batch -- few of their points
+// are candidates.  All points as queries, us merging / inserting / inserting before the vote:
+// 400000 points, leaves of 32, k = 24 1058 / 823 / 1002, k = 32 1196 / 945 / 1135, leaves
+// of 16 1039 / 992 / 1143; 2 * 10^6 points, leaves of 64, k = 32 5839 / 4251 / 6682; below the
+// line the two are closer and cross: 100000 points, leaves of 32 462 / 420 / 496, of 16 428 / 474
+// / 498 (queries of their own), 4000 points 257 / 307 / 341.
+template <int D>
+inline bool lane_merges(int most, int64_t n) {
+  return D != 4 || most <= kListBatch || n < (1 << 18);
 }
 // The list length of k for kNN over n points with one traversal per lane: k
 // rounded up, except that a merge reads kListBatch consecutive points, so
@@ -664,8 +676,8 @@ inline int lane_list(int k, int64_t n) {
 // 1019 / 948.
 inline bool lane_default(int d, int k, int most) { return d <= 4 && (most <= 32 || k > 16); }
 
-// Offers the cnt points from b on, a lane's leaf, to its list; most: no leaf
-// of the tree is larger (wave-uniform).  Without kMerge, in two passes per 32
+// Offers the cnt points from b on, a lane's leaf, to its list; least, most: no leaf
+// of the tree is smaller or larger (wave-uniform).  Without kMerge, in two passes per 32
 // points: the first computes every distance and marks the points that can
 // enter the list (float test against the current k-th distance, ties kept);
 // the second inserts the marked points, recomputing their distances.  The
@@ -676,10 +688,11 @@ inline bool lane_default(int d, int k, int most) { return d <= 4 && (most <= 32 
 // short rest of a leaf (at most kFewPoints: smoothing lengths on leaves of 20 points
 // 3.00 against 3.52 ms, 5000011 points) and where no lane has many candidates.
 template <int D, bool kMerge, class Space, class List>
-__device__ __forceinline__ void leaf_offer(const Space& sp, int32_t b, int cnt, int most,
+__device__ __forceinline__ void leaf_offer(const Space& sp, int32_t b, int cnt, int least, int most,
                                            const typename Space::Coord p[D], List& best) {
   constexpr int B = kMerge ? kListBatch : 32;
   constexpr int kFewPoints = 8;
+  constexpr int kAhead = D > 4 ? 4 : 2;
   for (int o = 0; o < cnt; o += B) {
     const typename Space::Dist w = best.worst_d2();
     const int m = min(cnt - o, B);
@@ -718,8 +731,14 @@ __device__ __forceinline__ void leaf_offer(const Space& sp, int32_t b, int cnt, 
       }
     } else {
       const auto* r = sp.run(c);
+      const int all = min(max(least - o, 0), B);  // every lane has these
+#pragma unroll kAhead
+      for (int i = 0; i < all; ++i) {
+        int32_t id = 0;
+        mask |= (uint32_t)(sp.dist(r, c, i, p, id) <= w) << i;
+      }
 #pragma unroll 1
-      for (int i = 0; i < m; ++i) {
+      for (int i = all; i < m; ++i) {
         int32_t id = 0;
         mask |= (uint32_t)(sp.dist(r, c, i, p, id) <= w) << i;
       }
@@ -761,6 +780,8 @@ __device__ __forceinline__ void knn_median(const Space& sp, const typename Space
   const auto& t = sp.t;
   constexpr int kWait = D > 4 ? 2 : kMerge ? 4 : 6;
   const uint32_t first = 1u << t.levels;
+  // every leaf holds lmin points or one more
+  const int lmin = (int)(t.n >> t.levels);
   const int lmax = (int)((t.n + (int64_t(1) << t.levels) - 1) >> t.levels);
   uint32_t h = 1;     // 1-based heap id of the lane's node (children 2h, 2h + 1)
   uint32_t pend = 0;  // bit l: the sibling of the path's level-l node waits
@@ -781,7 +802,7 @@ __device__ __forceinline__ void knn_median(const Space& sp, const typename Space
         const int32_t b = (int32_t)((j * t.n) >> t.levels);
         const int32_t e = (int32_t)(((j + 1) * t.n) >> t.levels);
         KDT_LANE_VISIT(t, kVisitPoints, e - b);
-        leaf_offer<D, kMerge>(sp, b, e - b, lmax, p, best);
+        leaf_offer<D, kMerge>(sp, b, e - b, lmin, lmax, p, best);
         pop = true;
       }
     } else if (!leaf) {
@@ -838,7 +859,7 @@ __device__ __forceinline__ void knn_one(const TreeView& t, const float p[D], Lis
         int64_t b, e;
         sh.range(node, b, e);
         KDT_LANE_VISIT(t, kVisitPoints, e - b);
-        leaf_offer<D, false>(space, (int32_t)b, (int)(e - b), 0, p, best);
+        leaf_offer<D, false>(space, (int32_t)b, (int)(e - b), 0, 0, p, best);
       } else {
         const uint32_t c0 = sh.left(node), c1 = c0 + 1;
         KDT_LANE_VISIT(t, kVisitNodes, 2);

@@ -27,13 +27,11 @@ constexpr int kQBlock = 128;
 // The per-lane stack lives in LDS, (levels + 1) entries per lane (the tree
 // depth bounds it: one pending sibling per level), sized at launch.  KTH:
 // only the k-th distance is written (modes 1 and 2), kept in a TopD list.
-template <int D, int KC, bool KTH, class Shape = MedianShape>
+template <int D, int KC, bool KTH, class Shape = MedianShape, bool kMerge = true>
 __global__ __launch_bounds__(kQBlock)
-__attribute__((amdgpu_waves_per_eu(lane_waves<D, KC, KTH, Shape>()))) void k_knn_lane(TreeView t, const float* __restrict__ q,
-                                                      int64_t nq, int k,
-                                                      const int32_t* __restrict__ order, int mode,
-                                                      int32_t* __restrict__ oidx,
-                                                      float* __restrict__ od2) {
+__attribute__((amdgpu_waves_per_eu(lane_waves<D, KC, KTH, Shape, kMerge>()))) void k_knn_lane(
+    TreeView t, const float* __restrict__ q, int64_t nq, int k, const int32_t* __restrict__ order,
+    int mode, int32_t* __restrict__ oidx, float* __restrict__ od2) {
   extern __shared__ uint32_t stk_dyn[];
   const int64_t s = xcd_block<kXcdRunLane>() * kQBlock + threadIdx.x;
   if (s >= nq) return;
@@ -52,12 +50,12 @@ __attribute__((amdgpu_waves_per_eu(lane_waves<D, KC, KTH, Shape>()))) void k_knn
   if constexpr (KTH) {
     TopD<KC> best;
     best.init(k);
-    knn_one<D, true, Shape>(t, p, best, stk_dyn + threadIdx.x, kQBlock);
+    knn_one<D, kMerge, Shape>(t, p, best, stk_dyn + threadIdx.x, kQBlock);
     knn_write_kth<KC>(best, mode, row, od2);
   } else {
     TopK<KC> best;
     best.init(k);
-    knn_one<D, true, Shape>(t, p, best, stk_dyn + threadIdx.x, kQBlock);
+    knn_one<D, kMerge, Shape>(t, p, best, stk_dyn + threadIdx.x, kQBlock);
     knn_write<KC>(best, k, mode, row, oidx, od2);
   }
 }
@@ -317,6 +315,11 @@ static kdt_status order_queries(const kdt_tree* t, const float* d_q, int64_t nq,
   return KDT_OK;
 }
 
+// Points of the largest leaf of a median tree.
+static int largest_leaf(int64_t n, int levels) {
+  return (int)((n + (int64_t(1) << levels) - 1) >> levels);
+}
+
 template <int D>
 static kdt_status knn_dispatch(const kdt_tree* t, const float* d_q, int64_t nq, int k,
                                int32_t* d_idx, float* d_d2, int mode, const int32_t* order,
@@ -346,6 +349,15 @@ static kdt_status knn_dispatch(const kdt_tree* t, const float* d_q, int64_t nq, 
   } else {                      \
     KDT_LANE_S(KC, MedianShape) \
   }
+  if constexpr (D == 4) {
+    if (lane_list(k, t->n) == 32 && mode == 0 && !t->nodes &&
+        !lane_merges<D>(largest_leaf(t->n, t->levels), t->n)) {
+      k_knn_lane<D, 32, false, MedianShape, false><<<grid, kQBlock, smem, stream>>>(
+          v, d_q, nq, k, order, mode, d_idx, d_d2);
+      KDT_HIP(hipGetLastError());
+      return KDT_OK;
+    }
+  }
   switch (lane_list(k, t->n)) {
     case 8: KDT_LANE(8) break;
     case 16: KDT_LANE(16) break;
@@ -365,9 +377,6 @@ static int knn_traversal(int d, int64_t n, int leaf, int most, int k, int asked)
   if (asked != 0) return asked;
   const Tuning t = tuned(d, n, k);
   return t.qpw == 64 && (t.set || !lane_default(d, k, most)) ? 2 : 1;
-}
-static int largest_leaf(int64_t n, int levels) {
-  return (int)((n + (int64_t(1) << levels) - 1) >> levels);
 }
 
 // ws: optional workspace for the query order (then nothing is allocated).
