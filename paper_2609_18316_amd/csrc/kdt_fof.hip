@@ -89,9 +89,9 @@ static kdt_status fof_launch(const TreeView& v, int leaf, int64_t n_nodes, float
     return KDT_EDEVICE;
   }
   if (leaf <= 64) {
-    // nodes of up to 32 points serve as leaves, as for the counts
-    int cap = 0;
-    const TreeView vc = count_view(v, leaf, &cap);
+    // nodes of up to 32 points serve as leaves, as for the counts (not in 16 dimensions)
+    int cap = leaf;
+    const TreeView vc = D > 8 ? v : count_view(v, leaf, &cap);
     return fof_packet_launch<D>(vc, cap, l2, labels, conn, stream);
   }
   k_fof_link<D><<<gl, kFBlock, 0, stream>>>(v, l2, labels, conn);

@@ -849,6 +849,11 @@ __host__ __device__ constexpr size_t fof_wave_floats(int leaf) {
 // This kernel on 2^24 clustered points: 9.3 ms before; 7.2 by the climb and
 // cached loads (uf_ld), 6.3 with the sets found side by side, 6.0 with
 // 32-point nodes as leaves.
+// In 16 dimensions two boxes do not fit the scalar registers, every bound is 32 to 48
+// instructions and leaves outnumber inner nodes, so there a node is tested when it is
+// taken from the stack, its clique flag is read and the tree's own leaves stay (20000 uniform
+// points, leaves of 32, b = 0.5, us: 4350 at first, 4708 with both boxes, 4381 so; normal points
+// on leaves of 16 1119, 1354 and 965).
 template <int D, class Metric = OpenMetric<D>>
 __device__ __forceinline__ void packet_fof(const TreeView& t, const float p[D], int64_t pos,
                                            int32_t me, bool active, float l2, int32_t base,
@@ -856,6 +861,7 @@ __device__ __forceinline__ void packet_fof(const TreeView& t, const float p[D], 
                                            uint32_t* __restrict__ conn, float* lds,
                                            int leaf_cap, const Metric& metric = Metric()) {
   constexpr int S = rec_stride(D);
+  constexpr bool kBothBoxes = D <= 8;
   const int lane = lane_id();
   const uint32_t first_leaf = (1u << t.levels) - 1u;
   int32_t myroot = base + me;  // an ancestor of this lane's point (see uf_union_from)
@@ -884,9 +890,12 @@ __device__ __forceinline__ void packet_fof(const TreeView& t, const float p[D], 
     j = (int64_t)node - ((int64_t(1) << lev) - 1);
     const int64_t b = node_begin(t.n, lev, j), e = node_begin(t.n, lev, j + 1);
     bool touch = (live >> lane) & 1ull;
-    bool full = touch && metric.maxdist(lo, hi, p) <= l2;
-    bool one = box_diag2<D>(lo, hi) <= l2;
+    bool full = false;
+    if (kBothBoxes) full = touch && metric.maxdist(lo, hi, p) <= l2;
+    // (a clique's flag is set too, but takes a load)
+    bool one = kBothBoxes && box_diag2<D>(lo, hi) <= l2;
     if (!one) one = flag_ld(conn + node) != 0;
+    if (!kBothBoxes) full = touch && metric.maxdist(lo, hi, p) <= l2;
     if (one || __any(full)) {
       const int32_t gfirst = base + __float_as_int(t.rec[b * S + D]);
       if (one) {
@@ -951,39 +960,50 @@ __device__ __forceinline__ void packet_fof(const TreeView& t, const float p[D], 
         }
       } else {
         const uint32_t c0 = 2 * node + 1;
-        float lo1[D], hi1[D];
-        load_box_uniform<D>(t.box, c0, lo, hi);
-        load_box_uniform<D>(t.box, c0 + 1, lo1, hi1);
         const int64_t mid = node_begin(t.n, lev + 1, 2 * j + 1);
-        const uint64_t m0 = __ballot(part && mid > pos && metric.mindist(lo, hi, p) <= l2);
-        const uint64_t m1 = __ballot(part && e > pos && metric.mindist(lo1, hi1, p) <= l2);
-        if (m1 != 0) {
-          if (m0 != 0) {
-            stackv = lane == sp ? c0 + 1 : stackv;
-            stk_lo = lane == sp ? (uint32_t)m1 : stk_lo;
-            stk_hi = lane == sp ? (uint32_t)(m1 >> 32) : stk_hi;
-            ++sp;
-          } else {
+        const auto push = [&](uint32_t c, uint64_t m) {
+          stackv = lane == sp ? c : stackv;
+          stk_lo = lane == sp ? (uint32_t)m : stk_lo;
+          stk_hi = lane == sp ? (uint32_t)(m >> 32) : stk_hi;
+          ++sp;
+        };
+        if constexpr (kBothBoxes) {
+          float lo1[D], hi1[D];
+          load_box_uniform<D>(t.box, c0, lo, hi);
+          load_box_uniform<D>(t.box, c0 + 1, lo1, hi1);
+          const uint64_t m0 = __ballot(part && mid > pos && metric.mindist(lo, hi, p) <= l2);
+          const uint64_t m1 = __ballot(part && e > pos && metric.mindist(lo1, hi1, p) <= l2);
+          if (m1 != 0) {
+            if (m0 != 0) {
+              push(c0 + 1, m1);
+            } else {
 #pragma unroll
-            for (int a = 0; a < D; ++a) lo[a] = lo1[a], hi[a] = hi1[a];
+              for (int a = 0; a < D; ++a) lo[a] = lo1[a], hi[a] = hi1[a];
+            }
           }
-        }
-        if ((m0 | m1) != 0) {
-          node = m0 != 0 ? c0 : c0 + 1;
-          live = m0 != 0 ? m0 : m1;
-          down = true;
+          if ((m0 | m1) != 0) {
+            node = m0 != 0 ? c0 : c0 + 1;
+            live = m0 != 0 ? m0 : m1;
+            down = true;
+          }
+        } else {
+          push(c0 + 1, __ballot(part));
+          const uint64_t m0 = __ballot(part && mid > pos);
+          if (m0 != 0) push(c0, m0);
         }
       }
     }
     if (down) continue;
-    if (sp > 0) {
+    live = 0;
+    while (sp > 0 && live == 0) {
       --sp;
       node = (uint32_t)__builtin_amdgcn_readlane((int)stackv, sp);
       live = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)stk_hi, sp) << 32) |
              (uint32_t)__builtin_amdgcn_readlane((int)stk_lo, sp);
       load_box_uniform<D>(t.box, node, lo, hi);
-      continue;
+      if (!kBothBoxes) live &= __ballot(metric.mindist(lo, hi, p) <= l2);
     }
+    if (live != 0) continue;
     // up the path: the next later sibling within reach
     live = 0;
     while (path != 0 && live == 0) {

@@ -462,8 +462,8 @@ static kdt_status torus_fof_impl(const kdt_tree* tr, float l, const float* perio
       tr->box, tr->n_nodes, l2, clique);
   k_torus_clique_join<D><<<g, 256, 0, stream>>>(v, clique, d_labels);
   if (tr->leaf <= 64) {
-    int cap = 0;
-    const TreeView vc = count_view(v, tr->leaf, &cap);
+    int cap = tr->leaf;
+    const TreeView vc = D > 8 ? v : count_view(v, tr->leaf, &cap);
     st = torus_fof_packet_launch<D>(vc, cap, l2, T, d_labels, clique, stream);
     if (st != KDT_OK) return st;
   } else {
