@@ -329,16 +329,21 @@ __global__ __launch_bounds__(kF64Block) void k_knn64(View64 v, const double* __r
 }
 
 // Closed-ball counts (FILL false) or lists (FILL true: the input indices of
-// row `row` written from offsets[row] on, in traversal order).
+// row `row` written from offsets[row] on, in traversal order).  apart: only the waves
+// that the wave-shared counts leave out.
 template <int D, bool FILL, typename Shape>
 __global__ __launch_bounds__(kF64Block) void k_range64(View64 v, const double* __restrict__ q,
                                                        int64_t nq, double r2,
                                                        const int32_t* __restrict__ order,
                                                        int32_t* __restrict__ count,
                                                        const int64_t* __restrict__ offsets,
-                                                       int32_t* __restrict__ out, int depth) {
+                                                       int32_t* __restrict__ out, int depth,
+                                                       bool apart) {
   extern __shared__ uint32_t stk[];
   const int64_t i = (int64_t)blockIdx.x * kF64Block + threadIdx.x;
+  if constexpr (!FILL && D <= 4) {
+    if (apart && lie_together<D>(q, nq, (int64_t)blockIdx.x * kF64Block)) return;
+  }
   if (i >= nq) return;
   double qq[D];
   const int64_t row = load_query64<D>(v, q, order, i, qq);
@@ -396,6 +401,18 @@ kdt_status by_dim(int d, F&& f) {
 // Stack entries a traversal can hold: the depth-first kNN keeps one pending
 // sibling per level, the ball traversal two children per level.
 int stack_depth(const kdt_tree* t) { return 2 * (t->levels + 1) + 2; }
+
+// Above so many external queries in input order, on trees of at least so many points and in up
+// to 4 dimensions, waves of queries that do not lie together take a traversal per lane:
+// shared, 64 strangers visit the union of their paths.
+// Balls of 50 points, us per lane / shared / so: 300000 in random order of 300000 uniform points
+// 1606 / 3839 / 1641, 10^6 of 2000003 4828 / 10673 / 4944; in the order of a curve
+// 877 / 318 / 329.  Few queries in a large clustered tree are the exception (65536 in random order
+// of 2000003 points 3378 / 1048 / 3162: the lanes wait for the halos).  Below the lines the shared
+// ones win in any order (100000 of 1000 points 230 / 184, 20000 of 300000 610 / 478; d = 8, 65536
+// of 20000 5828 / 1223).
+constexpr int64_t kUnsortedRows = int64_t(1) << 15;
+constexpr int64_t kUnsortedPoints = int64_t(1) << 13;
 
 // The query order (Hilbert curve over the root box, d <= 4; tree leaf
 // otherwise), taken from the float32 rounding of the queries.
@@ -628,31 +645,38 @@ extern "C" kdt_status kdt_range_f64(const kdt_tree* tree, const double* d_q, int
   // leaves and packed queries of a workgroup the 64 KiB of LDS a launch gets
   // (16 dimensions: leaves of up to 56 points).
   int cap = 0;
-  const View64 vc = count_view(v, tree->leaf, &cap);
+  // (a stored tree's depth is no shift: it may pass 64)
+  const View64 vc = tree->nodes ? v : count_view(v, tree->leaf, &cap);
   const bool shared = !tree->nodes && cap <= 64 && range64_packet_lds(tree->d, cap) <= 65536;
+  const bool apart = shared && d_q && !order && !d_offsets && nq > kUnsortedRows &&
+                     v.n >= kUnsortedPoints && tree->d <= 4;
   int32_t* cur = nullptr;
   auto launch = [&](bool fill, int32_t* out) {
     return by_dim(tree->d, [&](auto dd) -> kdt_status {
       constexpr int D = decltype(dd)::value;
       if (shared) {
         const FillOut fo{out, d_offsets, cur};
-        return range64_packet_launch<D>(vc, cap, d_q, nq, r2, order, d_count, stream,
-                                        fill ? &fo : nullptr);
+        const kdt_status st = range64_packet_launch<D>(vc, cap, d_q, nq, r2, order, d_count,
+                                                       stream, fill ? &fo : nullptr, apart);
+        if (st != KDT_OK || !apart) return st;
+        k_range64<D, false, MedianShape><<<g, kF64Block, smem, stream>>>(
+            v, d_q, nq, r2, order, d_count, d_offsets, out, depth, true);
+        return hipGetLastError() == hipSuccess ? KDT_OK : KDT_EDEVICE;
       }
       if (tree->nodes) {
         if (fill)
           k_range64<D, true, StoredShape><<<g, kF64Block, smem, stream>>>(
-              v, d_q, nq, r2, order, d_count, d_offsets, out, depth);
+              v, d_q, nq, r2, order, d_count, d_offsets, out, depth, false);
         else
           k_range64<D, false, StoredShape><<<g, kF64Block, smem, stream>>>(
-              v, d_q, nq, r2, order, d_count, d_offsets, out, depth);
+              v, d_q, nq, r2, order, d_count, d_offsets, out, depth, false);
       } else {
         if (fill)
           k_range64<D, true, MedianShape><<<g, kF64Block, smem, stream>>>(
-              v, d_q, nq, r2, order, d_count, d_offsets, out, depth);
+              v, d_q, nq, r2, order, d_count, d_offsets, out, depth, false);
         else
           k_range64<D, false, MedianShape><<<g, kF64Block, smem, stream>>>(
-              v, d_q, nq, r2, order, d_count, d_offsets, out, depth);
+              v, d_q, nq, r2, order, d_count, d_offsets, out, depth, false);
       }
       return hipGetLastError() == hipSuccess ? KDT_OK : KDT_EDEVICE;
     });

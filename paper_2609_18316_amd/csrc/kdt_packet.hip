@@ -143,6 +143,7 @@ struct BallQueries {
   using Shape = BallShape<D, Real>;
   const Real* q;  // [nq][D], or nullptr: the tree's own points
   Real r2;
+  bool apart = false;  // float64: only waves whose queries lie together
   __device__ __forceinline__ bool load(const View& t, int64_t nq, const int32_t* order,
                                        int64_t s, Shape& sh, int64_t& row) const {
     sh.r2 = r2;
@@ -235,6 +236,12 @@ __global__ __launch_bounds__(64 * kPWaves)
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int64_t s0 = (xcd_block<kXcdRunPacket>() * kPWaves + wave) * 64;
   if (s0 >= nq) return;
+  if constexpr (std::is_same_v<typename Q::View, View64> && !FILL && D <= 4) {
+    if (src.apart && !lie_together<D>(src.q, nq, s0)) {
+      wave_done(spill);
+      return;
+    }
+  }
   typename Q::Shape sh;
   int64_t row = 0;
   const bool active = src.load(t, nq, order, s0 + lane, sh, row);
@@ -492,9 +499,9 @@ kdt_status range_packet_launch(const TreeView& v, int leaf, const float* d_q, in
 template <int D>
 kdt_status range64_packet_launch(const View64& v, int leaf, const double* d_q, int64_t nq,
                                  double r2, const int32_t* order, int32_t* d_count,
-                                 hipStream_t stream, const FillOut* fill) {
-  return count_packet_launch<D>(v, leaf, BallQueries<D, View64>{d_q, r2}, nq, order, d_count, 0u,
-                                stream, "kdt_range_f64", fill);
+                                 hipStream_t stream, const FillOut* fill, bool apart) {
+  return count_packet_launch<D>(v, leaf, BallQueries<D, View64>{d_q, r2, apart}, nq, order,
+                                d_count, 0u, stream, "kdt_range_f64", fill);
 }
 
 template <int D>
@@ -538,7 +545,7 @@ size_t range64_packet_lds(int d, int leaf) {
                                              const FillOut*);                                    \
   template kdt_status range64_packet_launch<D>(const View64&, int, const double*, int64_t, double, \
                                                const int32_t*, int32_t*, hipStream_t,            \
-                                               const FillOut*);                                  \
+                                               const FillOut*, bool);                            \
   template kdt_status box_packet_launch<D>(const TreeView&, int, const float*, const float*,       \
                                            int64_t, const int32_t*, int32_t*, uint32_t,          \
                                            hipStream_t, const FillOut*);                         \

@@ -1165,15 +1165,40 @@ kdt_status knn_in_workspace(const kdt_tree* t, const float* d_q, int64_t nq, int
                             int32_t* d_idx, float* d_d2, int mode, const KnnArgs& a, void* ws,
                             size_t ws_bytes, hipStream_t stream);
 
+// Whether the 64 queries from s0 on (input order; all lanes call) lie together: the box around
+// them has at most 1/16 of the volume of the box around 64 queries from all of the input.
+// Queries along any curve stay below 1 %, those in random order above half.
+template <int D>
+__device__ __forceinline__ bool lie_together(const double* __restrict__ q, int64_t nq,
+                                             int64_t s0) {
+  const int lane = threadIdx.x & 63;
+  const int64_t mine = min(s0 + lane, nq - 1), far = nq / 64 * lane;
+  double own = 1.0, all = 1.0;
+  for (int a = 0; a < D; ++a) {
+    double lo[2] = {q[mine * D + a], q[far * D + a]}, hi[2] = {lo[0], lo[1]};
+    for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        lo[i] = min(lo[i], __shfl_xor(lo[i], o));
+        hi[i] = max(hi[i], __shfl_xor(hi[i], o));
+      }
+    own *= hi[0] - lo[0];
+    all *= hi[1] - lo[1];
+  }
+  return own * 16.0 <= all;  // (false for NaN)
+}
+
 template <int D>
 kdt_status range_packet_launch(const TreeView& v, int leaf, const float* d_q, int64_t nq, float r2,
                                const int32_t* order, int32_t* d_count, uint32_t split_budget,
                                hipStream_t stream, const FillOut* fill = nullptr);
-// The same over a float64 tree (leaves of at most 64 points).
+// The same over a float64 tree (leaves of at most 64 points).  apart: waves whose queries do
+// not lie together (lie_together) are left out.
 template <int D>
 kdt_status range64_packet_launch(const View64& v, int leaf, const double* d_q, int64_t nq,
                                  double r2, const int32_t* order, int32_t* d_count,
-                                 hipStream_t stream, const FillOut* fill = nullptr);
+                                 hipStream_t stream, const FillOut* fill = nullptr,
+                                 bool apart = false);
 // The LDS bytes of a workgroup of that launch.
 size_t range64_packet_lds(int d, int leaf);
 template <int D>
