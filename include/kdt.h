@@ -113,10 +113,10 @@ typedef struct {
                              still running in the launch's tail hands the big
                              subtrees of its stack on to later launches after
                              320 node visits, then every 10; 24 and 24 up to
-                             2^15 queries; counts of up to 2^15 to 2^17 queries
-                             by d and n, d <= 8, take a wave each instead).
-                             > 0: every wave
-                             hands subtrees on after this many visits, in
+                             49152 queries, 96 and 24 up to 2^16; counts of up
+                             to 2^15 to 2^17 queries by d and n, d <= 8, take a
+                             wave each instead).  > 0: every wave hands
+                             subtrees on after this many visits, in
                              every launch.  Results are identical either way;
                              it exists for tuning and for testing the
                              hand-off.  Negative: KDT_EINVAL. */

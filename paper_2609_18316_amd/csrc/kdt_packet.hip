@@ -31,8 +31,16 @@ constexpr int kPWaves = 4;  // waves per workgroup (independent packets)
 constexpr int kRangePasses = 5;
 constexpr uint32_t kRangeBudgetFirst = 320;
 constexpr uint32_t kRangeBudget = 10;
-constexpr int64_t kRangeFewWaves = 512;   // up to here:
+constexpr int64_t kRangeFewWaves = 768;   // up to here:
 constexpr uint32_t kRangeBudgetFew = 24;  // both budgets
+// Between the two, small balls should not hand on and large ones should (float64 counts
+// over trees of 1000 to 8 * 10^6 points, time relative to the few waves' budgets, mean and worst:
+// 40000 balls 1.03 and 1.24 so, 1.15 and 1.59 with the large launches' budgets; 65536 0.96 and 1.16,
+// 1.01 and 1.38; 100000 0.91 and 1.09, 0.90 and 1.24; lists of 65536 balls of 2 of 2^22
+// clustered points 845 us with the few waves', 929 so, 1073; of 131072 balls of 30 of 2^20
+// points, d = 2, 861, 825, 640).
+constexpr int64_t kRangeMidWaves = 1024;  // up to here, above kRangeFewWaves:
+constexpr uint32_t kRangeBudgetMid = 96;  // the first budget; the few waves' later one
 constexpr uint32_t kRangeManyTasks = 300000;  // from here on:
 constexpr uint32_t kRangeManyBudget = 96;     // the later budget
 constexpr uint32_t kRangeTaskCap = 1u << 20;
@@ -453,8 +461,14 @@ static kdt_status count_packet_launch(const typename Q::View& v, int leaf, Q src
   k_zero_tasks<<<1, 64, 0, stream>>>(counts, kRangePasses + kDoneShards);
   // a caller's budget applies to every wave of every launch
   const bool few = waves <= kRangeFewWaves;
-  const uint32_t first = split_budget ? split_budget : few ? kRangeBudgetFew : kRangeBudgetFirst;
-  const uint32_t later = split_budget ? split_budget : few ? kRangeBudgetFew : kRangeBudget;
+  const bool mid = !few && waves <= kRangeMidWaves;
+  const uint32_t first = split_budget ? split_budget
+                         : few        ? kRangeBudgetFew
+                         : mid        ? kRangeBudgetMid
+                                      : kRangeBudgetFirst;
+  const uint32_t later = split_budget ? split_budget
+                         : few || mid ? kRangeBudgetFew
+                                      : kRangeBudget;
   const uint32_t tail_from = split_budget                ? 0u
                              : waves > kRangeTailWaves ? (uint32_t)(waves - kRangeTailWaves)
                                                        : 0u;
