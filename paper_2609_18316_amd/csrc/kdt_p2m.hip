@@ -55,6 +55,8 @@ constexpr int kT = 16;                      // tile edge in cells
 constexpr int kTileCells = kT * kT * kT;    // float64 LDS tile: 32 KiB
 constexpr int64_t kChunk = 4096;            // particles per deposit work item
 constexpr int64_t kChunkMin = 128;          // of small deposits (chunk_of)
+constexpr int kSamples = 64;                // words behind the tile counters: the flag, sums of supports
+constexpr int kSampleOf = 16;               // workgroups per sampled particle
 
 // Lanes that share a particle's support in the SPH passes.  One lane each fills the
 // chip from about 2^20 particles on (2^22 on 160^3: forward and adjoint 1.18 and 0.56 ms;
@@ -71,11 +73,21 @@ void by_group(int64_t n, F&& f) {
     default: f(std::integral_constant<int, 8>());
   }
 }
-// Particles per work item of a deposit of `total` list entries: about 1024 items.
+// Particles per work item of a deposit of `total` list entries in `used` tiles, with about
+// `cells` cells per particle: about 1024 items.
 // A mesh of few tiles otherwise leaves most CUs idle (20000 particles on
-// 28^3, 8 tiles: forward 2430 us with items of 4096, 803 so).
-inline int64_t chunk_of(int64_t total) {
-  return std::min(kChunk, std::max(kChunkMin, total / 1024));
+// 28^3, 8 tiles: forward 2430 us with items of 4096, 803 so).  An item of a split tile costs a
+// tile of partial sums, so the fixed clouds and small supports (below kLight cells) take
+// larger items, and where many tiles share the work, only tiles of more than twice the mean
+// are split (200003 uniform particles on 128^3, us with every tile whole, with about 1024
+// items, and so: NGP 84 / 125 / 84, TSC 138 / 176 / 134, H of 1.5 cells 249 / 284 / 258).
+constexpr double kLight = 64.0;
+inline int64_t chunk_of(int sch, int64_t total, int64_t used, double cells) {
+  const bool light = cells < kLight;
+  const int64_t least[4] = {light ? 2 * kChunkMin : kChunkMin, kChunk, kChunk / 4, kChunk / 8};
+  int64_t chunk = std::max(least[sch], total / 1024);
+  if (light && used >= 256) chunk = std::max(chunk, 2 * total / used);
+  return std::min(kChunk, chunk);
 }
 
 // Scratch slots the deposit keeps on its stream between calls.
@@ -89,6 +101,13 @@ enum : int {
 // Calls without a particle order and at least this many particles order
 // them by home tile first.
 constexpr int64_t kSelfOrderMin = 1 << 16;
+
+// Particles up to which 8 lanes stay with a particle in the first pass: by turns these are
+// fewer than 128 waves, one after the other through 64 particles' supports (1000 particles with
+// the distances to their 32nd neighbours on 28^3 285 us by turns and 163 so, with H of 1.5 cells
+// 97 and 90).  In more, a wave by turns counts 64 particles in the tiles at once instead of 8
+// (20000 clustered particles with H of 1.5 cells on 64^3 250 us, 283 direct).
+constexpr int64_t kDirectRows = int64_t(1) << 13;
 
 inline size_t align256(size_t b) { return (b + 255) / 256 * 256; }
 
@@ -434,8 +453,10 @@ __device__ __forceinline__ bool tile_range(const Particle& p, int t0[3], int t1[
 // counts (one per image and overlapped tile); the validity flag for a
 // particle outside the box or with an invalid h, or for a tree whose
 // deferred finiteness check failed (tree_bad).  The gather's scattered
-// reads, if any, overlap the support sums.
-template <int SCH, int XS, int G>
+// reads, if any, overlap the support sums.  With kDirect each particle has its G lanes for the
+// whole pass and the first of them writes; else a lane has a particle and the lanes of a
+// wave take turns to share their supports.
+template <int SCH, int XS, int G, bool kDirect>
 __global__ __launch_bounds__(kPBlock) void k_p2m_prep(GridDev g, TileGrid tg,
                                                       const float* __restrict__ xin,
                                                       const float* __restrict__ min_,
@@ -446,7 +467,9 @@ __global__ __launch_bounds__(kPBlock) void k_p2m_prep(GridDev g, TileGrid tg,
                                                       float* __restrict__ fbuf,
                                                       uint32_t* __restrict__ tcount,
                                                       int32_t* __restrict__ bad) {
-  const int64_t t = xcd_block<kXcdRunP2M>() * kPBlock + threadIdx.x;
+  const int64_t t = kDirect ? xcd_block<kXcdRunP2M * G>() * (kPBlock / G) + threadIdx.x / G
+                            : xcd_block<kXcdRunP2M>() * kPBlock + threadIdx.x;
+  const bool first = !kDirect || threadIdx.x % G == 0;
   float x[3] = {0.0f, 0.0f, 0.0f}, h = 0.0f, m = 0.0f;
   bool ok = false;
   if (t == 0 && tree_bad && *tree_bad) atomicOr(bad, 1);
@@ -458,7 +481,7 @@ __global__ __launch_bounds__(kPBlock) void k_p2m_prep(GridDev g, TileGrid tg,
     ok = particle_ok<SCH>(g, x, h);
     if (!ok) atomicOr(bad, 1);
     to_unit(g, x, h);
-    P[t] = make_float4(x[0], x[1], x[2], h);
+    if (first) P[t] = make_float4(x[0], x[1], x[2], h);
   }
   // S in float64: a support of 10^5 cells (H near half the mesh) would
   // drift by 1e-5 in float32.  The wave's particles are taken 64 / G at a time, G
@@ -466,13 +489,14 @@ __global__ __launch_bounds__(kPBlock) void k_p2m_prep(GridDev g, TileGrid tg,
   const int lane = lane_id();
   double S = 0.0;
 #pragma unroll 1
-  for (int b = 0; b < G; ++b) {
+  for (int b = 0; b < (kDirect ? 1 : G); ++b) {
     const int src = b * (64 / G) + lane / G;
+    constexpr bool kMove = G > 1 && !kDirect;
     float gx[3], gh = h;
 #pragma unroll
-    for (int a = 0; a < 3; ++a) gx[a] = G > 1 ? __shfl(x[a], src) : x[a];
-    if (G > 1) gh = __shfl(h, src);
-    const bool gok = G > 1 ? __shfl((int)ok, src) != 0 : ok;
+    for (int a = 0; a < 3; ++a) gx[a] = kMove ? __shfl(x[a], src) : x[a];
+    if (kMove) gh = __shfl(h, src);
+    const bool gok = kMove ? __shfl((int)ok, src) != 0 : ok;
     const Images im = images_of<SCH>(g, gx, fmaxf(gh, g.cell));
     double part = 0.0;
     for (int img = 0; gok && img < 8; ++img) {
@@ -483,14 +507,14 @@ __global__ __launch_bounds__(kPBlock) void k_p2m_prep(GridDev g, TileGrid tg,
                           [&](int64_t, int, int, int, float w) { part += (double)w; });
     }
     part = group_sum<G>(part);
-    const double mine = G > 1 ? __shfl(part, (lane - b * (64 / G)) * G & 63) : part;
-    if (lane / (64 / G) == b) S = mine;
+    const double mine = kMove ? __shfl(part, (lane - b * (64 / G)) * G & 63) : part;
+    if (!kMove || lane / (64 / G) == b) S = mine;
   }
   const Images im = images_of<SCH>(g, x, fmaxf(h, g.cell));
   // every lane walks the same image numbers (8 at most), so the tile
   // aggregation below runs with the whole wave
   for (int img = 0; img < 8; ++img) {
-    const bool mine = t < n && (img & ~im.mask) == 0;
+    const bool mine = first && t < n && (img & ~im.mask) == 0;
     if (!__any(mine)) continue;
     Particle p;
     make_image(g, x, h, m, ok && mine, im, img, p);
@@ -502,7 +526,14 @@ __global__ __launch_bounds__(kPBlock) void k_p2m_prep(GridDev g, TileGrid tg,
   }
   // a particle inside the mesh has its own cell centre within
   // sqrt(3)/2 cell <= H, so S > 0
-  if (t < n) fbuf[t] = ok ? (float)((double)m / S) : 0.0f;
+  if (first && t < n) fbuf[t] = ok ? (float)((double)m / S) : 0.0f;
+  // a sample of the supports' sizes, for the host's choice of work items
+  if (SCH == kSph && threadIdx.x == 0 && blockIdx.x % kSampleOf == 0 && ok) {
+    uint32_t box = 1;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) box *= (uint32_t)min(im.hi_c[a] - im.lo_c[a] + 1, 15);
+    atomicAdd(bad + 1 + blockIdx.x / kSampleOf % (kSamples - 1), (int32_t)box);
+  }
 }
 
 // The key of the self-ordering of an unordered call: the tile of the cell
@@ -563,8 +594,9 @@ __global__ __launch_bounds__(kPBlock) void k_p2m_scatter(GridDev g, TileGrid tg,
   }
 }
 
+constexpr int32_t kRunsBit = 1 << 30;  // (above every tile's number)
 struct DepositChunk {
-  int32_t tile;
+  int32_t tile;  // | kRunsBit: each lane takes a run of the entries
   int32_t slot;  // -1: the tile's only chunk, written to the mesh; else its partial
   int64_t begin, end;
 };
@@ -579,7 +611,9 @@ __global__ __launch_bounds__(kPBlock) void k_p2m_tile(GridDev g, TileGrid tg,
                                                       float* __restrict__ mesh,
                                                       double* __restrict__ partial) {
   __shared__ double tile[kTileCells];
-  const DepositChunk ck = chunks[blockIdx.x];
+  DepositChunk ck = chunks[blockIdx.x];
+  const bool runs = SCH == kTsc && (ck.tile & kRunsBit) != 0;
+  ck.tile &= ~kRunsBit;
   const int tz = ck.tile % tg.nt[2], ty = (ck.tile / tg.nt[2]) % tg.nt[1],
             tx = ck.tile / (tg.nt[2] * tg.nt[1]);
   const int lo[3] = {tx * kT, ty * kT, tz * kT};
@@ -592,10 +626,11 @@ __global__ __launch_bounds__(kPBlock) void k_p2m_tile(GridDev g, TileGrid tg,
   // (2^24 particles on 256^3: 3.22 and 2.93 ms); NGP and CIC add too little for that to
   // pay for the scattered reads (1.32 and 1.76, 1.91 and 2.09 ms with runs).
   const int64_t cnt = ck.end - ck.begin;
-  const int64_t per = SCH != kTsc ? 1 : (cnt + kPBlock - 1) / kPBlock;
-  const int64_t first = SCH != kTsc ? ck.begin + threadIdx.x / G : ck.begin + threadIdx.x * per;
-  const int64_t last = SCH != kTsc ? ck.end : min(first + per, ck.end);
-  for (int64_t e = first; e < last; e += SCH != kTsc ? kPBlock / G : 1) {
+  const int64_t per = runs ? (cnt + kPBlock - 1) / kPBlock : 1;
+  const int64_t first = runs ? ck.begin + threadIdx.x * per : ck.begin + threadIdx.x / G;
+  const int64_t last = runs ? min(first + per, ck.end) : ck.end;
+  const int64_t step = runs ? 1 : kPBlock / G;
+  for (int64_t e = first; e < last; e += step) {
     const int32_t code = pairs[e];
     const int64_t t = g.periodic ? (int64_t)((uint32_t)code >> 3) : (int64_t)code;
     const int img = g.periodic ? (code & 7) : 0;
@@ -869,7 +904,8 @@ static kdt_status p2m_forward(int sch, const char* who, Source src, int64_t n,
     kdt_set_error("%s: mesh too large (%lld tiles of %d^3 cells)", who, (long long)n_tiles, kT);
     return KDT_EUNSUPPORTED;
   }
-  if (src.may_self_order && !src.order && n >= kSelfOrderMin) {
+  const bool own = src.may_self_order && !src.order && n >= kSelfOrderMin;
+  if (own) {
     const kdt_status st = self_order(g, grid->n, src.x, n, stream, who, &src.order);
     if (st != KDT_OK) return st;
   }
@@ -891,19 +927,30 @@ static kdt_status p2m_forward(int sch, const char* who, Source src, int64_t n,
   const unsigned gt = (unsigned)((n_tiles + 64 + 255) / 256);
   k_fill_u32<<<gt, 256, 0, stream>>>(tcount, n_tiles + 64, 0u);
   const unsigned gp = (unsigned)((n + kPBlock - 1) / kPBlock);
+  int64_t samples = 0;
   if (n > 0)
     by_scheme(sch, n, [&](auto c, auto group) {
       constexpr int S = decltype(c)::value, G = decltype(group)::value;
-      if (src.xs == 4)
-        k_p2m_prep<S, 4, G><<<gp, kPBlock, 0, stream>>>(g, tg, src.x, src.m, src.h, n, src.order,
-                                                        src.tree_bad, P, fbuf, tcount, bad);
-      else
-        k_p2m_prep<S, 3, G><<<gp, kPBlock, 0, stream>>>(g, tg, src.x, src.m, src.h, n, src.order,
-                                                        src.tree_bad, P, fbuf, tcount, bad);
+      const auto prep = [&](auto direct) {
+        constexpr bool kDirect = decltype(direct)::value;
+        constexpr int64_t per = kDirect ? kPBlock / G : kPBlock;  // particles of a workgroup
+        const unsigned gb = (unsigned)((n + per - 1) / per);
+        samples = (gb + kSampleOf - 1) / kSampleOf;
+        if (src.xs == 4)
+          k_p2m_prep<S, 4, G, kDirect><<<gb, kPBlock, 0, stream>>>(
+              g, tg, src.x, src.m, src.h, n, src.order, src.tree_bad, P, fbuf, tcount, bad);
+        else
+          k_p2m_prep<S, 3, G, kDirect><<<gb, kPBlock, 0, stream>>>(
+              g, tg, src.x, src.m, src.h, n, src.order, src.tree_bad, P, fbuf, tcount, bad);
+      };
+      if constexpr (G == 8) {
+        if (n <= kDirectRows) return prep(std::true_type());
+      }
+      prep(std::false_type());
     });
   // the per-tile counts size the lists: read them back (with the check flag)
-  std::vector<uint32_t> cnt((size_t)n_tiles + 1);
-  hipError_t e = hipMemcpyAsync(cnt.data(), tcount, sizeof(uint32_t) * (n_tiles + 1),
+  std::vector<uint32_t> cnt((size_t)n_tiles + kSamples);
+  hipError_t e = hipMemcpyAsync(cnt.data(), tcount, sizeof(uint32_t) * (n_tiles + kSamples),
                                 hipMemcpyDeviceToHost, stream);
   if (e == hipSuccess) e = hipStreamSynchronize(stream);
   if (e != hipSuccess) {
@@ -925,7 +972,15 @@ static kdt_status p2m_forward(int sch, const char* who, Source src, int64_t n,
     total += cnt[t];
   }
   toff[n_tiles] = total;
-  int64_t chunk = chunk_of(total);
+  int64_t used = 0;
+  for (int64_t t = 0; t < n_tiles; ++t) used += cnt[t] != 0;
+  double cells = sch * sch * sch;
+  if (sch == kSph) {
+    for (int64_t s = 1; s < kSamples; ++s) cells += cnt[n_tiles + s];
+    cells = cells / std::max<double>(1.0, (double)samples) * 0.52;
+  }
+  int64_t chunk = chunk_of(sch, total, used, cells);
+
   auto slots_for = [&](int64_t c) {
     int64_t s = 0;
     for (int64_t t = 0; t < n_tiles; ++t) {
@@ -936,19 +991,23 @@ static kdt_status p2m_forward(int sch, const char* who, Source src, int64_t n,
   };
   while (slots_for(chunk) * (int64_t)sizeof(double) * kTileCells > (int64_t(1) << 30)) chunk *= 2;
   std::vector<DepositChunk> chunks;
+  const auto code = [&](int64_t t) {
+    const bool runs = sch == kTsc && !own && cnt[t] >= 4 * kTileCells;
+    return (int32_t)t | (runs ? kRunsBit : 0);
+  };
   std::vector<SplitTile> split;
   int32_t slots = 0;
   chunks.reserve((size_t)n_tiles);
   for (int64_t t = 0; t < n_tiles; ++t) {
     const int64_t k = std::max<int64_t>(1, (cnt[t] + chunk - 1) / chunk);
     if (k == 1) {
-      chunks.push_back({(int32_t)t, -1, toff[t], toff[t] + cnt[t]});
+      chunks.push_back({code(t), -1, toff[t], toff[t] + cnt[t]});
       continue;
     }
     split.push_back({(int32_t)t, slots, (int32_t)k});
     for (int64_t c = 0; c < k; ++c) {
       const int64_t b = toff[t] + c * chunk;
-      chunks.push_back({(int32_t)t, slots++, b, std::min<int64_t>(b + chunk, toff[t] + cnt[t])});
+      chunks.push_back({code(t), slots++, b, std::min<int64_t>(b + chunk, toff[t] + cnt[t])});
     }
   }
   // largest chunks first, so the long ones do not form the tail of the launch
