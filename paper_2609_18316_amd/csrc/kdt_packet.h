@@ -1064,6 +1064,7 @@ __device__ __forceinline__ int64_t wave_ball(const TreeView& t, const Shape& sh,
     const int m = min(sp, 64);
     uint32_t node = lane < m ? stk[sp - 1 - lane] : 0u;
     sp -= m;
+    KDT_WAVE_VISIT(t, kVisitWaveNodes, m);
     bool whole = (node & kWholeBit) != 0;
     node &= ~kWholeBit;
     float lo[D], hi[D];
@@ -1100,6 +1101,7 @@ __device__ __forceinline__ int64_t wave_ball(const TreeView& t, const Shape& sh,
         rm &= rm - 1;
         const int64_t rb = (uint32_t)__builtin_amdgcn_readlane((int)b, l);
         const int rn = __builtin_amdgcn_readlane((int)n, l);
+        KDT_WAVE_VISIT(t, kVisitWavePoints, rn);
         for (int c = lane; c < rn; c += 64 * kWaveLoads) {
           float x[kWaveLoads][D];
           int32_t id[kWaveLoads];
@@ -1130,6 +1132,8 @@ __device__ __forceinline__ int64_t wave_ball(const TreeView& t, const Shape& sh,
           } else {
             ln[u] = 0u;
           }
+          [[maybe_unused]] const int read = __popcll(__ballot(ln[u] != 0u));
+          KDT_WAVE_VISIT(t, kVisitWavePoints, read);
         }
 #pragma unroll
         for (int u = 0; u < kWaveLeaves; ++u) {
