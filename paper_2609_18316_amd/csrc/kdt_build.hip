@@ -995,10 +995,12 @@ static kdt_status run_build(const Plan& p, const PlanDev& pd, const float* d_pts
   k_lds_subtree<D, W><<<subs, 64 * W, lds_bytes(D, p.sub_max, W), stream>>>(                   \
       pd.subs, pd.sets, w.x[0], w.p[0], w.x[1], w.p[1], tot, p.sub_max, o.box, o.axis, o.split, \
       o.rec, o.perm)
-  if (D <= 4 && subs <= kSubWideMost)
-    KDT_SUBTREE(kSubWide);
-  else
-    KDT_SUBTREE(kSubWaves);
+  bool wide = false;
+  if constexpr (D <= 4) {
+    wide = subs <= kSubWideMost;
+    if (wide) KDT_SUBTREE(kSubWide);
+  }
+  if (!wide) KDT_SUBTREE(kSubWaves);
 #undef KDT_SUBTREE
   KDT_HIP(hipGetLastError());
   return KDT_OK;
@@ -1009,9 +1011,10 @@ static void set_smem_attr(int cap) {
   (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_lds_subtree<D, kSubWaves>),
                             hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)lds_bytes(D, cap, kSubWaves));
-  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_lds_subtree<D, kSubWide>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)lds_bytes(D, cap, kSubWide));
+  if constexpr (D <= 4)
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_lds_subtree<D, kSubWide>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize,
+                              (int)lds_bytes(D, cap, kSubWide));
 }
 
 hipError_t pool_alloc(void** ptr, size_t bytes, hipStream_t stream) {

@@ -540,9 +540,6 @@ struct OpenMetric {
   }
 };
 
-#ifndef KNN_SM
-#define KNN_SM i
-#endif
 // What a per-lane kNN traversal measures: the float32 points of a tree
 // under a metric.
 template <int D, class Metric>
