@@ -728,11 +728,16 @@ __device__ __forceinline__ void leaf_offer(const Space& sp, int32_t b, int cnt, 
       }
     } else {
       const auto* r = sp.run(c);
-      const int all = min(max(least - o, 0), B);  // every lane has these
+      int all = 0;
+      // (the leftovers of a merge are few: 2^24 clustered points, d = 3, k = 32 5.20 ms, with
+      // this loop 5.23; in 4 dimensions 400000 points' 20th distances 774 us without it, 625)
+      if constexpr (!kMerge || D > 3) {
+        all = min(max(least - o, 0), B);  // every lane has these
 #pragma unroll kAhead
-      for (int i = 0; i < all; ++i) {
-        int32_t id = 0;
-        mask |= (uint32_t)(sp.dist(r, c, i, p, id) <= w) << i;
+        for (int i = 0; i < all; ++i) {
+          int32_t id = 0;
+          mask |= (uint32_t)(sp.dist(r, c, i, p, id) <= w) << i;
+        }
       }
 #pragma unroll 1
       for (int i = all; i < m; ++i) {
