@@ -112,9 +112,11 @@ typedef struct {
     int32_t split_budget; /* Ball counts with traversal 2.  0: default (a wave
                              still running in the launch's tail hands the big
                              subtrees of its stack on to later launches after
-                             320 node visits, then every 10; 24 and 24 up to
-                             49152 queries, 96 and 24 up to 2^16; counts of up
-                             to 2^15 to 2^17 queries by d and n, d <= 8, take a
+                             320 node visits, then every 10; 24 and 24 in
+                             lists of up to 2^17 and counts of up to 49152
+                             queries, 96 and 24 in counts of up to 2^16, float64
+                             2^17; counts of up to 2^15 to 2^17 queries by d
+                             and n, d <= 8, float32, take a
                              wave each instead).  > 0: every wave hands
                              subtrees on after this many visits, in
                              every launch.  Results are identical either way;

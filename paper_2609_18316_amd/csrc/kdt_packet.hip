@@ -31,16 +31,19 @@ constexpr int kPWaves = 4;  // waves per workgroup (independent packets)
 constexpr int kRangePasses = 5;
 constexpr uint32_t kRangeBudgetFirst = 320;
 constexpr uint32_t kRangeBudget = 10;
-constexpr int64_t kRangeFewWaves = 768;   // up to here:
-constexpr uint32_t kRangeBudgetFew = 24;  // both budgets
-// Between the two, small balls should not hand on and large ones should (float64 counts
-// over trees of 1000 to 8 * 10^6 points, time relative to the few waves' budgets, mean and worst:
-// 40000 balls 1.03 and 1.24 so, 1.15 and 1.59 with the large launches' budgets; 65536 0.96 and 1.16,
-// 1.01 and 1.38; 100000 0.91 and 1.09, 0.90 and 1.24; lists of 65536 balls of 2 of 2^22
-// clustered points 845 us with the few waves', 929 so, 1073; of 131072 balls of 30 of 2^20
-// points, d = 2, 861, 825, 640).
-constexpr int64_t kRangeMidWaves = 1024;  // up to here, above kRangeFewWaves:
-constexpr uint32_t kRangeBudgetMid = 96;  // the first budget; the few waves' later one
+constexpr uint32_t kRangeBudgetFew = 24;  // both budgets of launches of few waves:
+constexpr int64_t kRangeFewWaves = 768;       // counts
+constexpr int64_t kRangeFewWavesList = 2048;  // lists
+// Counts of up to so many waves more: small balls should not hand on and large ones should
+// (float64 counts over trees of 1000 to 8 * 10^6 points, time relative to the few waves' budgets,
+// mean and worst: 40000 balls 1.03 and 1.24 so, 1.15 and 1.59 with the large launches' budgets;
+// 65536 0.96 and 1.16, 1.01 and 1.38; 131072 0.86 and 1.08, 0.81 and 1.17).  Lists keep the
+// few waves' budgets: their fill waits for single waves more than it loses by handing on (75931
+// balls of 12 of 134189 clustered points 1.08 ms, 1.28 so and 1.43; of 131072 balls of 30 of
+// 130000 uniform points the order is the other, up to 1.3).
+constexpr int64_t kRangeMidWaves = 1024;
+constexpr int64_t kRangeMidWaves64 = 2048;  // float64, which has no search by a wave per ball
+constexpr uint32_t kRangeBudgetMid = 96;    // the first budget; the few waves' later one
 constexpr uint32_t kRangeManyTasks = 300000;  // from here on:
 constexpr uint32_t kRangeManyBudget = 96;     // the later budget
 constexpr uint32_t kRangeTaskCap = 1u << 20;
@@ -63,12 +66,15 @@ constexpr int64_t kRangeTailWaves = 4096;
 // points 78 and 14; 65536 of 65536 169 and 107; 131072 of 4096 points 74 and 142, of 65536 120
 // and 196, of 2^20 371 and 255; d = 2, 65536 of 65536 points 66 and 95, 131072 of 2^20 146 and
 // 237; d = 4, 131072 of 65536 points 302 and 221; d = 8, 65536 of 300 points 77 and 87, 131072
-// of 1000 139 and 192, of 16384 858 and 376.
+// of 1000 139 and 192, of 16384 858 and 376.  Where the two are close the points decide: 75000
+// balls of 130000 uniform points 160 and 130, of clustered ones 277 and 132, 131072 140 and 219,
+// 281 and 221.
 inline int64_t wave_rows(int d, int64_t n) {
   constexpr int64_t rows = int64_t(1) << 16;
   if (d == 2) return n >= (1 << 18) ? rows : rows / 2;
   const int64_t large = d == 3 ? 1 << 18 : d == 4 ? 1 << 16 : 1 << 12;
-  return n >= large ? 2 * rows : d == 8 ? rows / 2 : rows;
+  if (n >= large) return 2 * rows;
+  return d == 8 ? rows / 2 : d == 3 && n >= rows ? rows + rows / 4 : rows;
 }
 // The balls of large k hold many points: the 7 counts of 50021 balls of 2^23 clustered
 // points took 4.0 ms and take 1.05; kNN with k = 100, 262000 queries 4.86 and 3.94 ms,
@@ -460,8 +466,10 @@ static kdt_status count_packet_launch(const typename Q::View& v, int leaf, Q src
   }
   k_zero_tasks<<<1, 64, 0, stream>>>(counts, kRangePasses + kDoneShards);
   // a caller's budget applies to every wave of every launch
-  const bool few = waves <= kRangeFewWaves;
-  const bool mid = !few && waves <= kRangeMidWaves;
+  constexpr int64_t most =
+      std::is_same_v<typename Q::View, View64> ? kRangeMidWaves64 : kRangeMidWaves;
+  const bool few = waves <= (fill ? kRangeFewWavesList : kRangeFewWaves);
+  const bool mid = !fill && !few && waves <= most;
   const uint32_t first = split_budget ? split_budget
                          : few        ? kRangeBudgetFew
                          : mid        ? kRangeBudgetMid

@@ -14,8 +14,8 @@ ROWS = 1 << 16
 
 
 @pytest.mark.parametrize("d,n,nq", [
-    (2, (1 << 18) - 1, ROWS // 2), (2, 1 << 18, ROWS), (3, (1 << 18) - 1, ROWS),
-    (3, 1 << 18, 2 * ROWS), (4, ROWS - 1, ROWS), (4, ROWS, 2 * ROWS), (8, 4095, ROWS // 2),
+    (2, (1 << 18) - 1, ROWS // 2), (2, 1 << 18, ROWS), (3, ROWS - 1, ROWS),
+    (3, (1 << 18) - 1, ROWS + ROWS // 4), (3, 1 << 18, 2 * ROWS), (4, ROWS - 1, ROWS), (4, ROWS, 2 * ROWS), (8, 4095, ROWS // 2),
     (8, 4096, 2 * ROWS), (3, 1, ROWS), (16, 300, ROWS // 2),
 ])
 def test_counts_by_launch_size(d, n, nq):
