@@ -128,16 +128,6 @@ struct HipBlocks {
 // never destroyed, as g_scratch
 BlockCache<HipBlocks>& g_blocks = *new BlockCache<HipBlocks>();
 
-bool capturing(hipStream_t stream) {
-  if (!stream) return false;  // the null stream cannot be captured
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(stream, &cap) != hipSuccess) {
-    (void)hipGetLastError();
-    return true;
-  }
-  return cap != hipStreamCaptureStatusNone;
-}
-
 bool memory_should_fail() {
   int64_t v = g_fail_memory.load();
   while (v > 0) {
@@ -162,13 +152,23 @@ hipError_t with_all_memory(F&& get) {
 }
 }  // namespace
 
+bool stream_capturing(hipStream_t stream) {
+  if (!stream) return false;  // the null stream cannot be captured
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &cap) != hipSuccess) {
+    (void)hipGetLastError();
+    return true;
+  }
+  return cap != hipStreamCaptureStatusNone;
+}
+
 // Blocks up to kKeepBlock are kept (kdt_blocks.h); the pool serves the rest, and two more
 // cases: a stream under capture, whose graph has to own its memory, and the per-thread
 // default stream, one handle for as many streams as there are threads.
 hipError_t dev_alloc(void** ptr, size_t bytes, hipStream_t stream) {
   if (alloc_should_fail()) return hipErrorOutOfMemory;
   int dev = 0;
-  if (capturing(stream)) return pool_alloc(ptr, bytes, stream);
+  if (stream_capturing(stream)) return pool_alloc(ptr, bytes, stream);
   const bool keep = bytes <= kKeepBlock && stream != hipStreamPerThread &&
                     hipGetDevice(&dev) == hipSuccess;
   if (keep) {
@@ -182,7 +182,7 @@ hipError_t dev_alloc(void** ptr, size_t bytes, hipStream_t stream) {
 }
 
 void dev_free(void* const* ptrs, size_t n, hipStream_t stream) {
-  g_blocks.give(ptrs, n, stream, !capturing(stream));
+  g_blocks.give(ptrs, n, stream, !stream_capturing(stream));
 }
 void dev_free(void* ptr, hipStream_t stream) { dev_free(&ptr, 1, stream); }
 

@@ -262,6 +262,7 @@ kdt_status build_launch(const Plan& p, const PlanDev& pd, const float* d_pts,
 hipError_t dev_alloc(void** ptr, size_t bytes, hipStream_t stream);
 void dev_free(void* ptr, hipStream_t stream);
 void dev_free(void* const* ptrs, size_t n, hipStream_t stream);  // (NULL entries are skipped)
+bool stream_capturing(hipStream_t stream);  // false for the null stream
 // hipMalloc for memory that no stream owns; like dev_alloc, it asks again after the kept blocks
 // went back where memory does not suffice.
 hipError_t plain_alloc(void** ptr, size_t bytes);

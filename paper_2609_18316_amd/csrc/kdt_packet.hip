@@ -69,6 +69,7 @@ constexpr int64_t kRangeTailWaves = 4096;
 // of 1000 139 and 192, of 16384 858 and 376.  Where the two are close the points decide: 75000
 // balls of 130000 uniform points 160 and 130, of clustered ones 277 and 132, 131072 140 and 219,
 // 281 and 221.
+constexpr int64_t kWaveRowsMost = int64_t(1) << 17;
 inline int64_t wave_rows(int d, int64_t n) {
   constexpr int64_t rows = int64_t(1) << 16;
   if (d == 2) return n >= (1 << 18) ? rows : rows / 2;
@@ -434,8 +435,9 @@ static kdt_status count_packet_launch(const typename Q::View& v, int leaf, Q src
                                       const int32_t* order, int32_t* d_count,
                                       uint32_t split_budget, hipStream_t stream,
                                       const char* who, const FillOut* fill = nullptr) {
-  if constexpr (std::is_same_v<typename Q::View, TreeView> && D <= 8) {
-    if (!fill && split_budget == 0 && nq <= (Q::kLarge ? kWaveRowsLarge : wave_rows(D, v.n))) {
+  constexpr bool kByWave = std::is_same_v<typename Q::View, TreeView> && D <= 8;
+  [[maybe_unused]] const auto by_wave = [&]() -> kdt_status {
+    if constexpr (kByWave) {
       int cap = 0;
       const TreeView w = coarse_view(v, leaf, kWaveLeafCap, &cap);
       const size_t slice = wave_ball_bytes(w.levels);
@@ -446,9 +448,14 @@ static kdt_status count_packet_launch(const typename Q::View& v, int leaf, Q src
         kdt_set_error("%s: packet kernel launch failed", who);
         return KDT_EDEVICE;
       }
-      return KDT_OK;
     }
-  }
+    return KDT_OK;
+  };
+  // A wave per shape needs no scratch: so, up to kWaveRowsMost, also where there is none left
+  // for the task lists, and in a graph, which would own them.
+  const bool may = kByWave && !fill && split_budget == 0 &&
+                   nq <= (Q::kLarge ? kWaveRowsLarge : kWaveRowsMost);
+  if (may && (Q::kLarge || nq <= wave_rows(D, v.n) || stream_capturing(stream))) return by_wave();
   const unsigned grid = (unsigned)((nq + 64 * kPWaves - 1) / (64 * kPWaves));
   const size_t smem = count_wave_bytes<D, Q>(leaf) * kPWaves;
   PoolBuffers buf(stream);
@@ -461,6 +468,7 @@ static kdt_status count_packet_launch(const typename Q::View& v, int leaf, Q src
   // finished-wave counters
   if (!buf.get(&tasks, (size_t)cap * (kRangePasses - 1)) ||
       !buf.get(&counts, kRangePasses + kDoneShards)) {
+    if (may) return by_wave();
     kdt_set_error("%s: device allocation failed for the task lists", who);
     return KDT_ENOMEM;
   }

@@ -3,6 +3,7 @@ ball is searched by a wave of its own, and a launch with more hand-offs than the
 wants: equal to one traversal per lane, and a sample to the oracle."""
 import numpy as np
 import pytest
+import torch
 
 import oracle
 from paper_2609_18316_amd import kdt
@@ -46,3 +47,31 @@ def test_counts_with_many_hand_offs():
     np.testing.assert_array_equal(got[some], oracle.range_brute(x, q[some], 0.3))
     # a budget for every wave: no rule on the number of tasks
     np.testing.assert_array_equal(got, to_host(t.range(to_dev(q), 0.3, split_budget=400)))
+
+
+@pytest.mark.parametrize("d", (2, 3))
+def test_counts_without_scratch(d):
+    """Launches just above that line need no memory where there is none, nor in a graph."""
+    dev()
+    rng = np.random.Generator(np.random.PCG64(d))
+    x = to_dev(rng.random((2000, d)).astype(np.float32))
+    q = [to_dev(rng.random((ROWS + 1, d)).astype(np.float32)) for _ in range(4)]
+    t = kdt.build(x, leaf_size=24)
+    want = [to_host(t.range(p, 0.1, sort_queries=False)) for p in q]
+    say(f"counts without scratch d={d}")
+    try:
+        kdt.fail_alloc(1)
+        got = to_host(t.range(q[0], 0.1, sort_queries=False))
+    finally:
+        kdt.fail_alloc(0)
+    np.testing.assert_array_equal(got, want[0])
+    stream, graph, into = torch.cuda.Stream(), torch.cuda.CUDAGraph(), q[0].clone()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=stream):
+        out = t.range(into, 0.1, sort_queries=False)
+    for p, w in zip(q, want):
+        into.copy_(p)
+        graph.replay()
+        np.testing.assert_array_equal(to_host(out), w)
+        np.testing.assert_array_equal(to_host(t.range(p, 0.1, sort_queries=False)), w)
+    t.close()
