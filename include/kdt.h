@@ -115,12 +115,11 @@ typedef struct {
                              320 node visits, then every 10; 24 and 24 in
                              lists of up to 2^17 and counts of up to 49152
                              queries, 96 and 24 in counts of up to 2^16, float64
-                             2^17; counts of up to 2^15 to 2^17 queries by d
-                             and n, d <= 8, float32, take a
-                             wave each instead).  > 0: every wave hands
-                             subtrees on after this many visits, in
-                             every launch.  Results are identical either way;
-                             it exists for tuning and for testing the
+                             2^17; float32 counts of up to 2^15 to 2^17 queries
+                             by d and n, d <= 8, take a wave each instead).
+                             > 0: every wave hands subtrees on after this many
+                             visits, in every launch.  Results are identical
+                             either way; it exists for tuning and for testing the
                              hand-off.  Negative: KDT_EINVAL. */
     const float *period;  /* NULL: open boundaries.  Else a host array of d
                              periods L_a (finite, > 0): kdt_knn and kdt_range
@@ -595,9 +594,10 @@ const int32_t *kdt_tree_perm(const kdt_tree *tree);
  * indices: d_idx / d_d2 [total][k], d_labels [total].  Results are identical
  * to kdt_build + kdt_knn(NULL) + kdt_fof on each set.
  * use_graph = 1: the batched pipeline (forest build whose level kernels cover
- *   every set, persistent work-queue kNN and grouping kernels) is captured into
- *   a hipGraph on the first call and replayed; a call with different pointers
- *   captures again.  Nothing is allocated per call.
+ *   every set, kNN with a wave per 64 points of a set, the grouping and the
+ *   kNN of d > 4 as persistent work queues) is captured into a hipGraph on the
+ *   first call and replayed; a call with different pointers captures again.
+ *   Nothing is allocated per call.
  * use_graph = 2: the same batched kernels launched eagerly (no graph).
  * use_graph = 0: the per-set baseline -- kdt_build, kdt_knn and kdt_fof called
  *   once per set, eagerly (waits on `stream` to read d_l).
